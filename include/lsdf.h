@@ -356,7 +356,7 @@ int lsdf_robot_sdf_build_frnn(const float* link_T, int32_t C, int32_t L, const l
 /* ---- link SDF construction -------------------------------------------------
  * Sec. III-A: each link's signed distance field is computed once, offline,
  * on a grid in the link's own frame.  The paper does not say how; this call
- * uses the brute-force exact signed distance to a closed triangle mesh.
+ * uses the exact signed distance to a closed triangle mesh.
  *   verts       device float [nv][3] vertices in the link frame
  *   tris        device int32 [nt][3] triangles, outward (counter-clockwise)
  *   comp_first  host int32 [ncomp+1]: triangles [comp_first[k],
@@ -370,6 +370,13 @@ int lsdf_robot_sdf_build_frnn(const float* link_T, int32_t C, int32_t L, const l
 int lsdf_build_link_sdf(const float* verts, int32_t nv, const int32_t* tris, int32_t nt,
                         const int32_t* comp_first, int32_t ncomp, const lsdf_grid* desc,
                         void* grid_buf, void* stream);
+
+/* The same for n links (1 <= n <= LSDF_MAX_LINKS) in one launch: element i of
+ * each host array is link i's argument of lsdf_build_link_sdf (comp_first[i]
+ * may be NULL), grids [n] its descriptor.  Same values. */
+int lsdf_build_link_sdfs(int32_t n, const float* const* verts, const int32_t* nv, const int32_t* const* tris,
+                         const int32_t* nt, const int32_t* const* comp_first, const int32_t* ncomp,
+                         const lsdf_grid* grids, void* grid_buf, void* stream);
 
 /* ---- learned per-link SDF surrogate ---------------------------------------
  * An extension of the method (not in the paper): per link, a small network
@@ -467,12 +474,20 @@ int lsdf_mlp_train_step(float* params, float* adam_m, float* adam_v, int64_t t, 
 
 /* Training labels at N link-frame points of one link: the grid value
  * (lsdf_query_min_distance's arithmetic, identity pose) inside the grid box,
- * the exact signed distance to the mesh outside it (brute force, as in
+ * the exact signed distance to the mesh outside it (as in
  * lsdf_build_link_sdf).  Arguments as in lsdf_build_link_sdf; points device
  * [N][3], out device [N]. */
 int lsdf_sdf_labels(const float* verts, int32_t nv, const int32_t* tris, int32_t nt, const int32_t* comp_first,
                     int32_t ncomp, const lsdf_grid* desc, const void* grid_buf, const float* points, int64_t N,
                     float* out, void* stream);
+
+/* The same for n links (1 <= n <= LSDF_MAX_LINKS) in one launch: element i of
+ * each host array is link i's argument of lsdf_sdf_labels, each link with N
+ * points; the grids share a dtype.  Same values. */
+int lsdf_sdf_labels_links(int32_t n, const float* const* verts, const int32_t* nv, const int32_t* const* tris,
+                          const int32_t* nt, const int32_t* const* comp_first, const int32_t* ncomp,
+                          const lsdf_grid* grids, const void* grid_buf, const float* const* points, int64_t N,
+                          float* const* out, void* stream);
 
 /* Measurement aid, not part of the query path: `threads` threads each take
  * `iters` random cells of an n^3 FP32 grid (device, n^3 floats, x fastest,

@@ -40,13 +40,13 @@ BOUND_QUANTUM = 0.01
 
 def labels_for_samples(meshes, grids: lsdf.GridSet, samples: torch.Tensor) -> torch.Tensor:
     """Labels [L][N]: grid value inside each link's box, exact mesh distance
-    outside (lsdf_sdf_labels), for link-frame samples [L][N][3]."""
+    outside (lsdf_sdf_labels_links, one launch), for link-frame samples
+    [L][N][3]."""
     L, N = int(samples.shape[0]), int(samples.shape[1])
     out = torch.empty((L, N), dtype=torch.float32, device=samples.device)
-    for i, m in enumerate(meshes):
-        v = torch.as_tensor(np.asarray(m.verts, dtype=np.float32), device=samples.device)
-        t = torch.as_tensor(np.asarray(m.tris, dtype=np.int32), device=samples.device)
-        lsdf.sdf_labels(v, t, m.comp_first, grids, i, samples[i], out=out[i])
+    meshes = list(meshes)
+    if meshes:
+        lsdf.sdf_labels_links(meshes, grids, samples, out)
     return out
 
 

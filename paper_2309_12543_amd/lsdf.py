@@ -145,6 +145,11 @@ def load_library():
     lib.lsdf_build_link_sdf.restype = ct.c_int
     lib.lsdf_build_link_sdf.argtypes = [vp, i32, vp, i32, ct.POINTER(ct.c_int32), i32, ct.POINTER(lsdf_grid),
                                         vp, vp]
+    vpp, ip = ct.POINTER(vp), ct.POINTER(i32)
+    lib.lsdf_build_link_sdfs.restype = ct.c_int
+    lib.lsdf_build_link_sdfs.argtypes = [i32, vpp, ip, vpp, ip, vpp, ip, ct.POINTER(lsdf_grid), vp, vp]
+    lib.lsdf_sdf_labels_links.restype = ct.c_int
+    lib.lsdf_sdf_labels_links.argtypes = [i32, vpp, ip, vpp, ip, vpp, ip, ct.POINTER(lsdf_grid), vp, vpp, i64, vpp, vp]
     fp = ct.POINTER(ct.c_float)
     dom = ct.POINTER(lsdf_mlp_domain)
     lib.lsdf_mlp_eval.restype = ct.c_int
@@ -696,13 +701,42 @@ def build_link_sdf(verts: torch.Tensor, tris: torch.Tensor, comp_first, grids: G
                                    grids.buf.data_ptr(), _stream_handle(stream, verts.device)))
 
 
+def upload_meshes(meshes, device, stream=None):
+    """Host meshes in one device buffer (one copy): the argument arrays of
+    the calls that take several links (vertices, triangles and parts), and
+    what has to stay alive until the call returns.  The buffer itself is kept
+    until the work on ``stream`` (the current one when none is given) is done."""
+    n = len(meshes)
+    verts = [np.ascontiguousarray(m.verts, dtype=np.float32) for m in meshes]
+    tris = [np.ascontiguousarray(m.tris, dtype=np.int32) for m in meshes]
+    for v, t in zip(verts, tris):
+        if v.ndim != 2 or v.shape[1] != 3 or t.ndim != 2 or t.shape[1] != 3:
+            raise ValueError("verts must be [nv][3] and tris [nt][3]")
+    flat = np.concatenate([a.reshape(-1).view(np.int32) for a in verts + tris])
+    buf = torch.as_tensor(flat, device=device)
+    if stream is not None:
+        buf.record_stream(stream)
+    at = buf.data_ptr() + 4 * np.concatenate([[0], np.cumsum([a.size for a in verts + tris])[:-1]]).astype(np.int64)
+    comps = [None if m.comp_first is None else np.ascontiguousarray(np.asarray(m.comp_first, dtype=np.int32))
+             for m in meshes]
+    vpn, in_ = ct.c_void_p * n, ct.c_int32 * n
+    args = (n, vpn(*[int(x) for x in at[:n]]), in_(*[v.shape[0] for v in verts]), vpn(*[int(x) for x in at[n:]]),
+            in_(*[t.shape[0] for t in tris]), vpn(*[None if c is None else c.ctypes.data for c in comps]),
+            in_(*[0 if c is None else c.shape[0] - 1 for c in comps]))
+    return args, (buf, comps)
+
+
 def build_robot_grids(meshes, lo, hi, n, device="cuda", stream=None, dtype=torch.float32) -> GridSet:
-    """GridSet with every link's SDF built on the GPU from its mesh."""
+    """GridSet with every link's SDF built on the GPU from its mesh, in one
+    launch (lsdf_build_link_sdfs)."""
     gs = GridSet(lo, hi, n, device=device, dtype=dtype)
-    for i, m in enumerate(meshes):
-        v = torch.as_tensor(np.asarray(m.verts, dtype=np.float32), device=device)
-        t = torch.as_tensor(np.asarray(m.tris, dtype=np.int32), device=device)
-        build_link_sdf(v, t, m.comp_first, gs, i, stream=stream)
+    meshes = list(meshes)
+    if meshes:
+        if len(meshes) > gs.L:
+            raise IndexError(f"{len(meshes)} meshes for {gs.L} grids")
+        args, keep = upload_meshes(meshes, device, stream)
+        _check(load_library().lsdf_build_link_sdfs(*args, gs.desc, gs.buf.data_ptr(),
+                                                   _stream_handle(stream, gs.buf.device)))
     return gs
 
 
@@ -872,6 +906,23 @@ def sdf_labels(verts: torch.Tensor, tris: torch.Tensor, comp_first, grids: GridS
     _check(lib.lsdf_sdf_labels(verts.data_ptr(), int(verts.shape[0]), tris.data_ptr(), int(tris.shape[0]), cf_p, ncomp,
                                ct.pointer(grids.desc[index]), grids.buf.data_ptr(),
                                points.data_ptr() if N else None, N, out.data_ptr(), _stream_handle(stream, points.device)))
+    return out
+
+
+def sdf_labels_links(meshes, grids: GridSet, samples: torch.Tensor, out: torch.Tensor, stream=None) -> torch.Tensor:
+    """Training labels of the first len(meshes) links at their samples
+    [L][N][3] into out [L][N], in one launch (lsdf_sdf_labels_links)."""
+    n, N = len(meshes), int(samples.shape[1])
+    for i in range(n):
+        _require(samples[i], "points", torch.float32, (N, 3))
+        _require(out[i], "out", torch.float32, (N,))
+    if n > grids.L:
+        raise IndexError(f"{n} meshes for {grids.L} grids")
+    args, keep = upload_meshes(meshes, samples.device, stream)
+    ptrs = ct.c_void_p * n
+    _check(load_library().lsdf_sdf_labels_links(
+        *args, grids.desc, grids.buf.data_ptr(), ptrs(*[samples[i].data_ptr() if N else None for i in range(n)]), N,
+        ptrs(*[out[i].data_ptr() for i in range(n)]), _stream_handle(stream, samples.device)))
     return out
 
 
