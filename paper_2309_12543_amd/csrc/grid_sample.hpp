@@ -95,6 +95,18 @@ __device__ inline GridMap grid_map(const LinkGrid& lg, const float* T) {
     return g;
 }
 
+// Grid value at centred grid coordinates known to be inside the box.
+template <int DT>
+__device__ inline float cell_value(const typename GridT<DT>::T* __restrict__ G, const LinkGrid& lg, float v0, float v1,
+                                   float v2) {
+    const Cell cl = locate(lg, v0, v1, v2);
+    const typename GridT<DT>::T* cp = G + cl.idx;
+    const int nx = lg.n[0], nxy = lg.n[0] * lg.n[1];
+    using E = GridT<DT>;
+    return interpolate(E::get(cp, 0), E::get(cp, 1), E::get(cp, nx), E::get(cp, nx + 1), E::get(cp, nxy),
+                       E::get(cp, nxy + 1), E::get(cp, nxy + nx), E::get(cp, nxy + nx + 1), cl);
+}
+
 // Grid value of link-frame or world point x through map gm, +inf outside.
 // G points at the link's first element (storage type DT).
 template <bool CUBIC, int DT = LSDF_F32>
@@ -103,13 +115,7 @@ __device__ inline float sample_or_inf(const typename GridT<DT>::T* __restrict__ 
     const float v0 = fmaf(gm.m00, x, fmaf(gm.m01, y, fmaf(gm.m02, z, gm.w0)));
     const float v1 = fmaf(gm.m10, x, fmaf(gm.m11, y, fmaf(gm.m12, z, gm.w1)));
     const float v2 = fmaf(gm.m20, x, fmaf(gm.m21, y, fmaf(gm.m22, z, gm.w2)));
-    if (!inside<CUBIC>(lg, v0, v1, v2)) return INFINITY;
-    const Cell cl = locate(lg, v0, v1, v2);
-    const typename GridT<DT>::T* cp = G + cl.idx;
-    const int nx = lg.n[0], nxy = lg.n[0] * lg.n[1];
-    using E = GridT<DT>;
-    return interpolate(E::get(cp, 0), E::get(cp, 1), E::get(cp, nx), E::get(cp, nx + 1), E::get(cp, nxy),
-                       E::get(cp, nxy + 1), E::get(cp, nxy + nx), E::get(cp, nxy + nx + 1), cl);
+    return inside<CUBIC>(lg, v0, v1, v2) ? cell_value<DT>(G, lg, v0, v1, v2) : INFINITY;
 }
 
 }  // namespace lsdf

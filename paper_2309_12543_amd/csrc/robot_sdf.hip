@@ -6,10 +6,10 @@
 // It is kept here as the comparator of the per-point query: heavy
 // preparation and C x V voxels of memory against a trivial runtime.
 //
-// Build (one thread per environment voxel column of 32, or of 8 for the
-// network build, voxels x fastest,
-// so every store is coalesced and each voxel is written exactly once,
-// without atomics):
+// Build: every value is first set to +inf at full store width; then, per
+// (configuration, link), only the voxels whose centre can lie in the link's
+// grid box are sampled and take an atomic minimum (about 1 in 1,000 of a
+// configuration's 2 million at 128^3).
 //   * link i's block at configuration c covers voxels k .. k + 2m - 1 per
 //     axis, with k from the alignment of Eq. 1-3 (computed in double from
 //     the link origin: T_O = t - lo, k = round(T_O / r) - m) and m the
@@ -22,6 +22,10 @@
 //     holds the centre.  The centre is lo + (v + 1/2) r (double, rounded
 //     once to float) and the interpolant uses the plain query's arithmetic,
 //     so each value is bit-identical to the plain query at that point.
+// Bound by the HBM writes of the +inf fill.  200 configurations over 128^3
+// voxels (1.68 GB): 472 us with one thread per voxel column that tested every
+// link and stored 256 B a wave; 243 us of fill and 66 us of samples (gathers and
+// HBM atomics in about equal parts) now.
 // Runtime: zero an occupancy bitmap and a counter; voxelise the points
 // (floor((x - lo) / r) in double), keeping the first point of each voxel
 // in a list of distinct occupied voxels; one workgroup per configuration
@@ -36,9 +40,10 @@ using lsdf::GridT;
 using lsdf::LinkGrid;
 
 constexpr int kBlock = 256;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-struct LinkBlock {   // per (configuration, link): block corner and grid map
-    int32_t k[3];
+struct LinkBlock {   // per (configuration, link): the voxels to look at and the grid map
+    uint32_t range[3];   // first voxel and one past the last per axis, 16 bits each
     int32_t pad;
     lsdf::GridMap gm;
 };
@@ -56,6 +61,11 @@ struct BuildArgs {
     float* rs;                       // [C][n_z][n_y][n_x]
 };
 
+// The voxels of the environment link i's block covers at configuration c, cut
+// to those whose centre can lie in the link's grid box: the box's corners are
+// mapped back to the world with the inverse of the grid map, the box widened by
+// 1e-3 + 1e-5 half + 1e-4 |w| grid steps, far beyond the FP32 rounding of a mapped centre.
+// A map with no sound inverse (no pose of a rigid link) keeps the whole block.
 __global__ __launch_bounds__(kBlock) void align_kernel(BuildArgs a) {
     const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (t >= (int64_t)a.C * a.L) return;
@@ -63,86 +73,112 @@ __global__ __launch_bounds__(kBlock) void align_kernel(BuildArgs a) {
     const LinkGrid& lg = a.link[i];
     const float* T = a.link_T + t * 12;
     LinkBlock b{};
-    // Eq. 1-2: T_O = t - lo, k = round(T_O / r) - m
-    const float tr[3] = {T[3], T[7], T[11]};
-#pragma unroll
-    for (int ax = 0; ax < 3; ++ax) b.k[ax] = (int32_t)rint(((double)tr[ax] - a.lo[ax]) / a.r) - a.halfw[i];
     // the plain query's world-to-grid map of this pose (the transformation
     // of Eq. 4 with the grid scaling folded in)
     b.gm = lsdf::grid_map(lg, T);
+    const double m[3][3] = {{b.gm.m00, b.gm.m01, b.gm.m02}, {b.gm.m10, b.gm.m11, b.gm.m12}, {b.gm.m20, b.gm.m21, b.gm.m22}};
+    const double w[3] = {b.gm.w0, b.gm.w1, b.gm.w2};
+    double adj[3][3], norm = 0.0;   // adj = det m^-1
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const int r1 = (c + 1) % 3, r2 = (c + 2) % 3, c1 = (r + 1) % 3, c2 = (r + 2) % 3;
+            adj[r][c] = m[r1][c1] * m[r2][c2] - m[r1][c2] * m[r2][c1];
+            norm = fmax(norm, fabs(m[r][c]));
+        }
+    const double det = m[0][0] * adj[0][0] + m[0][1] * adj[1][0] + m[0][2] * adj[2][0];
+    // (the inverse's rounding, about 1e-16 norm^3 / det, stays below the widening)
+    const bool sound = fabs(det) > 1e-6 * norm * norm * norm;
+    const float tr[3] = {T[3], T[7], T[11]};
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax) {
+        // Eq. 1-2: T_O = t - lo, k = round(T_O / r) - m
+        const int32_t k = (int32_t)rint(((double)tr[ax] - a.lo[ax]) / a.r) - a.halfw[i];
+        int64_t lo = k, hi = (int64_t)k + 2 * a.halfw[i];
+        if (sound) {
+            double c = 0.0, e = 0.0;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                c -= adj[ax][q] / det * w[q];
+                e += fabs(adj[ax][q] / det) * ((double)lg.half[q] * (1.0 + 1e-5) + 1e-3 + 1e-4 * fabs(w[q]));
+            }
+            // voxel v's centre lies at lo + (v + 1/2) r; one voxel more at either end
+            const double v0 = floor((c - e - a.lo[ax]) / a.r) - 1.0, v1 = ceil((c + e - a.lo[ax]) / a.r) + 1.0;
+            lo = max(lo, (int64_t)fmin(fmax(v0, -1e9), 1e9));
+            hi = min(hi, (int64_t)fmin(fmax(v1, -1e9), 1e9));
+        }
+        lo = min(max(lo, (int64_t)0), (int64_t)a.n[ax]);
+        hi = min(max(hi, lo), (int64_t)a.n[ax]);
+        b.range[ax] = (uint32_t)lo | (uint32_t)hi << 16;   // n <= 4096
+    }
     a.blocks[t] = b;
 }
 
-// Build tiles: a workgroup covers 64 (x, one per lane) x 4 (y, one per
-// wave) x TZ (z, looped) voxels of one configuration, so that each wave
-// reads a link's block corner and map once (scalar loads) for TZ x 64
-// voxels and skips, with one uniform test, every link whose block misses
-// its tile.  The exact build takes TZ = 32: four times fewer workgroups
-// than 8, and its stores stream past the caches (non-temporal), since the
-// Robot SDFs are read only by a later runtime call (1.62 -> 1.06 ms for 500
-// waypoints over 128^3 voxels, against 0.61 ms for a plain fill of the same
-// 4.2 GB).  The network build keeps TZ = 8 (its per-voxel work is larger).
-constexpr int kTileX = 64, kTileY = kBlock / 64, kTileZ = 8, kBuildTileZ = 32;
-
-struct Tile {
-    int vx, vy, z0;
-    bool lane_ok;        // this lane's x and the wave's y lie in the environment
-};
-
-__device__ inline Tile tile_of(const int32_t n[3], int tz) {
-    const int tiles_x = (n[0] + kTileX - 1) / kTileX;
-    const int ty = (int)blockIdx.x / tiles_x;
-    const int tx = (int)blockIdx.x - ty * tiles_x;
-    Tile t;
-    t.vx = tx * kTileX + (int)(threadIdx.x & 63);
-    t.vy = ty * kTileY + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    t.z0 = (int)blockIdx.y * tz;
-    t.lane_ok = t.vx < n[0] && t.vy < n[1];
-    return t;
+// Every value of the Robot SDFs to +inf, before the minima: one 16 B store a
+// thread, so that the resident workgroups sweep the memory in order (1.68 GB in
+// 243 us, 6.9 TB/s; 4 stores a thread 276 us, a grid-stride loop 290 to 410 us,
+// non-temporal stores no better).
+__global__ __launch_bounds__(kBlock) void fill_inf_kernel(float* out, int64_t n, int64_t head, int64_t quads) {
+    // out[head] is 16-byte aligned; the odd values at either end go one by one
+    const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const f32x4 inf = {INFINITY, INFINITY, INFINITY, INFINITY};
+    if (t < quads) reinterpret_cast<f32x4*>(out + head)[t] = inf;
+    if (t < head) out[t] = INFINITY;
+    if (t < 4 && head + 4 * quads + t < n) out[head + 4 * quads + t] = INFINITY;
 }
 
-// Does the block [k, k + w) per axis meet this wave's tile (x over the
-// wave's 64 voxels, its y row, z over tz levels)?  Wave-uniform.
-__device__ inline bool tile_meets(const Tile& t, const int32_t k[3], int w, int tz) {
-    const int x0 = t.vx - (int)(threadIdx.x & 63);
-    return k[0] < x0 + kTileX && k[0] + w > x0 && t.vy >= k[1] && t.vy < k[1] + w && k[2] < t.z0 + tz &&
-           k[2] + w > t.z0;
-}
-
-template <bool CUBIC, int DT>
-__global__ __launch_bounds__(kBlock) void build_kernel(BuildArgs a, int32_t c0,
-                                                       const typename GridT<DT>::T* __restrict__ grid) {
-    const Tile t = tile_of(a.n, kBuildTileZ);
-    const int c = c0 + (int)blockIdx.z;
-    const float x = (float)(a.lo[0] + ((double)t.vx + 0.5) * a.r);
-    const float y = (float)(a.lo[1] + ((double)t.vy + 0.5) * a.r);
-    float zc[kBuildTileZ], best[kBuildTileZ];
-#pragma unroll
-    for (int dz = 0; dz < kBuildTileZ; ++dz) {
-        zc[dz] = (float)(a.lo[2] + ((double)(t.z0 + dz) + 0.5) * a.r);
-        best[dz] = INFINITY;
+int launch_fill_inf(const char* who, float* out, int64_t n, hipStream_t s) {
+    // launches of at most 2^30 quads each (2^22 workgroups)
+    constexpr int64_t kMost = (int64_t)1 << 32;
+    for (int64_t at = 0; at < n; at += kMost) {
+        float* p = out + at;
+        const int64_t cnt = std::min(kMost, n - at);
+        const int64_t head = std::min<int64_t>(cnt, (4 - (int64_t)((reinterpret_cast<uintptr_t>(p) >> 2) & 3)) & 3);
+        const int64_t quads = (cnt - head) / 4;
+        hipLaunchKernelGGL(fill_inf_kernel, dim3((unsigned)(quads / kBlock + 1)), dim3(kBlock), 0, s, p, cnt, head, quads);
+        const int rc = lsdf::check_launch(who);
+        if (rc != LSDF_OK) return rc;
     }
-    const LinkBlock* bl = a.blocks + (int64_t)c * a.L;
-    for (int i = 0; i < a.L; ++i) {
-        const LinkBlock b = bl[i];
-        const int w = 2 * a.halfw[i];
-        if (!tile_meets(t, b.k, w, kBuildTileZ)) continue;
-        // only the voxels the link's aligned block covers
-        if (!(t.vx >= b.k[0] && t.vx < b.k[0] + w)) continue;
+    return LSDF_OK;
+}
+
+// Minimum of v (not NaN, not -0) into *p, which holds +inf or other such
+// minima: the bits of non-negative floats order like signed integers, those of
+// negative ones against unsigned.
+__device__ inline void atomic_min(float* p, float v) {
+    if (v >= 0.0f)
+        atomicMin(reinterpret_cast<int*>(p), __float_as_int(v));
+    else
+        atomicMax(reinterpret_cast<unsigned*>(p), __float_as_uint(v));
+}
+
+constexpr int kBuildShares = 16;   // workgroups that share a pair's voxels
+
+// One (configuration, link) per workgroup (y: shares of its voxels): samples
+// the voxels in its range, x fastest over the threads, and takes an atomic
+// minimum for those in the box.
+template <bool CUBIC, int DT>
+__global__ __launch_bounds__(kBlock) void build_kernel(BuildArgs a, const typename GridT<DT>::T* __restrict__ grid) {
+    const int64_t V = (int64_t)a.n[0] * a.n[1] * a.n[2];
+    for (int64_t t = blockIdx.x; t < (int64_t)a.C * a.L; t += gridDim.x) {
+        const LinkBlock b = a.blocks[t];
+        const int i = (int)(t % a.L);
         const LinkGrid& lg = a.link[i];
-#pragma unroll
-        for (int dz = 0; dz < kBuildTileZ; ++dz) {
-            const int vz = t.z0 + dz;
-            if (vz >= b.k[2] && vz < b.k[2] + w)
-                best[dz] = fminf(best[dz], lsdf::sample_or_inf<CUBIC, DT>(grid + lg.offset, lg, b.gm, x, y, zc[dz]));
+        float* rs = a.rs + t / a.L * V;
+        const int x0 = b.range[0] & 0xffff, y0 = b.range[1] & 0xffff, z0 = b.range[2] & 0xffff;
+        const uint32_t nx = (b.range[0] >> 16) - x0, ny = (b.range[1] >> 16) - y0, nz = (b.range[2] >> 16) - z0;
+        const int64_t count = (int64_t)nx * ny * nz;
+        for (int64_t v = (int64_t)blockIdx.y * kBlock + threadIdx.x; v < count; v += (int64_t)gridDim.y * kBlock) {
+            const uint32_t row = (uint32_t)v / nx, vx = x0 + ((uint32_t)v - row * nx);   // at most 2^32 voxels
+            const uint32_t vz = z0 + row / ny, vy = y0 + row % ny;
+            const float x = (float)(a.lo[0] + ((double)vx + 0.5) * a.r);
+            const float y = (float)(a.lo[1] + ((double)vy + 0.5) * a.r);
+            const float z = (float)(a.lo[2] + ((double)vz + 0.5) * a.r);
+            const float val = lsdf::sample_or_inf<CUBIC, DT>(grid + lg.offset, lg, b.gm, x, y, z);
+            if (val < INFINITY) atomic_min(&rs[((int64_t)vz * a.n[1] + vy) * a.n[0] + vx], val);
         }
     }
-    if (!t.lane_ok) return;
-    const int64_t V = (int64_t)a.n[0] * a.n[1] * a.n[2];
-    float* out = a.rs + (int64_t)c * V + ((int64_t)t.z0 * a.n[1] + t.vy) * a.n[0] + t.vx;
-#pragma unroll
-    for (int dz = 0; dz < kBuildTileZ; ++dz)
-        if (t.z0 + dz < a.n[2]) __builtin_nontemporal_store(best[dz], &out[(int64_t)dz * a.n[0] * a.n[1]]);
 }
 
 // The same build with the transformation of Eq. 5: each block voxel's
@@ -152,7 +188,7 @@ __global__ __launch_bounds__(kBlock) void build_kernel(BuildArgs a, int32_t c0,
 struct LinkBlockNN {
     int32_t k[3];
     int32_t pad;
-    float h[LSDF_FRNN_HIDDEN];       // hidden layer of f at this rotation
+    float h[LSDF_FRNN_HIDDEN];       // hidden layer of f at this rotation, unit 4 s + g at 8 g + s
     float dtinv[3];
     float pad2;
 };
@@ -171,82 +207,115 @@ struct BuildNNArgs {
     float* rs;
 };
 
+// One thread per hidden unit of each (configuration, link); unit 0's also
+// aligns the block.
 __global__ __launch_bounds__(kBlock) void align_nn_kernel(BuildNNArgs a) {
-    const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t t = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / LSDF_FRNN_HIDDEN;
+    const int u = threadIdx.x % LSDF_FRNN_HIDDEN;
     if (t >= (int64_t)a.C * a.L) return;
     const float* T = a.link_T + t * 12;
-    LinkBlockNN b{};
+    LinkBlockNN& b = a.blocks[t];
+    const float x[9] = {T[0], T[1], T[2], T[4], T[5], T[6], T[8], T[9], T[10]};
+    const float* W1 = a.params;
+    float acc = W1[LSDF_FRNN_HIDDEN * 9 + u];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) acc = fmaf(W1[u * 9 + k], x[k], acc);
+    b.h[8 * (u & 3) + (u >> 2)] = fmaxf(acc, 0.0f);
+    if (u != 0) return;
     double dt[3];
 #pragma unroll
     for (int ax = 0; ax < 3; ++ax) {
         // Eq. 1-3: T_O = t - lo, k = round(T_O / r) - m, dt = T_O - (k + m) r
         const double t_o = (double)T[4 * ax + 3] - a.lo[ax];
-        b.k[ax] = (int32_t)rint(t_o / a.r) - a.m;
-        dt[ax] = t_o - ((double)b.k[ax] + (double)a.m) * a.r;
+        const int32_t k = (int32_t)rint(t_o / a.r) - a.m;
+        dt[ax] = t_o - ((double)k + (double)a.m) * a.r;
+        b.k[ax] = k;
     }
     // dt_inv = -R^T dt / e_r  (R[row][col] = T[4 row + col])
 #pragma unroll
     for (int ax = 0; ax < 3; ++ax)
         b.dtinv[ax] = (float)(-((double)T[ax] * dt[0] + (double)T[4 + ax] * dt[1] + (double)T[8 + ax] * dt[2]) /
                               (double)a.er);
-    const float x[9] = {T[0], T[1], T[2], T[4], T[5], T[6], T[8], T[9], T[10]};
-    const float* W1 = a.params;
-    const float* b1 = W1 + LSDF_FRNN_HIDDEN * 9;
-    for (int u = 0; u < LSDF_FRNN_HIDDEN; ++u) {
-        float acc = b1[u];
-#pragma unroll
-        for (int k = 0; k < 9; ++k) acc = fmaf(W1[u * 9 + k], x[k], acc);
-        b.h[u] = fmaxf(acc, 0.0f);
-    }
-    a.blocks[t] = b;
 }
 
+// One wave takes 16 block voxels and runs over its share of the (link, 16
+// configurations) groups.  f's output layer is a product of K = 32 over 3
+// outputs a voxel and is done on FP32 MFMA (v_mfma_f32_16x16x4: one chain of
+// fused multiply-adds per output in the order of K, the bits of a scalar
+// loop): A the voxels' weights of one component (lane l: voxel l mod 16, k =
+// 4 s + l / 16), kept in registers over all groups, B the hidden layers (lane
+// l: configuration l mod 16, the same k), so that lane l ends with the 3
+// components of voxels 4 (l / 16) + r at configuration l mod 16.  A point in
+// the link's box is sampled and its value goes to the environment voxel by an
+// atomic minimum (one in some tens of points is; the values were set to +inf
+// before).
+// Bound by MFMA issue (2 x 96 FLOP a block voxel, link and configuration: 35
+// of 85 us; the samples and their atomics take about 25 more) beside the +inf
+// fill (HBM).  40 configurations x 7 links, 44^3 block voxels, 128^3 voxels:
+// 2.01 ms a call with one thread per environment voxel, which read its 384 B
+// of weights from L2 for every link and configuration; 0.143 ms now.  The four
+// points' gathers issued together, and 5 or 6 waves a SIMD, measured the same.
+constexpr int kTile = 16;            // block voxels and configurations per MFMA tile
+constexpr int64_t kNNWaves = 8192;   // waves of a build, about
+constexpr int kSteps = LSDF_FRNN_HIDDEN / 4;
+
 template <bool CUBIC, int DT>
-__global__ __launch_bounds__(kBlock) void build_nn_kernel(BuildNNArgs a, int32_t c0,
-                                                          const typename GridT<DT>::T* __restrict__ grid) {
-    const Tile t = tile_of(a.n, kTileZ);
-    const int c = c0 + (int)blockIdx.z;
-    const int w = 2 * a.m;
-    const int64_t O = 3 * (int64_t)w * w * w;
+__global__ __launch_bounds__(kBlock) void build_nn_kernel(BuildNNArgs a, const typename GridT<DT>::T* __restrict__ grid) {
+    const int lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
+    const int w = 2 * a.m, V = w * w * w;   // at most 128^3
+    const int j0 = ((int)blockIdx.x * (kBlock / 64) + (int)(threadIdx.x >> 6)) * kTile;
+    if (j0 >= V) return;
     const float* W2 = a.params + LSDF_FRNN_HIDDEN * 10;
-    const float* b2 = W2 + O * LSDF_FRNN_HIDDEN;
-    float best[kTileZ];
+    const float* b2 = W2 + (int64_t)3 * V * LSDF_FRNN_HIDDEN;
+    float wt[3][kSteps];
+    const int ja = min(j0 + col, V - 1);
 #pragma unroll
-    for (int dz = 0; dz < kTileZ; ++dz) best[dz] = INFINITY;
-    const LinkBlockNN* bl = a.blocks + (int64_t)c * a.L;
-    for (int i = 0; i < a.L; ++i) {
-        const LinkBlockNN& b = bl[i];
-        if (!tile_meets(t, b.k, w, kTileZ)) continue;
-        const int jx = t.vx - b.k[0], jy = t.vy - b.k[1];
-        if (!(jx >= 0 && jx < w)) continue;
+    for (int ax = 0; ax < 3; ++ax)
+#pragma unroll
+        for (int s = 0; s < kSteps; ++s) wt[ax][s] = W2[(int64_t)(3 * ja + ax) * LSDF_FRNN_HIDDEN + 4 * s + g];
+    f32x4 bias[3];
+    uint32_t jv[4];   // voxel coordinates in the block, a byte each (2 m <= 128)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int jc = min(j0 + 4 * g + r, V - 1);
+        const int jz = jc / (w * w), jy = (jc - jz * w * w) / w;
+        jv[r] = (uint32_t)(jc - (jz * w + jy) * w) | (uint32_t)jy << 8 | (uint32_t)jz << 16;
+#pragma unroll
+        for (int ax = 0; ax < 3; ++ax) bias[ax][r] = b2[3 * jc + ax];
+    }
+    const int cgroups = (a.C + kTile - 1) / kTile;
+    const int64_t env_v = (int64_t)a.n[0] * a.n[1] * a.n[2];
+    for (int gr = blockIdx.y; gr < a.L * cgroups; gr += gridDim.y) {
+        const int i = gr / cgroups;
+        const int c = (gr - i * cgroups) * kTile + col;
+        const LinkBlockNN& b = a.blocks[(int64_t)min(c, a.C - 1) * a.L + i];
+        f32x4 y[3] = {bias[0], bias[1], bias[2]};
+        const f32x4 h0 = *reinterpret_cast<const f32x4*>(&b.h[8 * g]), h1 = *reinterpret_cast<const f32x4*>(&b.h[8 * g + 4]);
+#pragma unroll
+        for (int s = 0; s < kSteps; ++s)
+#pragma unroll
+            for (int ax = 0; ax < 3; ++ax)
+                y[ax] = __builtin_amdgcn_mfma_f32_16x16x4f32(wt[ax][s], s < 4 ? h0[s] : h1[s - 4], y[ax], 0, 0, 0);
+        const int k0 = b.k[0], k1 = b.k[1], k2 = b.k[2];
+        const float t[3] = {b.dtinv[0], b.dtinv[1], b.dtinv[2]};
         const LinkGrid& lg = a.link[i];
-        // link-frame point to centred grid coordinates: v_a = l_a invh_a + cen_a
-        lsdf::GridMap id{};
-        id.m00 = lg.invh[0]; id.w0 = lg.cen[0];
-        id.m11 = lg.invh[1]; id.w1 = lg.cen[1];
-        id.m22 = lg.invh[2]; id.w2 = lg.cen[2];
-        for (int dz = 0; dz < kTileZ; ++dz) {
-            const int jz = t.z0 + dz - b.k[2];
-            if (jz < 0 || jz >= w) continue;
-            const int64_t o = 3 * (((int64_t)jz * w + jy) * w + jx);
-            float l[3];
+        const typename GridT<DT>::T* G = grid + lg.offset;
 #pragma unroll
-            for (int ax = 0; ax < 3; ++ax) {
-                const float* row = W2 + (o + ax) * LSDF_FRNN_HIDDEN;
-                float yv = b2[o + ax];
-#pragma unroll
-                for (int u = 0; u < LSDF_FRNN_HIDDEN; ++u) yv = fmaf(row[u], b.h[u], yv);
-                l[ax] = a.er * (yv + b.dtinv[ax]);
+        for (int r = 0; r < 4; ++r) {
+            // link-frame point e_r (f + dt_inv), then centred grid coordinates v_a = l_a invh_a + cen_a
+            const float v0 = fmaf(lg.invh[0], a.er * (y[0][r] + t[0]), lg.cen[0]);
+            const float v1 = fmaf(lg.invh[1], a.er * (y[1][r] + t[1]), lg.cen[1]);
+            const float v2 = fmaf(lg.invh[2], a.er * (y[2][r] + t[2]), lg.cen[2]);
+            const uint32_t vx = (uint32_t)k0 + (jv[r] & 0xff), vy = (uint32_t)k1 + (jv[r] >> 8 & 0xff),
+                           vz = (uint32_t)k2 + (jv[r] >> 16);
+            const bool covered = vx < (uint32_t)a.n[0] && vy < (uint32_t)a.n[1] && vz < (uint32_t)a.n[2] && c < a.C &&
+                                 j0 + 4 * g + r < V;
+            if (covered && lsdf::inside<CUBIC>(lg, v0, v1, v2)) {
+                const float val = lsdf::cell_value<DT>(G, lg, v0, v1, v2);
+                atomic_min(&a.rs[(int64_t)c * env_v + ((int64_t)vz * a.n[1] + vy) * a.n[0] + vx], val);
             }
-            best[dz] = fminf(best[dz], lsdf::sample_or_inf<CUBIC, DT>(grid + lg.offset, lg, id, l[0], l[1], l[2]));
         }
     }
-    if (!t.lane_ok) return;
-    const int64_t V = (int64_t)a.n[0] * a.n[1] * a.n[2];
-    float* out = a.rs + (int64_t)c * V + ((int64_t)t.z0 * a.n[1] + t.vy) * a.n[0] + t.vx;
-#pragma unroll
-    for (int dz = 0; dz < kTileZ; ++dz)
-        if (t.z0 + dz < a.n[2]) out[(int64_t)dz * a.n[0] * a.n[1]] = best[dz];
 }
 
 struct RuntimeArgs {
@@ -453,22 +522,18 @@ LSDF_API int lsdf_robot_sdf_build(const float* link_T, int32_t C, int32_t L, con
     const int64_t CL = (int64_t)C * L;
     hipLaunchKernelGGL(align_kernel, dim3((unsigned)((CL + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, a);
     if ((rc = check_launch("robot_sdf_build (align)")) != LSDF_OK) return rc;
-    // x, y: the tiles of one configuration, z: up to 65535 configurations per launch
-    const dim3 bd(kBlock);
-    for (int32_t c0 = 0; c0 < C; c0 += 65535) {
-        const dim3 gd((unsigned)(((env->n[0] + kTileX - 1) / kTileX) * ((env->n[1] + kTileY - 1) / kTileY)),
-                      (unsigned)((env->n[2] + kBuildTileZ - 1) / kBuildTileZ), (unsigned)std::min<int32_t>(65535, C - c0));
-        switch (dtype * 2 + (cubic ? 1 : 0)) {
-            case LSDF_F32 * 2 + 1: hipLaunchKernelGGL((build_kernel<true, LSDF_F32>), gd, bd, 0, s, a, c0, static_cast<const float*>(grid_buf)); break;
-            case LSDF_F32 * 2: hipLaunchKernelGGL((build_kernel<false, LSDF_F32>), gd, bd, 0, s, a, c0, static_cast<const float*>(grid_buf)); break;
-            case LSDF_BF16 * 2 + 1: hipLaunchKernelGGL((build_kernel<true, LSDF_BF16>), gd, bd, 0, s, a, c0, static_cast<const uint16_t*>(grid_buf)); break;
-            case LSDF_BF16 * 2: hipLaunchKernelGGL((build_kernel<false, LSDF_BF16>), gd, bd, 0, s, a, c0, static_cast<const uint16_t*>(grid_buf)); break;
-            case LSDF_F16 * 2 + 1: hipLaunchKernelGGL((build_kernel<true, LSDF_F16>), gd, bd, 0, s, a, c0, static_cast<const _Float16*>(grid_buf)); break;
-            default: hipLaunchKernelGGL((build_kernel<false, LSDF_F16>), gd, bd, 0, s, a, c0, static_cast<const _Float16*>(grid_buf)); break;
-        }
-        if ((rc = check_launch("robot_sdf_build")) != LSDF_OK) return rc;
+    if ((rc = launch_fill_inf("robot_sdf_build (fill)", robot_sdf, (int64_t)C * V, s)) != LSDF_OK) return rc;
+    // x: (configuration, link) pairs, y: shares of a pair's voxels
+    const dim3 gd((unsigned)std::min<int64_t>(CL, 1 << 20), kBuildShares), bd(kBlock);
+    switch (dtype * 2 + (cubic ? 1 : 0)) {
+        case LSDF_F32 * 2 + 1: hipLaunchKernelGGL((build_kernel<true, LSDF_F32>), gd, bd, 0, s, a, static_cast<const float*>(grid_buf)); break;
+        case LSDF_F32 * 2: hipLaunchKernelGGL((build_kernel<false, LSDF_F32>), gd, bd, 0, s, a, static_cast<const float*>(grid_buf)); break;
+        case LSDF_BF16 * 2 + 1: hipLaunchKernelGGL((build_kernel<true, LSDF_BF16>), gd, bd, 0, s, a, static_cast<const uint16_t*>(grid_buf)); break;
+        case LSDF_BF16 * 2: hipLaunchKernelGGL((build_kernel<false, LSDF_BF16>), gd, bd, 0, s, a, static_cast<const uint16_t*>(grid_buf)); break;
+        case LSDF_F16 * 2 + 1: hipLaunchKernelGGL((build_kernel<true, LSDF_F16>), gd, bd, 0, s, a, static_cast<const _Float16*>(grid_buf)); break;
+        default: hipLaunchKernelGGL((build_kernel<false, LSDF_F16>), gd, bd, 0, s, a, static_cast<const _Float16*>(grid_buf)); break;
     }
-    return LSDF_OK;
+    return check_launch("robot_sdf_build");
 }
 
 LSDF_API int lsdf_robot_sdf_build_frnn(const float* link_T, int32_t C, int32_t L, const lsdf_grid* grids,
@@ -518,24 +583,25 @@ LSDF_API int lsdf_robot_sdf_build_frnn(const float* link_T, int32_t C, int32_t L
     a.rs = robot_sdf;
     hipStream_t s = as_stream(stream);
     const int64_t CL = (int64_t)C * L;
-    hipLaunchKernelGGL(align_nn_kernel, dim3((unsigned)((CL + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(align_nn_kernel, dim3((unsigned)((CL * LSDF_FRNN_HIDDEN + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, a);
     if ((rc = check_launch("robot_sdf_build_frnn (align)")) != LSDF_OK) return rc;
-    // x, y: the tiles of one configuration, z: up to 65535 configurations per launch
+    if ((rc = launch_fill_inf("robot_sdf_build_frnn (fill)", robot_sdf, (int64_t)C * V, s)) != LSDF_OK) return rc;
+    // x: 64 block voxels, y: shares of the groups, about 8 waves a SIMD in all
+    // (a wave's weights, loaded once, serve its whole share: 16 a SIMD 5 us
+    // slower, 32 a SIMD 37 us)
+    const int64_t bv = (int64_t)8 * m * m * m, xb = (bv + kTile * (kBlock / 64) - 1) / (kTile * (kBlock / 64));
+    const int64_t groups = (int64_t)L * ((C + kTile - 1) / kTile);
+    const dim3 gd((unsigned)xb, (unsigned)std::min<int64_t>({groups, 65535, (kNNWaves / (kBlock / 64) + xb - 1) / xb}));
     const dim3 bd(kBlock);
-    for (int32_t c0 = 0; c0 < C; c0 += 65535) {
-        const dim3 gd((unsigned)(((env->n[0] + kTileX - 1) / kTileX) * ((env->n[1] + kTileY - 1) / kTileY)),
-                      (unsigned)((env->n[2] + kTileZ - 1) / kTileZ), (unsigned)std::min<int32_t>(65535, C - c0));
-        switch (dtype * 2 + (cubic ? 1 : 0)) {
-            case LSDF_F32 * 2 + 1: hipLaunchKernelGGL((build_nn_kernel<true, LSDF_F32>), gd, bd, 0, s, a, c0, static_cast<const float*>(grid_buf)); break;
-            case LSDF_F32 * 2: hipLaunchKernelGGL((build_nn_kernel<false, LSDF_F32>), gd, bd, 0, s, a, c0, static_cast<const float*>(grid_buf)); break;
-            case LSDF_BF16 * 2 + 1: hipLaunchKernelGGL((build_nn_kernel<true, LSDF_BF16>), gd, bd, 0, s, a, c0, static_cast<const uint16_t*>(grid_buf)); break;
-            case LSDF_BF16 * 2: hipLaunchKernelGGL((build_nn_kernel<false, LSDF_BF16>), gd, bd, 0, s, a, c0, static_cast<const uint16_t*>(grid_buf)); break;
-            case LSDF_F16 * 2 + 1: hipLaunchKernelGGL((build_nn_kernel<true, LSDF_F16>), gd, bd, 0, s, a, c0, static_cast<const _Float16*>(grid_buf)); break;
-            default: hipLaunchKernelGGL((build_nn_kernel<false, LSDF_F16>), gd, bd, 0, s, a, c0, static_cast<const _Float16*>(grid_buf)); break;
-        }
-        if ((rc = check_launch("robot_sdf_build_frnn")) != LSDF_OK) return rc;
+    switch (dtype * 2 + (cubic ? 1 : 0)) {
+        case LSDF_F32 * 2 + 1: hipLaunchKernelGGL((build_nn_kernel<true, LSDF_F32>), gd, bd, 0, s, a, static_cast<const float*>(grid_buf)); break;
+        case LSDF_F32 * 2: hipLaunchKernelGGL((build_nn_kernel<false, LSDF_F32>), gd, bd, 0, s, a, static_cast<const float*>(grid_buf)); break;
+        case LSDF_BF16 * 2 + 1: hipLaunchKernelGGL((build_nn_kernel<true, LSDF_BF16>), gd, bd, 0, s, a, static_cast<const uint16_t*>(grid_buf)); break;
+        case LSDF_BF16 * 2: hipLaunchKernelGGL((build_nn_kernel<false, LSDF_BF16>), gd, bd, 0, s, a, static_cast<const uint16_t*>(grid_buf)); break;
+        case LSDF_F16 * 2 + 1: hipLaunchKernelGGL((build_nn_kernel<true, LSDF_F16>), gd, bd, 0, s, a, static_cast<const _Float16*>(grid_buf)); break;
+        default: hipLaunchKernelGGL((build_nn_kernel<false, LSDF_F16>), gd, bd, 0, s, a, static_cast<const _Float16*>(grid_buf)); break;
     }
-    return LSDF_OK;
+    return check_launch("robot_sdf_build_frnn");
 }
 
 namespace {
