@@ -9,17 +9,15 @@
 //   target_o = sum_b R[b][a] P_j[b],  P_j = (j + 1/2) / m - 1 per axis.
 //   Parameters: W1[32][9], b1[32], W2[3V][32], b2[3V] (FP32).
 //
-// Training step (all FP32, deterministic: no floating-point atomics):
-//   hidden kernel  z, h for the B rotations of the batch;
-//   output kernel  one thread per output row o, 128 rows per workgroup:
-//                  the B outputs of row o, their errors against the exact
-//                  target, dW2[o] and db2[o] (each row owned by one thread),
-//                  the workgroup's partial loss and its partial of
-//                  dh = sum_o g_o W2[o] (g_o = sign(error) / (B 3V)), with
-//                  the signs and the rows staged in LDS;
-//   reduce kernels sum the partials in two levels (64 slices, then one
-//                  workgroup): loss, dh; then dW1, db1 through the ReLU;
-//   Adam kernel    one thread per parameter.
+// Training step (all FP32, deterministic: no floating-point atomics), two
+// kernels:
+//   step kernel    every wave takes 16 outputs at a time: their values, their errors against the exact target,
+//                  dW2 and db2 and their Adam update, and the wave's share of
+//                  the loss and of dh = sum_o g_o W2[o] (g_o = sign(error) /
+//                  (B 3V)), with every product on FP32 MFMA;
+//   finish kernel  a workgroup per hidden unit sums the shares in order:
+//                  loss, dh, then dW1, db1 through the ReLU and their Adam
+//                  update.
 // Max-error kernel: max |f(R) - R^T P| over rotations and outputs (the
 // paper's 10^7-transformation test), one thread per output row, rotations
 // in tiles of 64 whose hidden layers are computed once per workgroup.
@@ -30,11 +28,12 @@
 namespace {
 
 constexpr int kH = LSDF_FRNN_HIDDEN;
-constexpr int kRows = 128;          // output rows per workgroup
+constexpr int kRows = 128;          // output rows per workgroup of the max-error kernel
 constexpr int kMaxB = 64;           // rotations per training step
 constexpr int kTile = 64;           // rotations per tile in the max-error kernel
-constexpr int kReduceThreads = 1024;   // the single workgroup of the last reduction
-constexpr int kSlices = 64;         // first level of the partial-sum reduction
+constexpr int kStepBlock = 256;     // threads of the step kernel's workgroups
+constexpr int kStepGroups = 512;    // its workgroups at most: two a CU
+constexpr int kFinishBlock = 1024;  // threads of the finish kernel's workgroups
 
 struct Layout {
     int64_t V, O;                   // voxels, outputs (3 V)
@@ -67,246 +66,317 @@ __device__ inline float frnn_target(const float* r, int64_t o, int m) {
 }
 
 struct TrainArgs {
-    const float* params;
+    float* params;
     const float* R;          // [B][9]
-    float* z;                // [B][kH]
-    float* h;                // [B][kH]
     float* grad;             // [n]
-    float* part_dh;          // [blocks][B][kH]
-    float* part_loss;        // [blocks]
-    float* part2_dh;         // [kSlices][B][kH]
-    float* part2_loss;       // [kSlices]
+    float* adam_m;           // [n], or NULL: the gradient only
+    float* adam_v;
+    float* part_dh;          // [groups][kH][kMaxB], without the factor 1 / (B 3V)
+    float* part_loss;        // [groups]
     float* loss_out;         // [1] or NULL
     Layout lay;
     int32_t m;
     int32_t B;
-    int32_t blocks;
+    int32_t groups;          // workgroups of the step kernel
+    float lr, b1, b2, eps, c1, c2;   // c1 = 1 / (1 - b1^t), c2 = 1 / (1 - b2^t)
 };
 
-__global__ __launch_bounds__(256) void frnn_hidden_kernel(TrainArgs a) {
-    const int t = blockIdx.x * 256 + threadIdx.x;
-    if (t >= a.B * kH) return;
-    const int b = t / kH, u = t - b * kH;
-    const float* W1 = a.params + a.lay.w1;
-    float acc = a.params[a.lay.b1 + u];
-#pragma unroll
-    for (int k = 0; k < 9; ++k) acc = fmaf(W1[u * 9 + k], a.R[b * 9 + k], acc);
-    a.z[t] = acc;
-    a.h[t] = fmaxf(acc, 0.0f);
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+// four floats at any element: a vector load needs no alignment beyond one's
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+
+struct AdamState {
+    float p, m, v;
+};
+__device__ inline AdamState adam(const TrainArgs& a, AdamState s, float g) {
+    const float m = fmaf(a.b1, s.m, (1.0f - a.b1) * g);
+    const float v = fmaf(a.b2, s.v, (1.0f - a.b2) * g * g);
+    return {s.p - a.lr * (m * a.c1) / (sqrtf(v * a.c2) + a.eps), m, v};
 }
 
-__global__ __launch_bounds__(kRows) void frnn_output_kernel(TrainArgs a) {
-    static_assert(kRows == (kMaxB / 4) * (kH / 4), "one 4 x 4 tile of dh per thread");
-    __shared__ float hs[kMaxB][kH];
-    __shared__ float rs[kMaxB][9];
-    // sign of g[row][b] (g is +scale, -scale or 0), transposed: rows contiguous,
-    // the pad staggers the rotations over the banks
-    __shared__ __align__(16) int8_t sgT[kMaxB][kRows + 4];
-    __shared__ float4 ws4[kRows][kH / 4];       // W2 rows in 16 B chunks, chunk c stored at c ^ (row mod 8)
-    __shared__ float ls[kRows];
-    const int tid = threadIdx.x;
-    const int B = a.B;
-    for (int k = tid; k < B * kH; k += kRows) hs[k / kH][k % kH] = a.h[k];
-    for (int k = tid; k < B * 9; k += kRows) rs[k / 9][k % 9] = a.R[k];
-    const int64_t o = (int64_t)blockIdx.x * kRows + tid;
-    const bool live = o < a.lay.O;
-    float wrow[kH];
+// Gradient g of parameter k, and its Adam update when there are moments.
+__device__ inline void update(const TrainArgs& a, int64_t k, float g) {
+    a.grad[k] = g;
+    if (!a.adam_m) return;
+    const AdamState s = adam(a, {a.params[k], a.adam_m[k], a.adam_v[k]}, g);
+    a.params[k] = s.p;
+    a.adam_m[k] = s.m;
+    a.adam_v[k] = s.v;
+}
+
+// Pre-activation of hidden unit u at rotation r.
+__device__ inline float hidden(const TrainArgs& a, int u, const float* r) {
+    const float* W1 = a.params + a.lay.w1 + u * 9;
+    float acc = a.params[a.lay.b1 + u];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) acc = fmaf(W1[k], r[k], acc);
+    return acc;
+}
+
+__device__ inline float masked(float e, uint32_t mask) { return __uint_as_float(__float_as_uint(e) & mask); }
+__device__ inline float sign_of(float e) { return e > 0.0f ? 1.0f : (e < 0.0f ? -1.0f : 0.0f); }
+
+// What a wave reads of its 16 outputs (lane: c, g as below).
+struct Unit {
+    float wo[kH / 4];         // W2[o][4 s + g], o the unit's output c
+    float wu[4][2];           // W2[output 4 g + r][16 ut + c]
+    f32x4 p[2], m[2], v[2];   // W2[o][16 ut + 4 g ..] and its moments
+    float bias, bias_m, bias_v;   // b2[o] and its moments
+};
+template <bool ADAM>
+__device__ inline Unit load_unit(const TrainArgs& a, int q, int c, int g) {
     const float* W2 = a.params + a.lay.w2;
+    const int64_t last = a.lay.O - 1, o = min((int64_t)16 * q + c, last);
+    Unit u;
 #pragma unroll
-    for (int u = 0; u < kH; ++u) wrow[u] = live ? W2[o * kH + u] : 0.0f;
+    for (int s = 0; s < kH / 4; ++s) u.wo[s] = W2[o * kH + 4 * s + g];
 #pragma unroll
-    for (int c = 0; c < kH / 4; ++c)
-        ws4[tid][c ^ (tid & 7)] = make_float4(wrow[4 * c], wrow[4 * c + 1], wrow[4 * c + 2], wrow[4 * c + 3]);
-    const float bias = live ? a.params[a.lay.b2 + o] : 0.0f;
-    // this row's block voxel and component (the target is R^T P_j, component a)
-    int comp = 0;
-    float px = 0.0f, py = 0.0f, pz = 0.0f;
-    if (live) {
-        const int64_t j = o / 3;
-        comp = (int)(o - 3 * j);
-        const int w = 2 * a.m;
-        const int jx = (int)(j % w), jy = (int)((j / w) % w), jz = (int)(j / ((int64_t)w * w));
-        const float inv = 1.0f / (float)a.m;
-        px = fmaf((float)jx + 0.5f, inv, -1.0f);
-        py = fmaf((float)jy + 0.5f, inv, -1.0f);
-        pz = fmaf((float)jz + 0.5f, inv, -1.0f);
+    for (int r = 0; r < 4; ++r) {
+        const int64_t ok = min((int64_t)16 * q + 4 * g + r, last);
+#pragma unroll
+        for (int ut = 0; ut < 2; ++ut) u.wu[r][ut] = W2[ok * kH + 16 * ut + c];
     }
-    __syncthreads();
-    const float scale = 1.0f / ((float)B * (float)a.lay.O);
-    float dw[kH];
+    u.bias = a.params[a.lay.b2 + o];
+    if (ADAM) {
+        u.bias_m = a.adam_m[a.lay.b2 + o];
+        u.bias_v = a.adam_v[a.lay.b2 + o];
+    }
 #pragma unroll
-    for (int u = 0; u < kH; ++u) dw[u] = 0.0f;
-    float db = 0.0f, loss = 0.0f;
-    for (int b = 0; b < B; ++b) {
-        float y = bias;
-#pragma unroll
-        for (int u = 0; u < kH; ++u) y = fmaf(wrow[u], hs[b][u], y);
-        float g = 0.0f;
-        int8_t sg = 0;
-        if (live) {
-            const float* r = rs[b];
-            const float t = fmaf(r[comp], px, fmaf(r[3 + comp], py, r[6 + comp] * pz));
-            const float e = y - t;
-            loss += fabsf(e);
-            sg = e > 0.0f ? 1 : (e < 0.0f ? -1 : 0);
-            g = e > 0.0f ? scale : (e < 0.0f ? -scale : 0.0f);
+    for (int ut = 0; ut < 2; ++ut) {
+        const int64_t k = o * kH + 16 * ut + 4 * g;
+        if (ADAM) {
+            u.p[ut] = *reinterpret_cast<const f32x4_any*>(W2 + k);
+            u.m[ut] = *reinterpret_cast<const f32x4_any*>(a.adam_m + a.lay.w2 + k);
+            u.v[ut] = *reinterpret_cast<const f32x4_any*>(a.adam_v + a.lay.w2 + k);
         }
-        sgT[b][tid] = sg;
-#pragma unroll
-        for (int u = 0; u < kH; ++u) dw[u] = fmaf(g, hs[b][u], dw[u]);
-        db += g;
     }
-    if (live) {
-        float* gW2 = a.grad + a.lay.w2 + o * kH;
-#pragma unroll
-        for (int u = 0; u < kH; ++u) gW2[u] = dw[u];
-        a.grad[a.lay.b2 + o] = db;
-    }
-    ls[tid] = loss;
+    return u;
+}
+
+// The step kernel.  Products run on v_mfma_f32_16x16x4 (lane l, c = l mod 16,
+// g = l / 16: A row c and B column c at k = 4 step + g; D column c, rows 4 g +
+// r), which is one chain of fused multiply-adds per output in the order of k:
+// the outputs' K = 32 runs in the units' order, so an error and its sign are
+// those of a scalar loop.  The errors are wanted with the rotations along K
+// (for dW2) and with the outputs along K (for dh); rather than transposed
+// through LDS they are formed both ways, from the same registers: W H^T gives
+// lane l the outputs 4 g + r at rotation c, H W^T the output c at rotations
+// 4 g + r, each already in the next product's operand layout (its K index
+// permuted alike on both sides).  Signs stand for g; the factor 1 / (B 3V) is
+// applied to the sums.
+// Two waves a SIMD (244 registers) share 27 us of MFMA, about as much VALU and
+// the memory traffic (parameters and moments read and written, the gradient
+// written: 236 MB at 44^3 voxels, 42 us at the rate the separate Adam kernel
+// reached), which overlap in part: 80 us for a step of 64 rotations.  Separate
+// kernels for the hidden layer, the outputs (FP32 VALU, 107 us), two levels of
+// sums and Adam (42 us) took 154 us a step, the two kernels here 91 to 97.  At 3
+// and 4 waves a SIMD (spills) 105 to 184 us; 16 voxels of one component a unit
+// instead of 16 adjacent outputs, and 1,024 workgroups, measured the same; the
+// gradient's stores past the caches 1 to 7 us faster.
+template <bool ADAM>
+__global__ __launch_bounds__(kStepBlock, 2) void frnn_step_kernel(TrainArgs a) {
+    constexpr int kTilesB = kMaxB / 16, kSteps = kH / 4, kStride = kH + 1;
+    __shared__ float hs[kMaxB][kStride];                // hidden layer, 0 past the batch
+    __shared__ __align__(16) float rt[9][kMaxB];        // rotations, transposed
+    __shared__ float share[kH * kMaxB];
+    __shared__ float share_loss[kStepBlock / 64];
+    const int tid = threadIdx.x, lane = tid & 63, c = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int B = a.B;
+    const int O = (int)a.lay.O, w = 2 * a.m;
+    const int units = (O + 15) / 16;
+    int q = blockIdx.x * (kStepBlock / 64) + wave;
+    Unit u = load_unit<ADAM>(a, min(q, units - 1), c, g);   // on its way during the hidden layer
+    for (int k = tid; k < 9 * kMaxB; k += kStepBlock) rt[k / kMaxB][k % kMaxB] = k % kMaxB < B ? a.R[k % kMaxB * 9 + k / kMaxB] : 0.0f;
     __syncthreads();
-    // this workgroup's share of dh[b][u] = sum over its rows of g W2[o][u],
-    // rows in order; thread t holds b = 4 (t / 8) + i, u = 4 (t mod 8) + k
-    const int bt = tid >> 3, ut = tid & 7;
-    float acc[4][4];
+    {
+        // thread t: unit t mod 32 at rotations t / 32, t / 32 + 8, ..
+        const int u = tid % kH;
+        const float* W1 = a.params + a.lay.w1 + u * 9;
+        float w1[9];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+        for (int k = 0; k < 9; ++k) w1[k] = W1[k];
+        const float b1 = a.params[a.lay.b1 + u];
+        for (int b = tid / kH; b < kMaxB; b += kStepBlock / kH) {
+            float acc = b1;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) acc[i][k] = 0.0f;
-    for (int r0 = 0; r0 < kRows; r0 += 4) {
-        uint32_t sg4[4];   // the signs of rows r0 .. r0 + 3, one byte each
+            for (int k = 0; k < 9; ++k) acc = fmaf(w1[k], rt[k][b], acc);
+            hs[b][u] = b < B ? fmaxf(acc, 0.0f) : 0.0f;
+        }
+    }
+    __syncthreads();
+    f32x4 dh[2][kTilesB];   // units 16 ut + 4 g + r, rotation 16 bt + c
 #pragma unroll
-        for (int i = 0; i < 4; ++i) sg4[i] = *reinterpret_cast<const uint32_t*>(&sgT[4 * bt + i][r0]);
+    for (int bt = 0; bt < kTilesB; ++bt) dh[0][bt] = dh[1][bt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    const float scale = 1.0f / ((float)B * (float)a.lay.O);
+    const float inv = 1.0f / (float)a.m;
+    float loss = 0.0f;
+    const int stride = gridDim.x * (kStepBlock / 64);
+    for (; q < units; q += stride) {
+        // the next unit's rows are on their way while this one's are used
+        const Unit next = load_unit<ADAM>(a, min(q + stride, units - 1), c, g);
+        // this lane's output with the outputs along columns or rows (c), and
+        // with them along K (4 g + r); past the last one that stands in, its
+        // signs 0 where sums are formed
+        const int of = 16 * q + c, o = min(of, O - 1), j = o / 3, comp = o - 3 * j;
+        const uint32_t live = of < O ? ~0u : 0u;
+        const float bias = u.bias;
+        const int jz = j / (w * w), jy = (j - jz * w * w) / w, jx = j - (jz * w + jy) * w;
+        const float px = fmaf((float)jx + 0.5f, inv, -1.0f), py = fmaf((float)jy + 0.5f, inv, -1.0f),
+                    pz = fmaf((float)jz + 0.5f, inv, -1.0f);
+        f32x4 bias_k, px_k, py_k, pz_k;
+        uint32_t live_k[4];
+        int comp_k[4];
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-            const float4 wv = ws4[r0 + rr][ut ^ ((r0 + rr) & 7)];
+        for (int r = 0; r < 4; ++r) {
+            live_k[r] = 16 * q + 4 * g + r < O ? ~0u : 0u;
+            comp_k[r] = (uint32_t)(16 * q + 4 * g + r) % 3u;
+            bias_k[r] = __shfl(bias, 4 * g + r, 64);
+            px_k[r] = __shfl(px, 4 * g + r, 64);
+            py_k[r] = __shfl(py, 4 * g + r, 64);
+            pz_k[r] = __shfl(pz, 4 * g + r, 64);
+        }
+        f32x4 dw[2] = {};   // dW2[o][16 ut + 4 g + r] / scale
+        float db = 0.0f;
+        // the outputs of rotations 16 bt .., rotations along columns (y) and along K (z)
+        auto outputs = [&](int bt, f32x4& y, f32x4& z) {
+            y = bias_k;
+            z = f32x4{bias, bias, bias, bias};
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                // g itself, rebuilt exactly from its sign
-                const float gi = (float)(int8_t)(sg4[i] >> (8 * rr)) * scale;
-                acc[i][0] = fmaf(gi, wv.x, acc[i][0]);
-                acc[i][1] = fmaf(gi, wv.y, acc[i][1]);
-                acc[i][2] = fmaf(gi, wv.z, acc[i][2]);
-                acc[i][3] = fmaf(gi, wv.w, acc[i][3]);
+            for (int s = 0; s < kSteps; ++s) {
+                const float h = hs[16 * bt + c][4 * s + g];
+                y = __builtin_amdgcn_mfma_f32_16x16x4f32(u.wo[s], h, y, 0, 0, 0);
+                z = __builtin_amdgcn_mfma_f32_16x16x4f32(h, u.wo[s], z, 0, 0, 0);
+            }
+        };
+        f32x4 y, z, yn, zn;
+        outputs(0, y, z);
+#pragma unroll
+        for (int bt = 0; bt < kTilesB; ++bt) {
+            if (16 * bt >= B) break;
+            // the next rotations' products run under this one's errors
+            if (bt + 1 < kTilesB) outputs(bt + 1, yn, zn);
+            const int b = 16 * bt + c;
+            const f32x4 r0 = *reinterpret_cast<const f32x4*>(&rt[comp][16 * bt + 4 * g]);
+            const f32x4 r1 = *reinterpret_cast<const f32x4*>(&rt[3 + comp][16 * bt + 4 * g]);
+            const f32x4 r2 = *reinterpret_cast<const f32x4*>(&rt[6 + comp][16 * bt + 4 * g]);
+            const uint32_t in_c = b < B ? ~0u : 0u;   // masks, not conditions: no branches between the products
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                // outputs along K: dh
+                const float ty = fmaf(rt[comp_k[r]][b], px_k[r], fmaf(rt[3 + comp_k[r]][b], py_k[r], rt[6 + comp_k[r]][b] * pz_k[r]));
+                const float sy = sign_of(masked(y[r] - ty, live_k[r] & in_c));
+                // rotations along K: the loss, dW2 and db2
+                const uint32_t in_k = 16 * bt + 4 * g + r < B ? ~0u : 0u;
+                const float tz = fmaf(r0[r], px, fmaf(r1[r], py, r2[r] * pz));
+                const float e = masked(z[r] - tz, in_k);
+                loss += fabsf(masked(e, live));
+                const float sz = sign_of(e);
+                db += sz;
+#pragma unroll
+                for (int ut = 0; ut < 2; ++ut) {
+                    dh[ut][bt] = __builtin_amdgcn_mfma_f32_16x16x4f32(u.wu[r][ut], sy, dh[ut][bt], 0, 0, 0);
+                    dw[ut] = __builtin_amdgcn_mfma_f32_16x16x4f32(hs[16 * bt + 4 * g + r][16 * ut + c], sz, dw[ut], 0, 0, 0);
+                }
+            }
+            y = yn;
+            z = zn;
+        }
+        db += __shfl_xor(db, 16, 64);
+        db += __shfl_xor(db, 32, 64);
+        // no branches from here to the next unit: a wait for its rows then only
+        // counts the stores behind them instead of waiting for those too
+        // (lanes past the block hold the last voxel's values, and the four
+        // lanes of a b2 the same one: they store alike)
+#pragma unroll
+        for (int ut = 0; ut < 2; ++ut) {
+            const int64_t k = a.lay.w2 + (int64_t)o * kH + 16 * ut + 4 * g;
+            const f32x4 gr = dw[ut] * scale;
+            __builtin_nontemporal_store(gr, reinterpret_cast<f32x4_any*>(a.grad + k));
+            if (ADAM) {
+                f32x4 p4, m4, v4;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const AdamState st = adam(a, {u.p[ut][r], u.m[ut][r], u.v[ut][r]}, gr[r]);
+                    p4[r] = st.p;
+                    m4[r] = st.m;
+                    v4[r] = st.v;
+                }
+                *reinterpret_cast<f32x4_any*>(a.params + k) = p4;
+                *reinterpret_cast<f32x4_any*>(a.adam_m + k) = m4;
+                *reinterpret_cast<f32x4_any*>(a.adam_v + k) = v4;
             }
         }
+        a.grad[a.lay.b2 + o] = db * scale;
+        if (ADAM) {
+            const AdamState st = adam(a, {u.bias, u.bias_m, u.bias_v}, db * scale);
+            a.params[a.lay.b2 + o] = st.p;
+            a.adam_m[a.lay.b2 + o] = st.m;
+            a.adam_v[a.lay.b2 + o] = st.v;
+        }
+        u = next;
     }
-    float* pd = a.part_dh + (int64_t)blockIdx.x * B * kH;
+    // the workgroup's shares, its waves in order
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int b = 4 * bt + i;
-        if (b < B) *reinterpret_cast<float4*>(&pd[b * kH + 4 * ut]) = make_float4(acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
+    for (int off = 32; off > 0; off >>= 1) loss += __shfl_xor(loss, off, 64);
+    if (lane == 0) share_loss[wave] = loss;
+    for (int v = 0; v < kStepBlock / 64; ++v) {
+        if (wave == v) {
+#pragma unroll
+            for (int ut = 0; ut < 2; ++ut)
+#pragma unroll
+                for (int bt = 0; bt < kTilesB; ++bt)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        float& t = share[(16 * ut + 4 * g + r) * kMaxB + 16 * bt + c];
+                        t = v == 0 ? dh[ut][bt][r] : t + dh[ut][bt][r];
+                    }
+        }
+        __syncthreads();
     }
+    for (int k = tid; k < kH * kMaxB; k += kStepBlock) a.part_dh[(int64_t)blockIdx.x * kH * kMaxB + k] = share[k];
     if (tid == 0) {
         float s = 0.0f;
-        for (int r = 0; r < kRows; ++r) s += ls[r];
+        for (int v = 0; v < kStepBlock / 64; ++v) s += share_loss[v];
         a.part_loss[blockIdx.x] = s;
     }
 }
 
-// First level of the reduction: slice s sums the output kernel's partials
-// of workgroups s, s + kSlices, ... (in that fixed order).
-__global__ __launch_bounds__(256) void frnn_slice_kernel(TrainArgs a) {
-    const int sl = blockIdx.y;
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    const int BH = a.B * kH;
-    // the sums run in the fixed order; their loads are issued kBatch at a time
-    constexpr int kBatch = 8;
-    if (p < BH) {
-        float s = 0.0f;
-        for (int blk0 = sl; blk0 < a.blocks; blk0 += kBatch * kSlices) {
-            float v[kBatch];
-#pragma unroll
-            for (int k = 0; k < kBatch; ++k) {
-                const int blk = blk0 + k * kSlices;
-                v[k] = blk < a.blocks ? a.part_dh[(int64_t)blk * BH + p] : 0.0f;
-            }
-#pragma unroll
-            for (int k = 0; k < kBatch; ++k)
-                if (blk0 + k * kSlices < a.blocks) s += v[k];
-        }
-        a.part2_dh[(int64_t)sl * BH + p] = s;
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        float s = 0.0f;
-        for (int blk0 = sl; blk0 < a.blocks; blk0 += kBatch * kSlices) {
-            float v[kBatch];
-#pragma unroll
-            for (int k = 0; k < kBatch; ++k) {
-                const int blk = blk0 + k * kSlices;
-                v[k] = blk < a.blocks ? a.part_loss[blk] : 0.0f;
-            }
-#pragma unroll
-            for (int k = 0; k < kBatch; ++k)
-                if (blk0 + k * kSlices < a.blocks) s += v[k];
-        }
-        a.part2_loss[sl] = s;
-    }
-}
-
-// One workgroup: sums the slices, then the first layer's gradient through
-// the ReLU.
-__global__ __launch_bounds__(kReduceThreads) void frnn_reduce_kernel(TrainArgs a) {
-    __shared__ float dz[kMaxB][kH];
-    __shared__ float rs[kMaxB * 9];
-    const int tid = threadIdx.x;
-    const int B = a.B;
-    for (int k = tid; k < B * 9; k += kReduceThreads) rs[k] = a.R[k];
-    // the slices are summed in order, with 16 loads in flight per thread
-    for (int p = tid; p < B * kH; p += kReduceThreads) {
-        float s = 0.0f;
-#pragma unroll
-        for (int sl0 = 0; sl0 < kSlices; sl0 += 16) {
-            float v[16];
-#pragma unroll
-            for (int k = 0; k < 16; ++k) v[k] = a.part2_dh[(int64_t)(sl0 + k) * B * kH + p];
-#pragma unroll
-            for (int k = 0; k < 16; ++k) s += v[k];
-        }
-        dz[p / kH][p % kH] = a.z[p] > 0.0f ? s : 0.0f;
-    }
+// The finish kernel: workgroup u sums dh of hidden unit u over the step
+// kernel's workgroups (16 interleaved runs, each in order, then the runs in
+// order) and forms dW1[u], db1[u] through the ReLU; workgroup 0 also the loss.
+__global__ __launch_bounds__(kFinishBlock) void frnn_finish_kernel(TrainArgs a) {
+    constexpr int kRuns = kFinishBlock / kMaxB;
+    static_assert(kMaxB == 64, "a lane per rotation");
+    __shared__ float run[kRuns][kMaxB];
+    const int u = blockIdx.x, b = threadIdx.x & 63, part = threadIdx.x >> 6;
+    float s = 0.0f;
+#pragma unroll 8
+    for (int k = part; k < a.groups; k += kRuns) s += a.part_dh[((int64_t)k * kH + u) * kMaxB + b];
+    run[part][b] = s;
     __syncthreads();
-    for (int p = tid; p < kH * 10; p += kReduceThreads) {
-        if (p < kH * 9) {
-            const int u = p / 9, k = p - u * 9;
-            float s = 0.0f;
-            for (int b = 0; b < B; ++b) s = fmaf(dz[b][u], rs[b * 9 + k], s);
-            a.grad[a.lay.w1 + p] = s;
-        } else {
-            const int u = p - kH * 9;
-            float s = 0.0f;
-            for (int b = 0; b < B; ++b) s += dz[b][u];
-            a.grad[a.lay.b1 + u] = s;
+    const float scale = 1.0f / ((float)a.B * (float)a.lay.O);
+    if (part == 0) {
+        float d = 0.0f;
+        for (int k = 0; k < kRuns; ++k) d += run[k][b];
+        const float* r = a.R + min(b, a.B - 1) * 9;
+        d = b < a.B && hidden(a, u, r) > 0.0f ? d * scale : 0.0f;
+        float mine = 0.0f;   // lane k < 9: dW1[u][k], lane 9: db1[u]
+#pragma unroll
+        for (int k = 0; k < 10; ++k) {
+            float t = k < 9 ? d * r[k] : d;
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+            if (b == k) mine = t;
         }
-    }
-    if (tid == 0 && a.loss_out) {
-        float v[kSlices];
+        if (b < 10) update(a, b < 9 ? a.lay.w1 + u * 9 + b : a.lay.b1 + u, mine);
+    } else if (part == 1 && u == 0 && a.loss_out) {
+        float l = 0.0f;
+        for (int k = b; k < a.groups; k += 64) l += a.part_loss[k];
 #pragma unroll
-        for (int sl = 0; sl < kSlices; ++sl) v[sl] = a.part2_loss[sl];
-        float s = 0.0f;
-#pragma unroll
-        for (int sl = 0; sl < kSlices; ++sl) s += v[sl];
-        a.loss_out[0] = s / ((float)B * (float)a.lay.O);
+        for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off, 64);
+        if (b == 0) a.loss_out[0] = l / ((float)a.B * (float)a.lay.O);
     }
-}
-
-struct AdamArgs {
-    float* p;
-    float* m;
-    float* v;
-    const float* g;
-    int64_t n;
-    float lr, b1, b2, eps, c1, c2;   // c1 = 1 - b1^t, c2 = 1 - b2^t
-};
-
-__global__ __launch_bounds__(256) void frnn_adam_kernel(AdamArgs a) {
-    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (k >= a.n) return;
-    const float g = a.g[k];
-    const float m = fmaf(a.b1, a.m[k], (1.0f - a.b1) * g);
-    const float v = fmaf(a.b2, a.v[k], (1.0f - a.b2) * g * g);
-    a.m[k] = m;
-    a.v[k] = v;
-    a.p[k] -= a.lr * (m / a.c1) / (sqrtf(v / a.c2) + a.eps);
 }
 
 struct EvalArgs {
@@ -372,6 +442,13 @@ int check_m(const char* who, int32_t m) {
 
 size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 
+// Workgroups of the step kernel: a wave per 16 voxels and component, two
+// workgroups a CU at most.
+int64_t step_groups(const Layout& l) {
+    const int64_t units = (l.O + 15) / 16, waves = kStepBlock / 64;
+    return std::min<int64_t>(kStepGroups, (units + waves - 1) / waves);
+}
+
 }  // namespace
 
 LSDF_API int lsdf_frnn_nparam(int32_t m, int64_t* n) {
@@ -391,10 +468,8 @@ LSDF_API int lsdf_frnn_train_workspace_size(int32_t m, int32_t B, size_t* bytes)
     if (rc != LSDF_OK) return rc;
     if (B < 1 || B > kMaxB) return fail(LSDF_E_SHAPE, "frnn_train_workspace_size: B = %d out of [1, %d]", (int)B, kMaxB);
     if (!bytes) return fail(LSDF_E_INVALID_ARG, "frnn_train_workspace_size: bytes is NULL");
-    const Layout l = layout(m);
-    const int64_t blocks = (l.O + kRows - 1) / kRows;
-    *bytes = 2 * align256((size_t)B * kH * 4) + align256((size_t)blocks * B * kH * 4) + align256((size_t)blocks * 4) +
-             align256((size_t)kSlices * B * kH * 4) + align256((size_t)kSlices * 4);
+    const int64_t groups = step_groups(layout(m));
+    *bytes = align256((size_t)groups * kH * kMaxB * 4) + align256((size_t)groups * 4);
     return LSDF_OK;
 }
 
@@ -420,34 +495,29 @@ LSDF_API int lsdf_frnn_train_step(float* params, float* adam_m, float* adam_v, i
     a.lay = layout(m);
     a.params = params;
     a.R = R;
+    a.grad = grad;
+    a.adam_m = adam_m;
+    a.adam_v = adam_v;
+    a.loss_out = loss_out;
     a.m = m;
     a.B = B;
-    a.blocks = (int32_t)((a.lay.O + kRows - 1) / kRows);
-    char* ws = static_cast<char*>(workspace);
-    a.z = reinterpret_cast<float*>(ws);
-    a.h = reinterpret_cast<float*>(ws + align256((size_t)B * kH * 4));
-    a.part_dh = reinterpret_cast<float*>(ws + 2 * align256((size_t)B * kH * 4));
-    const size_t off_loss = 2 * align256((size_t)B * kH * 4) + align256((size_t)a.blocks * B * kH * 4);
-    a.part_loss = reinterpret_cast<float*>(ws + off_loss);
-    const size_t off2 = off_loss + align256((size_t)a.blocks * 4);
-    a.part2_dh = reinterpret_cast<float*>(ws + off2);
-    a.part2_loss = reinterpret_cast<float*>(ws + off2 + align256((size_t)kSlices * B * kH * 4));
-    a.grad = grad;
-    a.loss_out = loss_out;
+    a.groups = (int32_t)step_groups(a.lay);
+    a.part_dh = static_cast<float*>(workspace);
+    a.part_loss = reinterpret_cast<float*>(static_cast<char*>(workspace) + align256((size_t)a.groups * kH * kMaxB * 4));
+    a.lr = lr;
+    a.b1 = beta1;
+    a.b2 = beta2;
+    a.eps = eps;
+    a.c1 = (float)(1.0 / (1.0 - std::pow((double)beta1, (double)t)));
+    a.c2 = (float)(1.0 / (1.0 - std::pow((double)beta2, (double)t)));
     hipStream_t s = as_stream(stream);
-    hipLaunchKernelGGL(frnn_hidden_kernel, dim3((B * kH + 255) / 256), dim3(256), 0, s, a);
-    if ((rc = check_launch("frnn_train_step (hidden)")) != LSDF_OK) return rc;
-    hipLaunchKernelGGL(frnn_output_kernel, dim3((unsigned)a.blocks), dim3(kRows), 0, s, a);
-    if ((rc = check_launch("frnn_train_step (output)")) != LSDF_OK) return rc;
-    hipLaunchKernelGGL(frnn_slice_kernel, dim3((B * kH + 255) / 256, kSlices), dim3(256), 0, s, a);
-    if ((rc = check_launch("frnn_train_step (slices)")) != LSDF_OK) return rc;
-    hipLaunchKernelGGL(frnn_reduce_kernel, dim3(1), dim3(kReduceThreads), 0, s, a);
-    if ((rc = check_launch("frnn_train_step (reduce)")) != LSDF_OK) return rc;
-    if (!adam_m) return LSDF_OK;   // gradient only
-    AdamArgs d{params, adam_m, adam_v, grad, a.lay.n, lr, beta1, beta2, eps,
-               (float)(1.0 - std::pow((double)beta1, (double)t)), (float)(1.0 - std::pow((double)beta2, (double)t))};
-    hipLaunchKernelGGL(frnn_adam_kernel, dim3((unsigned)((a.lay.n + 255) / 256)), dim3(256), 0, s, d);
-    return check_launch("frnn_train_step (adam)");
+    if (adam_m)
+        hipLaunchKernelGGL(frnn_step_kernel<true>, dim3((unsigned)a.groups), dim3(kStepBlock), 0, s, a);
+    else
+        hipLaunchKernelGGL(frnn_step_kernel<false>, dim3((unsigned)a.groups), dim3(kStepBlock), 0, s, a);
+    if ((rc = check_launch("frnn_train_step (step)")) != LSDF_OK) return rc;
+    hipLaunchKernelGGL(frnn_finish_kernel, dim3(kH), dim3(kFinishBlock), 0, s, a);
+    return check_launch("frnn_train_step (finish)");
 }
 
 LSDF_API int lsdf_frnn_max_error(const float* params, int32_t m, const float* R, int64_t N, float* out_max,
