@@ -23,6 +23,9 @@ constexpr int kQueryBlock = 768;
 constexpr int kQueryWaves = kQueryBlock / 64;
 constexpr int kTileChunk = 8;               // 32-pair tiles a wave takes at a time: 256 points of one configuration
 constexpr int kChunkPts = kTileChunk * TILE;
+constexpr int kRounds = kChunkPts / 64;      // a chunk's points, one per lane
+constexpr int kMaxTake = 16;                // chunks a wave takes at a time, at most
+constexpr int kQueueCap = TILE + kChunkPts;        // pairs waiting: fewer than a tile, and a chunk's
 
 struct Domain {
     float cen[3];
@@ -60,6 +63,19 @@ __device__ inline bool sphere_beyond(const float4& sph, const float (&R)[9], con
     return (core_distance(u[0], u[1], u[2], dm.core) - sph.w) - dm.bound > thr;
 }
 
+// A pose's rotation (row-major) and translation.
+struct Pose {
+    float R[9], t[3];
+};
+__device__ inline void load_pose(const float* T, Pose& o) {
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+#pragma unroll
+        for (int s = 0; s < 3; ++s) o.R[3 * r + s] = T[4 * r + s];
+        o.t[r] = T[4 * r + 3];
+    }
+}
+
 __device__ inline float wave_min(float v) {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) v = fminf(v, __shfl_xor(v, off, 64));
@@ -86,8 +102,8 @@ struct EvalArgs {
 };
 
 __global__ __launch_bounds__(kBlock) void mlp_eval_kernel(EvalArgs p) {
-    __shared__ __bf16 sW2[WTILE_ELEMS];
-    __shared__ __bf16 sW3[WTILE_ELEMS];
+    __shared__ __align__(16) __bf16 sW2[WTILE_ELEMS];
+    __shared__ __align__(16) __bf16 sW3[WTILE_ELEMS];
     __shared__ SmallParams sp;
     stage_weights(sW2, p.params + OFF_W2, false);
     stage_weights(sW3, p.params + OFF_W3, false);
@@ -134,35 +150,69 @@ struct QueryMlpArgs {
     const float* points;
     uint32_t* keys;
     const float* ubound;     // [C][L] upper bounds U of the first kernel, or NULL (no bound: no skipping)
-    const float4* tile_sph;  // [ceil(M / 32)] spheres bounding each tile's points (when ubound != NULL)
-    const float4* chunk_sph; // [ceil(M / 256)] spheres bounding each chunk's points
+    const float4* chunk_sph; // [ceil(M / 256)] spheres bounding each chunk's points (when ubound != NULL)
     const int32_t* seed;     // [2][C][L] the chunks holding the pair that gave U and the sampled pair
                              // nearest the core box (-1: none), taken first
     int64_t M;
-    int64_t tiles_per_link;
-    int32_t tiles_per_c;
+    int32_t take;            // chunks a wave takes at a time
     int32_t C;
     int32_t L;
     float margin;
 };
 
+// The value of E - B above which a pair of (c, i) cannot hold its minimum: the
+// upper bound U, the smallest value found so far by any wave (the key; a stale
+// read is larger, so still a bound from above), and the margin, below which a
+// pair may take the grid's value.
+__device__ inline float threshold(const QueryMlpArgs& p, int c, int i) {
+    float lim = p.ubound[(int64_t)c * p.L + i];
+    const uint32_t kv = __hip_atomic_load(&p.keys[(int64_t)c * p.L + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (kv) lim = fminf(lim, lsdf::from_ordered_bits(~kv));
+    return fmaxf(lim, p.margin);
+}
+
+// Orders one wave's accesses to its queue (the hardware keeps them in order;
+// this keeps the compiler from moving them).
+__device__ inline void queue_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// A pair waiting for the network: its point relative to the domain centre, its
+// configuration, and the point's number (for the grid's value).
+struct PairQueue {
+    float4 u_c[kQueryWaves][kQueueCap];   // u, configuration bits
+    int64_t point[kQueryWaves][kQueueCap];
+};
+
+// The clearance query.  Every workgroup takes every link in turn (its weights
+// staged once per link); a link's chunks (256 points of one configuration) are
+// dealt round-robin to the workgroups, and a workgroup's waves take them a
+// few at a time from a counter in LDS: the pairs a bounded query must
+// evaluate cluster (points near a link, at configurations near the obstacle),
+// so a fixed share per wave would leave the workgroup waiting on its busiest
+// wave at every link.  A lane tests one of the chunks taken; the pairs of those
+// that pass are tested one per lane, and the pairs that may hold a minimum wait
+// in a queue of the wave's, from which the network takes 32 at a time,
+// whichever chunks and configurations they came from.  (Evaluating every
+// 16-pair half of a tile that held one such pair ran the network on 1.4 times
+// the pairs, and each pair was tested by four lanes.)
+// Bound by the VALU work of the network's SiLUs (72 % VALU busy): 500 x 100,000
+// x 7 with the network on 5.7 % of the pairs 4.69 -> 3.26 ms, 60 x 8,000 x 7
+// 0.80 -> 0.20 ms.
 template <bool CUBIC, int DT>
 // The register budget of 3 waves per SIMD (168 VGPRs) also schedules the tile
 // loop better than the default 2 (248).
 __global__ __launch_bounds__(kQueryBlock) __attribute__((amdgpu_waves_per_eu(3, 3))) void query_mlp_kernel(QueryMlpArgs p) {
-    __shared__ __bf16 sW2[WTILE_ELEMS];
-    __shared__ __bf16 sW3[WTILE_ELEMS];
+    __shared__ __align__(16) __bf16 sW2[WTILE_ELEMS];
+    __shared__ __align__(16) __bf16 sW3[WTILE_ELEMS];
     __shared__ SmallParams sp;
+    __shared__ PairQueue sq;
+    __shared__ int s_next;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // every workgroup takes every link in turn (its weights staged once per
-    // link); a link's chunks (kTileChunk tiles, 256 points of one
-    // configuration) are dealt round-robin to the workgroups, and a
-    // workgroup's waves take its chunks one at a time from a counter in LDS:
-    // the tiles a bounded query must evaluate cluster (points near a link, at
-    // configurations near the obstacle), so a fixed share per wave would
-    // leave the workgroup waiting on its busiest wave at every link
-    __shared__ int s_next;
+    float4* const q_u = sq.u_c[wave];
+    int64_t* const q_j = sq.point[wave];
     const int64_t groups = (p.M + kChunkPts - 1) / kChunkPts;   // chunks per configuration
     const int64_t nchunks = (int64_t)p.C * groups;
     // a bounded query first takes, per configuration, the chunk that holds the
@@ -184,178 +234,194 @@ __global__ __launch_bounds__(kQueryBlock) __attribute__((amdgpu_waves_per_eu(3, 
         const LinkGrid& lg = p.link[i];
         const Domain& dm = p.dom[i];
         const typename GridT<DT>::T* G = static_cast<const typename GridT<DT>::T*>(p.grid) + lg.offset;
-        float best = INFINITY;
-        int cur = -1;
-        GridMap gm{};
-        float R[9] = {}, tr[3] = {};
-        float thr = INFINITY;   // tiles whose pairs all have E - B above this are skipped
-        float ub_c = INFINITY;  // the current configuration's upper bound U
-        int64_t seed_c = -1, near_c = -1;   // and its seed chunks
-        auto flush = [&](int c) {
-            const float w = wave_min(best);
-            if (lane == 0 && w < INFINITY) atomicMax(&p.keys[(int64_t)c * p.L + i], ~lsdf::ordered_bits(w));
-            best = INFINITY;
+        int run_c = -1;          // configuration whose minimum so far is `run` (unbounded query)
+        float run = INFINITY;
+        int waiting = 0;         // pairs in the queue, wave-uniform, below kBatch between rounds
+        auto put = [&](int c, float v) {
+            if (v < INFINITY) atomicMax(&p.keys[(int64_t)c * p.L + i], ~lsdf::ordered_bits(v));
+        };
+        // the network on the last n <= TILE pairs of the queue
+        auto evaluate = [&](int n) {
+            waiting -= n;
+            queue_fence();
+            float xh[NT][3], e[NT], m[NT];
+            int c[NT];
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                const float4 q = q_u[waiting + min(16 * nt + (lane & 15), n - 1)];
+                const float u[3] = {q.x, q.y, q.z};
+#pragma unroll
+                for (int a = 0; a < 3; ++a) xh[nt][a] = u[a] * dm.inv[a];
+                e[nt] = core_distance(u[0], u[1], u[2], dm.core);
+                c[nt] = __float_as_int(q.w);
+            }
+            static_assert(NT == 2, "a batch of two 16-pair halves");
+            forward_tile<NT>(sW2, sW3, &sp, xh, m);
+            float best = INFINITY;
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                float v = INFINITY;
+                if (lane < 16 && 16 * nt + lane < n) {
+                    // below the margin the grid's value replaces the estimate;
+                    // a point outside the grid box keeps the estimate, since
+                    // the grid has no value there
+                    float tb;
+                    const float est = bounded_share(m[nt], dm.bound, dm.inv_bound, tb) + e[nt];
+                    v = est;
+                    if (est < p.margin) {
+                        const float* x = p.points + 3 * q_j[waiting + 16 * nt + lane];
+                        const GridMap gm = grid_map(lg, p.link_T + ((int64_t)c[nt] * p.L + i) * 12);
+                        const float g = sample_or_inf<CUBIC, DT>(G, lg, gm, x[0], x[1], x[2]);
+                        if (g < INFINITY) v = g;
+                    }
+                }
+                m[nt] = v;
+                best = fminf(best, v);
+            }
+            const int c0 = __builtin_amdgcn_readfirstlane(c[0]);
+            if (__ballot(c[0] != c0 || c[1] != c0)) {   // pairs of several configurations
+                if (lane < 16) {
+                    put(c[0], m[0]);
+                    put(c[1], m[1]);
+                }
+            } else if (p.ubound) {
+                // the minimum goes to the key at once, so that later chunks of
+                // (c, i), on any wave, skip against it
+                best = wave_min(best);
+                if (lane == 0) put(c0, best);
+            } else {
+                if (c0 != run_c) {
+                    if (run_c >= 0 && lane == 0) put(run_c, run);
+                    run_c = c0;
+                    run = INFINITY;
+                }
+                run = fminf(run, wave_min(best));
+            }
+            queue_fence();
         };
         for (;;) {
             int slot = 0;
-            if (lane == 0) slot = atomicAdd(&s_next, 1);
-            slot = __builtin_amdgcn_readfirstlane(__shfl(slot, 0, 64));
-            const int64_t vs = (int64_t)blockIdx.x + (int64_t)slot * gridDim.x;
-            if (vs >= nseed + nchunks) break;
-            int c;
-            int64_t grp;
-            if (vs < nseed) {
-                c = (int)(vs < p.C ? vs : vs - p.C);
-                grp = p.seed[vs * p.L + i];
-                // the near chunk when it is not the first one already
-                if (grp < 0 || (vs >= p.C && grp == p.seed[(int64_t)c * p.L + i])) continue;
-            } else {
-                c = (int)((vs - nseed) / groups);
-                grp = (vs - nseed) - (int64_t)c * groups;
-            }
-            if (c != cur) {
-                if (cur >= 0 && !p.ubound) flush(cur);   // (a bounded query flushes every chunk)
-                cur = c;
-                const float* T = p.link_T + ((int64_t)c * p.L + i) * 12;
-                gm = grid_map(lg, T);
-                for (int r = 0; r < 3; ++r) {
-                    for (int s = 0; s < 3; ++s) R[3 * r + s] = T[4 * r + s];
-                    tr[r] = T[4 * r + 3];
-                }
-                if (p.ubound) ub_c = p.ubound[(int64_t)c * p.L + i];
-                if (p.seed) {
-                    seed_c = p.seed[(int64_t)c * p.L + i];
-                    near_c = p.seed[((int64_t)p.C + c) * p.L + i];
-                }
-            }
-            if (vs >= nseed && (grp == seed_c || grp == near_c)) continue;   // taken in the seed slots
-            if (p.ubound) {
-                // the threshold also falls to the smallest value found so far
-                // for (c, i) by any wave (the key; a stale read is larger, so
-                // still a bound of the minimum from above)
-                float lim = ub_c;
-                const uint32_t kv =
-                    __hip_atomic_load(&p.keys[(int64_t)c * p.L + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (kv) lim = fminf(lim, lsdf::from_ordered_bits(~kv));
-                thr = fmaxf(lim, p.margin);
-            }
-            // a chunk (then a tile) whose bounding sphere keeps every pair's
-            // E - B above thr is skipped whole: E is 1-Lipschitz in the
-            // link-frame point, so E >= E(centre) - radius over the sphere
-            // (the radius is widened far beyond the FP32 rounding of E)
-            if (p.ubound && sphere_beyond(p.chunk_sph[grp], R, tr, dm, thr)) continue;
-            for (int64_t k = grp * kTileChunk; k < min((grp + 1) * kTileChunk, (int64_t)p.tiles_per_c); ++k) {
-                if (p.ubound && sphere_beyond(p.tile_sph[k], R, tr, dm, thr)) continue;
-                const int64_t j0 = k * TILE;
-                float xh[NT][3], px[NT][3], e[NT];
-                bool indom[NT];
-                bool any[NT];
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) {
-                    const int64_t j = j0 + 16 * nt + (lane & 15);
-                    const int64_t jj = min(j, p.M - 1);
-                    px[nt][0] = p.points[3 * jj + 0];
-                    px[nt][1] = p.points[3 * jj + 1];
-                    px[nt][2] = p.points[3 * jj + 2];
-                    float u[3];
-                    const bool in = pair_frame(R, tr, dm, px[nt][0], px[nt][1], px[nt][2], u, xh[nt]);
-                    e[nt] = core_distance(u[0], u[1], u[2], dm.core);
-                    indom[nt] = (j < p.M) && in;
-                    // a pair with E - B above thr cannot hold the minimum (its
-                    // value exceeds the value of some pair: a found minimum,
-                    // or the upper bound U of a pair that cannot fall back)
-                    any[nt] = __ballot(indom[nt] && (e[nt] - dm.bound <= thr)) != 0;
-                }
-                static_assert(NT == 2, "a tile of two 16-pair halves");
-                if (!any[0] && !any[1]) continue;
-                float m[NT];
-                if (any[0] && any[1]) {
-                    forward_tile<NT>(sW2, sW3, &sp, xh, m);
+            if (lane == 0) slot = atomicAdd(&s_next, p.take);
+            slot = __builtin_amdgcn_readfirstlane(slot);
+            const int64_t v0 = (int64_t)blockIdx.x + (int64_t)slot * gridDim.x;
+            if (v0 >= nseed + nchunks) break;
+            // a lane per chunk taken: its configuration and whether it is to be
+            // done at all (a chunk whose bounding sphere keeps every pair's E - B
+            // above the threshold is not: E is 1-Lipschitz in the link-frame
+            // point, so E >= E(centre) - radius over the sphere, the radius
+            // widened far beyond the FP32 rounding of E)
+            const int64_t vs = v0 + (int64_t)lane * gridDim.x;
+            bool take = lane < p.take && vs < nseed + nchunks;
+            int c = 0, grp = 0;
+            if (take) {
+                if (vs < nseed) {
+                    c = (int)(vs < p.C ? vs : vs - p.C);
+                    grp = p.seed[vs * p.L + i];
+                    // the near chunk when it is not the first one already
+                    take = grp >= 0 && !(vs >= p.C && grp == p.seed[(int64_t)c * p.L + i]);
                 } else {
-                    // only one half may hold the minimum: the network runs on
-                    // that half alone (each 16-pair half is its own MFMA
-                    // column group, so its values are the same bits), and the
-                    // other half's pairs are skipped like a whole tile's
-                    const bool h0 = any[0];
-                    const float xs[1][3] = {{h0 ? xh[0][0] : xh[1][0], h0 ? xh[0][1] : xh[1][1],
-                                             h0 ? xh[0][2] : xh[1][2]}};
-                    float m1[1];
-                    forward_tile<1>(sW2, sW3, &sp, xs, m1);
-                    m[0] = m1[0];
-                    m[1] = m1[0];
-                    if (h0) indom[1] = false; else indom[0] = false;
-                }
-                if (lane < 16) {
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt) {
-                        if (!indom[nt]) continue;
-                        // below the margin the grid's value replaces the estimate;
-                        // a point outside the grid box keeps the estimate, since
-                        // the grid has no value there
-                        float tb;
-                        const float est = bounded_share(m[nt], dm.bound, dm.inv_bound, tb) + e[nt];
-                        float v = est;
-                        if (est < p.margin) {
-                            const float g = sample_or_inf<CUBIC, DT>(G, lg, gm, px[nt][0], px[nt][1], px[nt][2]);
-                            if (g < INFINITY) v = g;
-                        }
-                        best = fminf(best, v);
-                    }
+                    c = (int)((vs - nseed) / groups);
+                    grp = (int)((vs - nseed) - (int64_t)c * groups);
+                    if (p.seed)   // taken in the seed slots
+                        take = grp != p.seed[(int64_t)c * p.L + i] && grp != p.seed[((int64_t)p.C + c) * p.L + i];
                 }
             }
-            // this chunk's minimum goes to the key at once, so that later
-            // chunks of (c, i), on any wave, skip against it
-            if (p.ubound) flush(c);
+            if (take && p.ubound) {
+                Pose o;
+                load_pose(p.link_T + ((int64_t)c * p.L + i) * 12, o);
+                take = !sphere_beyond(p.chunk_sph[grp], o.R, o.t, dm, threshold(p, c, i));
+            }
+            // a chunk's points, fetched while the chunk before it is evaluated
+            float x[kRounds][3];
+            auto fetch = [&](int g) {
+                const int64_t j0 = (int64_t)g * kChunkPts + lane;
+#pragma unroll
+                for (int r = 0; r < kRounds; ++r)
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) x[r][a] = p.points[3 * min(j0 + 64 * r, p.M - 1) + a];
+            };
+            uint64_t left = __ballot(take);
+            if (left) fetch(__builtin_amdgcn_readlane(grp, __builtin_ctzll(left)));
+            while (left) {   // wave-uniform
+                const int from = __builtin_ctzll(left);
+                left &= left - 1;
+                const int cc = __builtin_amdgcn_readlane(c, from);
+                const int64_t j0 = (int64_t)__builtin_amdgcn_readlane(grp, from) * kChunkPts + lane;
+                Pose o;
+                load_pose(p.link_T + ((int64_t)cc * p.L + i) * 12, o);
+                // the threshold again: it may have fallen since
+                const float thr = p.ubound ? threshold(p, cc, i) : INFINITY;
+                // a pair with E - B above thr cannot hold the minimum (its value
+                // exceeds the value of some pair: a found minimum, or the upper
+                // bound U of a pair that cannot fall back); compared squared,
+                // with room for the rounding on either side (a pair too many
+                // changes nothing)
+                const float reach = fmaxf(thr + dm.bound, 0.0f) * 1.00001f + 1e-6f, reach2 = reach * reach;
+                float u[kRounds][3];
+                uint64_t mask[kRounds];
+#pragma unroll
+                for (int r = 0; r < kRounds; ++r) {
+                    float xh[3];
+                    const bool in = pair_frame(o.R, o.t, dm, x[r][0], x[r][1], x[r][2], u[r], xh);
+                    mask[r] = __ballot(j0 + 64 * r < p.M && in && core_distance2(u[r][0], u[r][1], u[r][2], dm.core) <= reach2);
+                }
+#pragma unroll
+                for (int r = 0; r < kRounds; ++r) {
+                    if (mask[r] >> lane & 1) {
+                        const int at = waiting + __builtin_popcountll(mask[r] & ((1ull << lane) - 1));
+                        q_u[at] = make_float4(u[r][0], u[r][1], u[r][2], __int_as_float(cc));
+                        q_j[at] = j0 + 64 * r;
+                    }
+                    waiting += __builtin_popcountll(mask[r]);
+                }
+                if (left) fetch(__builtin_amdgcn_readlane(grp, __builtin_ctzll(left)));
+                while (waiting >= TILE) evaluate(TILE);
+            }
         }
-        if (cur >= 0) flush(cur);
+        if (waiting > 0) evaluate(waiting);
+        if (run_c >= 0 && lane == 0) put(run_c, run);
     }
 }
 
-// Bounding spheres of the learned query's point tiles (32 points) and chunks
-// (256 points), one thread per tile: the centre of the points' box and the
-// largest distance to it, widened by a relative 1e-5 and by 1e-4 m, which
-// covers the FP32 rounding of the pose and of E (about 1e-6 m on clouds a few
-// metres across) many times over.  A chunk's sphere bounds its tiles'
-// spheres (eight adjacent lanes combine by shuffles).
-__global__ __launch_bounds__(256) void mlp_sphere_kernel(const float* __restrict__ points, int64_t M,
-                                                         float4* tile_sph, float4* chunk_sph) {
+// Bounding spheres of the learned query's chunks (256 points), eight lanes per
+// chunk, 32 points each: the centre of the points' box and the largest
+// distance to it, widened by a relative 1e-5 and by 1e-4 m, which covers the
+// FP32 rounding of the pose and of E (about 1e-6 m on clouds a few metres
+// across) many times over.
+__global__ __launch_bounds__(256) void mlp_sphere_kernel(const float* __restrict__ points, int64_t M, float4* chunk_sph) {
     const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t nt = (M + TILE - 1) / TILE;
     float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    const int64_t j0 = k * TILE, j1 = min(j0 + TILE, M);
-    for (int64_t j = j0; j < j1; ++j)
+    const int64_t j0 = k / kTileChunk * kChunkPts + k % kTileChunk;   // every eighth point
+#pragma unroll 8
+    for (int t = 0; t < TILE; ++t) {
+        const int64_t j = min(j0 + t * kTileChunk, M - 1);
+#pragma unroll
         for (int a = 0; a < 3; ++a) {
             lo[a] = fminf(lo[a], points[3 * j + a]);
             hi[a] = fmaxf(hi[a], points[3 * j + a]);
         }
+    }
     float cen[3];
-    for (int a = 0; a < 3; ++a) cen[a] = 0.5f * (lo[a] + hi[a]);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+#pragma unroll
+        for (int o = 1; o < kTileChunk; o <<= 1) {
+            lo[a] = fminf(lo[a], __shfl_xor(lo[a], o, 64));
+            hi[a] = fmaxf(hi[a], __shfl_xor(hi[a], o, 64));
+        }
+        cen[a] = 0.5f * (lo[a] + hi[a]);
+    }
     float r2 = 0.0f;
-    for (int64_t j = j0; j < j1; ++j) {
+#pragma unroll 8
+    for (int t = 0; t < TILE; ++t) {
+        const int64_t j = min(j0 + t * kTileChunk, M - 1);
         const float dx = points[3 * j] - cen[0], dy = points[3 * j + 1] - cen[1], dz = points[3 * j + 2] - cen[2];
         r2 = fmaxf(r2, fmaf(dx, dx, fmaf(dy, dy, dz * dz)));
     }
-    const float r = fmaf(sqrtf(r2), 1.00001f, 1e-4f);
-    if (k < nt) tile_sph[k] = make_float4(cen[0], cen[1], cen[2], r);
-    // the chunk: box of the eight tiles' boxes, then the farthest tile sphere
-    float clo[3], chi[3];
-    for (int a = 0; a < 3; ++a) {
-        clo[a] = lo[a];
-        chi[a] = hi[a];
-        for (int o = 1; o < kTileChunk; o <<= 1) {
-            clo[a] = fminf(clo[a], __shfl_xor(clo[a], o, 64));
-            chi[a] = fmaxf(chi[a], __shfl_xor(chi[a], o, 64));
-        }
-    }
-    float cc[3];
-    for (int a = 0; a < 3; ++a) cc[a] = 0.5f * (clo[a] + chi[a]);
-    float rr = 0.0f;
-    if (k < nt) {
-        const float dx = cen[0] - cc[0], dy = cen[1] - cc[1], dz = cen[2] - cc[2];
-        rr = sqrtf(fmaf(dx, dx, fmaf(dy, dy, dz * dz))) + r;
-    }
-    for (int o = 1; o < kTileChunk; o <<= 1) rr = fmaxf(rr, __shfl_xor(rr, o, 64));
-    if (k < nt && k % kTileChunk == 0) chunk_sph[k / kTileChunk] = make_float4(cc[0], cc[1], cc[2], fmaf(rr, 1.00001f, 1e-4f));
+#pragma unroll
+    for (int o = 1; o < kTileChunk; o <<= 1) r2 = fmaxf(r2, __shfl_xor(r2, o, 64));
+    if (k % kTileChunk == 0 && k / kTileChunk * kChunkPts < M)
+        chunk_sph[k / kTileChunk] = make_float4(cen[0], cen[1], cen[2], fmaf(sqrtf(r2), 1.00001f, 1e-4f));
 }
 
 // First kernel of a bounded learned query: per (configuration c, link i),
@@ -497,8 +563,7 @@ struct TrainArgs {
 // SiLU(z) and SiLU'(z) share one sigmoid, s = 1 / (1 + exp(-z)):
 // SiLU = z s, SiLU' = s (1 + z (1 - s)).  SiLU'(z2) and SiLU'(z3) of every
 // unit a lane holds are kept for the backward pass; SiLU'(z1), needed last,
-// is recomputed from the inputs then (the same bits, three FMA and the
-// sigmoid per unit), which keeps the kernel within its registers.  A
+// is recomputed from the inputs then (the same bits), which keeps the kernel within its registers.  A
 // lane's units in a result tile (16 mt + 4 g + r) are the units of its B
 // operand slots (perm_unit), so the kept derivatives line up with the
 // backward products with no exchange.
@@ -513,10 +578,10 @@ constexpr int kTrainWaves = kTrainBlock / 64;
 static_assert(kSplit % (TILE_TRAIN * kTrainWaves) == 0, "a batch of whole workgroups");
 
 __global__ __launch_bounds__(kTrainBlock) void train_fwdbwd_kernel(TrainArgs p) {
-    __shared__ __bf16 sW2[WTILE_ELEMS];
-    __shared__ __bf16 sW3[WTILE_ELEMS];
-    __shared__ __bf16 sW3t[WTILE_ELEMS];
-    __shared__ __bf16 sW2t[WTILE_ELEMS];
+    __shared__ __align__(16) __bf16 sW2[WTILE_ELEMS];
+    __shared__ __align__(16) __bf16 sW3[WTILE_ELEMS];
+    __shared__ __align__(16) __bf16 sW3t[WTILE_ELEMS];
+    __shared__ __align__(16) __bf16 sW2t[WTILE_ELEMS];
     __shared__ SmallParams sp;
     const int l = blockIdx.y;
     const float* P = p.params + (int64_t)l * NPARAM;
@@ -557,16 +622,17 @@ __global__ __launch_bounds__(kTrainBlock) void train_fwdbwd_kernel(TrainArgs p) 
     // ---- forward ----
     float g2[8][4], g3[8][4];   // SiLU' of this lane's units
     bf16x8 b[4];
+    const float xk = input_operand(xh, g);
 #pragma unroll
-    for (int s = 0; s < 4; ++s)
+    for (int mt = 0; mt < 8; ++mt) {
+        const f32x4 z = input_layer(&sp, mt, lane, xk);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int u = perm_unit(s, 8 * g + e);
-            const float z = fmaf(sp.w1[u][0], xh[0], fmaf(sp.w1[u][1], xh[1], fmaf(sp.w1[u][2], xh[2], sp.b1[u])));
-            const __bf16 h = (__bf16)silu(z);
-            b[s][e] = h;
-            p.w.h1[plane + u * B + c] = h;
+        for (int r = 0; r < 4; ++r) {
+            const __bf16 h = (__bf16)silu(z[r]);
+            b[mt >> 1][(mt & 1) * 4 + r] = h;
+            p.w.h1[plane + (16 * mt + 4 * g + r) * B + c] = h;
         }
+    }
     float m = 0.0f;
 #pragma unroll
     for (int layer = 0; layer < 2; ++layer) {
@@ -657,7 +723,8 @@ __global__ __launch_bounds__(kTrainBlock) void train_fwdbwd_kernel(TrainArgs p) 
             for (int s = 0; s < 4; ++s)
                 acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lds_a(sW, mt, s, lane), b[s], acc[mt], 0, 0, 0);
 #pragma unroll
-        for (int mt = 0; mt < 8; ++mt)
+        for (int mt = 0; mt < 8; ++mt) {
+            const f32x4 z1 = layer == 0 ? f32x4{} : input_layer(&sp, mt, lane, xk);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int u = 16 * mt + 4 * g + r;
@@ -668,10 +735,10 @@ __global__ __launch_bounds__(kTrainBlock) void train_fwdbwd_kernel(TrainArgs p) 
                     p.w.dz2[plane + u * B + c] = db;
                 } else {
                     // dz1 = (W2^T dz2) * SiLU'(z1), kept in FP32
-                    const float z = fmaf(sp.w1[u][0], xh[0], fmaf(sp.w1[u][1], xh[1], fmaf(sp.w1[u][2], xh[2], sp.b1[u])));
-                    p.w.dz1[plane + u * B + c] = acc[mt][r] * silu_grad_of(z, sigmoid(z));
+                    p.w.dz1[plane + u * B + c] = acc[mt][r] * silu_grad_of(z1[r], sigmoid(z1[r]));
                 }
             }
+        }
     }
 }
 
@@ -1043,26 +1110,27 @@ LSDF_API int lsdf_query_min_distance_mlp(const float* link_T, int32_t C, int32_t
     a.C = C;
     a.L = L;
     a.margin = margin;
-    a.tiles_per_c = (int32_t)((M + TILE - 1) / TILE);
-    a.tiles_per_link = (int64_t)C * a.tiles_per_c;
-    if (a.tiles_per_link > 0) {
+    const int64_t chunks = (int64_t)C * ((M + kChunkPts - 1) / kChunkPts);
+    if (chunks > 0) {
         const int cus = device_cus();
         if (cus <= 0) return fail(LSDF_E_DEVICE, "query_mlp: cannot read the device's compute-unit count");
         // one workgroup per CU (each takes every link in turn), no more than
         // the chunks of one link need
-        const int64_t chunks = (a.tiles_per_link + kTileChunk - 1) / kTileChunk;
         const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>(cus, (chunks + kQueryWaves - 1) / kQueryWaves)));
         if ((rc = launch_zero_words(a.keys, (int64_t)C * L, s)) != LSDF_OK) return rc;
+        // a wave comes back for more about 8 times, so that the last ones taken
+        // even the waves out (big batches of chunks cost less each: 8 a time
+        // 3.74 ms, 4 or 16 4.0 and 3.9 ms for 500 x 100,000 x 7)
+        a.take = (int32_t)std::max<int64_t>(1, std::min<int64_t>(kMaxTake, chunks / (8 * kQueryWaves * (int64_t)grid.x)));
         bool bounded = false;
         for (int i = 0; i < L; ++i) bounded = bounded || a.dom[i].inv_bound != 0.0f;
         if (bounded) {
             // the upper bounds, after the keys in the workspace (which holds
             // the plain query's tables too, far more than C L words)
             float* ub = reinterpret_cast<float*>(static_cast<char*>(workspace) + ((size_t)C * L * 4 + 255) / 256 * 256);
-            // then the tile and chunk spheres and the seed chunks
+            // then the chunk spheres and the seed chunks
             const int64_t nt = (M + TILE - 1) / TILE;
-            float4* tsph = reinterpret_cast<float4*>(reinterpret_cast<char*>(ub) + ((size_t)C * L * 4 + 255) / 256 * 256);
-            float4* csph = tsph + (nt + 15) / 16 * 16;
+            float4* csph = reinterpret_cast<float4*>(reinterpret_cast<char*>(ub) + ((size_t)C * L * 4 + 255) / 256 * 256);
             int32_t* seed = reinterpret_cast<int32_t*>(csph + (nt + kTileChunk - 1) / kTileChunk);
             const size_t used = static_cast<size_t>(reinterpret_cast<char*>(seed + 2 * (int64_t)C * L) -
                                                     static_cast<char*>(workspace));
@@ -1080,11 +1148,9 @@ LSDF_API int lsdf_query_min_distance_mlp(const float* link_T, int32_t C, int32_t
             hipLaunchKernelGGL(mlp_bound_kernel, dim3((unsigned)((C + kBoundConfigs - 1) / kBoundConfigs), L),
                                dim3(kBoundBlock), 0, s, b);
             if ((rc = check_launch("query_min_distance_mlp bounds")) != LSDF_OK) return rc;
-            hipLaunchKernelGGL(mlp_sphere_kernel, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, s, points, M, tsph,
-                               csph);
+            hipLaunchKernelGGL(mlp_sphere_kernel, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, s, points, M, csph);
             if ((rc = check_launch("query_min_distance_mlp spheres")) != LSDF_OK) return rc;
             a.ubound = ub;
-            a.tile_sph = tsph;
             a.chunk_sph = csph;
             a.seed = seed;
         }
@@ -1102,7 +1168,7 @@ LSDF_API int lsdf_query_min_distance_mlp(const float* link_T, int32_t C, int32_t
         if ((rc = check_launch("query_min_distance_mlp")) != LSDF_OK) return rc;
         if (ev1 && hipEventRecord(ev1, s) != hipSuccess) return fail(LSDF_E_DEVICE, "query_mlp: event record failed");
     }
-    return lsdf::launch_query_finalize(a.tiles_per_link > 0 ? a.keys : nullptr, out_dist, out_link, out_link_dist, C, L,
+    return lsdf::launch_query_finalize(chunks > 0 ? a.keys : nullptr, out_dist, out_link, out_link_dist, C, L,
                                        s);
 }
 

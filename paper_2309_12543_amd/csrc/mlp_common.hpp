@@ -56,7 +56,7 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
 // Small FP32 parameters kept in LDS (W1 and w4 already rounded to bf16).
 struct SmallParams {
-    float w1[H][3];
+    float w1[4][H];   // columns 2, 1, 0 of W1, then zeros: the input layer's K order
     float b1[H];
     float b2[H];
     float b3[H];
@@ -75,11 +75,14 @@ __device__ inline float bf16_round(float x) { return (float)(__bf16)x; }
 // Core term of the estimate: the distance from a link-frame point to the
 // link's core box, given u = l - centre and the box's half extents k:
 // || max(|u| - k, 0) ||, the square root correctly rounded.
-__device__ inline float core_distance(float ux, float uy, float uz, const float (&k)[3]) {
+__device__ inline float core_distance2(float ux, float uy, float uz, const float (&k)[3]) {
     const float qx = fmaxf(fabsf(ux) - k[0], 0.0f);
     const float qy = fmaxf(fabsf(uy) - k[1], 0.0f);
     const float qz = fmaxf(fabsf(uz) - k[2], 0.0f);
-    return __builtin_sqrtf(fmaf(qx, qx, fmaf(qy, qy, qz * qz)));
+    return fmaf(qx, qx, fmaf(qy, qy, qz * qz));
+}
+__device__ inline float core_distance(float ux, float uy, float uz, const float (&k)[3]) {
+    return __builtin_sqrtf(core_distance2(ux, uy, uz, k));
 }
 
 // sigmoid(z) = 1 / (1 + exp(-z)); SiLU(z) = z sigmoid(z) and
@@ -110,6 +113,25 @@ __device__ inline float silu_grad_of(float z, float s) { return s * (1.0f + z * 
 // units and K runs over input units (forward); transpose = true: rows are
 // input units and K runs over output units (backward, W^T).
 __device__ inline void stage_weights(__bf16* dst, const float* __restrict__ W, bool transpose) {
+    typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));   // rows start at any element
+    if (!transpose) {
+        // a lane's 8 elements are two runs of 4 in a row: two vector loads and
+        // one LDS store (element by element, a workgroup waited on 43 loads in
+        // turn for every matrix)
+        for (int idx = threadIdx.x; idx < WTILE_ELEMS / 8; idx += blockDim.x) {
+            const int lane = idx & 63, s = (idx >> 6) & 3, mt = idx >> 8;
+            const float* row = W + (16 * mt + (lane & 15)) * H + 32 * s + 4 * (lane >> 4);
+            const f32x4_any lo = *reinterpret_cast<const f32x4_any*>(row), hi = *reinterpret_cast<const f32x4_any*>(row + 16);
+            bf16x8 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                v[e] = (__bf16)lo[e];
+                v[4 + e] = (__bf16)hi[e];
+            }
+            *reinterpret_cast<bf16x8*>(dst + 8 * idx) = v;
+        }
+        return;
+    }
     for (int idx = threadIdx.x; idx < WTILE_ELEMS; idx += blockDim.x) {
         const int e = idx & 7;
         const int lane = (idx >> 3) & 63;
@@ -117,14 +139,13 @@ __device__ inline void stage_weights(__bf16* dst, const float* __restrict__ W, b
         const int mt = idx >> 11;
         const int row = 16 * mt + (lane & 15);
         const int k = perm_unit(s, 8 * (lane >> 4) + e);
-        const float v = transpose ? W[k * H + row] : W[row * H + k];
-        dst[idx] = (__bf16)v;
+        dst[idx] = (__bf16)W[k * H + row];
     }
 }
 
 __device__ inline void stage_small(SmallParams* sp, const float* __restrict__ P) {
     for (int u = threadIdx.x; u < H; u += blockDim.x) {
-        for (int k = 0; k < 3; ++k) sp->w1[u][k] = bf16_round(P[OFF_W1 + 3 * u + k]);
+        for (int k = 0; k < 4; ++k) sp->w1[k][u] = k < 3 ? bf16_round(P[OFF_W1 + 3 * u + 2 - k]) : 0.0f;
         sp->b1[u] = P[OFF_B1 + u];
         sp->b2[u] = P[OFF_B2 + u];
         sp->b3[u] = P[OFF_B3 + u];
@@ -136,6 +157,22 @@ __device__ inline void stage_small(SmallParams* sp, const float* __restrict__ P)
 
 __device__ inline bf16x8 lds_a(const __bf16* tiles, int mt, int s, int lane) {
     return *reinterpret_cast<const bf16x8*>(tiles + ((mt * 4 + s) * 64 + lane) * 8);
+}
+
+// The input layer's pre-activations of units 16 mt + 4 g + r for this lane's
+// pair, z = w0 x0 + (w1 x1 + (w2 x2 + b1)), on v_mfma_f32_16x16x4: one chain of
+// fused multiply-adds from the bias on in the order of K (x2, x1, x0, and a
+// zero), in the lanes that hold those units of layer 2's operand.  (As three
+// FMA a unit it was 192 of an evaluation's 1,700 VALU instructions, which bound
+// it; the matrix cores are mostly idle beside the SiLUs.)
+__device__ inline float input_operand(const float (&xh)[3], int g) {
+    return g == 0 ? xh[2] : g == 1 ? xh[1] : g == 2 ? xh[0] : 0.0f;
+}
+__device__ inline f32x4 input_layer(const SmallParams* sp, int mt, int lane, float xk) {
+    const int g = lane >> 4;
+    const f32x4 b = {sp->b1[16 * mt + 4 * g], sp->b1[16 * mt + 4 * g + 1], sp->b1[16 * mt + 4 * g + 2],
+                     sp->b1[16 * mt + 4 * g + 3]};
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(sp->w1[g][16 * mt + (lane & 15)], xk, b, 0, 0, 0);
 }
 
 // Forward pass of one wave tile (16 NT_ pairs).  xh[nt] is this lane's input
@@ -150,22 +187,19 @@ __device__ inline void forward_tile(const __bf16* sW2, const __bf16* sW3, const 
     // loop they would need 256 VGPRs
     asm volatile("" ::: "memory");
 
-    // input layer (FP32 VALU) straight into layer 2's B operands
+    // input layer (FP32) straight into layer 2's B operands
     bf16x8 b[4][NT_];
+    float xk[NT_];
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
+    for (int nt = 0; nt < NT_; ++nt) xk[nt] = input_operand(xh[nt], g);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int u = perm_unit(s, 8 * g + e);
+    for (int mt = 0; mt < 8; ++mt)
 #pragma unroll
-            for (int nt = 0; nt < NT_; ++nt) {
-                const float z = fmaf(sp->w1[u][0], xh[nt][0],
-                                     fmaf(sp->w1[u][1], xh[nt][1], fmaf(sp->w1[u][2], xh[nt][2], sp->b1[u])));
-                const __bf16 h = (__bf16)silu(z);
-                b[s][nt][e] = h;
-            }
+        for (int nt = 0; nt < NT_; ++nt) {
+            const f32x4 z = input_layer(sp, mt, lane, xk[nt]);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) b[mt >> 1][nt][(mt & 1) * 4 + r] = (__bf16)silu(z[r]);
         }
-    }
 
     // two 128x128 layers on MFMA
 #pragma unroll
