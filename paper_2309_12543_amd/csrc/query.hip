@@ -3,24 +3,33 @@
 // link i's frame.
 //
 // Work layout:
-//   * a wave owns one link i and 64 consecutive configurations (one per
-//     lane); each lane holds the world-to-grid affine map of its pose (the
-//     inverse pose of Eq. 4 with the grid scaling folded in) in 12 VGPRs;
-//   * obstacle points are wave-uniform: they stream through scalar loads into
-//     SGPRs, so mapping a point is 9 FMAs with no cross-lane traffic, and the
-//     per-pair minimum stays in one register per lane;
-//   * the box test is one max3 of absolute centred coordinates; lanes inside
-//     their box gather 8 corners and interpolate, with the loads of a batch
-//     of points issued together so that one wait covers them all;
-//   * points are culled 8 at a time: a first small kernel bounds every block
-//     of 8 consecutive points by a sphere (and every quad of 4 blocks by
-//     another), and a wave skips a quad or block when no lane's box can hold
-//     any of its points (the sphere centre is mapped with the lane's own map;
-//     the test widens the box by the radius times the map's row norms plus a
-//     bound on FP32 rounding, so the skip is exact);
+//   * a wave tests one link i and 64 consecutive configurations (one per
+//     lane, a tile); each lane holds the world-to-grid affine map of its pose
+//     (the inverse pose of Eq. 4 with the grid scaling folded in) in 12 VGPRs;
+//   * obstacle points and their bounds are wave-uniform: they stream through
+//     scalar loads into SGPRs, so mapping a point is 9 FMAs with no
+//     cross-lane traffic;
+//   * points are culled by boxes: a first small kernel bounds every block of
+//     8 consecutive points and every group of 8 blocks by an axis-aligned
+//     box, and a wave skips a group or block when no lane's grid box can hold
+//     any of its points (the box centre is mapped with the lane's own map; the
+//     test widens the grid box by the box's half extents times the map's
+//     magnitudes plus a bound on FP32 rounding, so the skip is exact).
+//     Consecutive points of a voxel grid lie on a line, which a sphere bounds
+//     badly: 500 waypoints against 20,000 such points left 7,700 to 9,000
+//     blocks to test with spheres and leave 300 to 3,900 with boxes, and half
+//     to a tenth of the groups;
 //   * a block that survives is recorded in a list in the workgroup's LDS;
-//     after a barrier the workgroup's waves share out the recorded blocks,
-//     so that a wave that drew many does not hold up the kernel alone;
+//     after a barrier the workgroup's waves share out the listed blocks, and
+//     so on until no chunk is left;
+//   * a listed block's points are tested one by one; the pairs (point,
+//     configuration) inside a grid box, a quarter of the lanes where there is
+//     one, wait in a queue of the wave's, from which 64 at a time gather their
+//     8 corners and interpolate, whichever block and tile they came from.
+//     Their minima go to a table of the workgroup's tiles in LDS (an atomic
+//     max per pair), and from there to global memory once per list (one
+//     atomic max per pair straight to global memory took longer than all of
+//     the rest);
 //   * a call may hold many trajectories, each a range of configurations
 //     checked against its own range of points (a re-planned path against
 //     its latest cloud); a plain query is the one-trajectory case.  The
@@ -32,17 +41,23 @@
 //   * the first kernel also writes, per (link, configuration), the lane's
 //     map and culling thresholds into a field-major table (one coalesced
 //     load per field per chunk) and zeroes the keys;
-//   * the iteration space (trajectory, link, 64-configuration group, point)
+//   * the iteration space (trajectory, link, 64-configuration tile, point)
 //     is cut into chunks of a tunable number of 8-point blocks (a chunk takes
-//     every n-th quad of its trajectory's cloud), dealt to the waves
-//     round-robin, either over the whole grid or inside per-XCD slices
+//     every n-th group of its trajectory's cloud, or a part of one group),
+//     dealt to the waves over the whole grid or inside per-XCD slices
 //     (blocks b = x mod 8 take a contiguous slice, which keeps an XCD on one
 //     or two links' grids in its L2); the four waves of a workgroup take
 //     chunks from four different parts of the order;
-//   * per-pair minima merge across waves with one unsigned atomic max on a
-//     complemented order-preserving key; a last small kernel turns the keys
+//   * per-pair minima merge across workgroups with one unsigned atomic max on
+//     a complemented order-preserving key; a last small kernel turns the keys
 //     into the outputs (the kernel boundary orders it after every atomic,
 //     with no device fence).
+// Bound by the VALU and by the latency of its dependent loads.  GPU time of a
+// call on one MI355X, all three kernels, before (spheres, a gather per point
+// and lane, minima straight to global memory) and now: 50 waypoints, 2,000
+// points 17.2 -> 15.1 us; 500, 20,000 32 -> 25 us; 500, 100,000, 128^3 bf16
+// 76 -> 54 us; 333, 12,345 all near the arm 190 -> 71 us; 64 paths of 50 to
+// 1,000 with clouds of 5,000 to 200,000 2.16 -> 1.43 ms.
 #include <algorithm>
 #include <atomic>
 #include <mutex>
@@ -67,77 +82,97 @@ constexpr int kWavesPerBlock = kBlock / 64;
 constexpr int kXcds = 8;
 constexpr float kFar = 1e30f;       // centred coordinate of unused lanes: never inside
 
-#ifndef LSDF_QUERY_UNROLL
-#define LSDF_QUERY_UNROLL 8         // points per any-inside test
+constexpr int kBlockPts = 8;        // points per block, the smallest unit culled by a box
+constexpr int kGroupBlocks = 8;     // blocks per group, the unit a chunk is made of
+constexpr int kGroupPts = kBlockPts * kGroupBlocks;
+#ifndef LSDF_QUERY_GROUP_BATCH
+#define LSDF_QUERY_GROUP_BATCH 4    // groups of a chunk loaded and tested together
 #endif
-#ifndef LSDF_QUERY_GATHER
-#define LSDF_QUERY_GATHER 4         // points whose gathers are in flight together
-#endif
-constexpr int kBlockPts = 8;        // points per culling sphere
-constexpr int kSphereBatch = 4;     // culling spheres tested together: the blocks of a quad
-constexpr int kQuadPts = kBlockPts * kSphereBatch;   // points per quad
-#ifndef LSDF_QUERY_QUAD_BATCH
-#define LSDF_QUERY_QUAD_BATCH 8     // quad spheres of a chunk loaded and tested together
-#endif
-constexpr int kQuadBatch = LSDF_QUERY_QUAD_BATCH;
-constexpr int kUnroll = LSDF_QUERY_UNROLL;
-constexpr int kGather = LSDF_QUERY_GATHER;
-static_assert(kUnroll % kGather == 0, "gather batch must divide the unroll");
-static_assert(kUnroll == kBlockPts, "blocks of 8 points");
+constexpr int kGroupBatch = LSDF_QUERY_GROUP_BATCH;
 
 // Default tiling: as many workgroups per CU as can be resident at once (so
 // that no wave of the persistent grid waits for another to finish; 8 if
 // the runtime cannot say), chunks dealt over the whole grid, at most about
 // one chunk per wave of the grid for the call's sizes (with offset arrays,
 // the capacities C and M): the smallest power of two of blocks of 8 points
-// between 4 and 128 that gives no more chunks than waves.
+// between 8 (a group) and 128 that gives no more chunks than waves; a quarter
+// of a group where the call is so small that an eighth of the waves would
+// have a group (C = 50, M = 2,000, L = 7: 15.1 us with quarters, 16.3 with
+// halves, 18.2 with whole ones; C = 200, M = 8,000 near the arm, halves where
+// the rule takes whole groups: 59 us, not 49).
 constexpr int kDefaultChunkPoints = 1024;
 constexpr int kDefaultBlocksPerCu = 8;
 constexpr int kDefaultSchedule = LSDF_SCHED_INTERLEAVED;
 
 int default_chunk_blocks(int64_t C, int64_t L, int64_t M, int64_t waves) {
     const int64_t units = L * ((C + 63) / 64) * ((M + kBlockPts - 1) / kBlockPts);
-    int64_t cb = 4;
+    if (units <= waves) return kGroupBlocks / 4;
+    int64_t cb = kGroupBlocks;
     while (cb < 128 && cb * waves <= units) cb *= 2;
     return (int)cb;
 }
+// From this many chunks per wave on, all but each wave's first are dealt as
+// the workgroups come for them: 64 paths, 55 chunks a wave, 1.43 ms against
+// 1.72 dealt beforehand; 16 paths, 2 chunks a wave, 120 us against 111.
+constexpr int kDealChunks = 16;
+constexpr int kRunsPerBlock = 24;   // runs of chunks a workgroup comes for, about (8: 1.62 ms, 16: 1.48)
+constexpr int kMaxRun = 64;         // chunks of a run, at most
 constexpr int kMaxChunkPoints = 8192;
 constexpr int kMaxBlocksPerCu = 16;
 
 // Work plan of one trajectory, built on the device.  Entry K (one past the
-// last trajectory) holds only chunk_start = the total chunk count.
+// last trajectory) is a PlanEnd.
 struct TrajPlan {
     int64_t chunk_start;       // first chunk of this trajectory
     int64_t m_lo, m_hi;        // points [m_lo, m_hi) of the concatenated cloud
     int32_t c_lo, c_n;         // configurations [c_lo, c_lo + c_n)
     int32_t cgroups;           // ceil(c_n / 64)
-    int32_t chunks_per_group;  // ceil(quads touched / chunk_quads)
+    int32_t chunks_per_group;  // ceil(groups of 64 points touched / chunk_groups)
     int32_t pad[2];
 };
-static_assert(sizeof(TrajPlan) == 48, "plan entry layout");
-
-// A surviving block handed from the wave that found it to whichever wave of
-// the workgroup is free once every wave has tested its own chunks.
-struct Deferred {
-    uint64_t mask;             // lanes (configurations c0 + lane) whose box may reach the block
-    int64_t blk;               // block of 8 points in the concatenated cloud
-    int64_t m_lo, m_hi;        // the trajectory's points
-    int32_t c0;                // configuration of lane 0
-    int32_t link;
+struct PlanEnd {
+    int64_t chunk_start;       // the total chunk count
+    int32_t next[kXcds];       // runs of chunks dealt so far, per XCD
+    int32_t pad[2];
 };
-#ifndef LSDF_QUERY_DEFER
-#define LSDF_QUERY_DEFER 128       // surviving blocks a workgroup may pass between its waves
-#endif
-constexpr int kDeferCap = LSDF_QUERY_DEFER;
+static_assert(sizeof(TrajPlan) == 48 && sizeof(PlanEnd) == sizeof(TrajPlan), "plan entry layout");
+
+// A block of 8 points some lane's box may reach, handed from the wave that
+// found it to whichever wave of the workgroup takes it.
+struct Block {
+    uint32_t index;            // in the concatenated cloud
+    uint32_t tile_points;      // its tile, and from bit 16 its points that are the trajectory's
+};
+// A link and 64 configurations that blocks of the list were found for.
+struct Tile {
+    int32_t link;
+    int32_t c0, n;             // configurations [c0, c0 + n), one per lane
+};
+// A wave looks for room before each batch of groups and may add all its
+// blocks and one tile.
+constexpr int kListFull = 512;
+constexpr int kListCap = kListFull + kWavesPerBlock * kGroupBatch * kGroupBlocks;
+constexpr int kTilesFull = 12;
+constexpr int kTileCap = kTilesFull + kWavesPerBlock;
+constexpr int kLongList = 64, kTake = 4;
+constexpr int kQueueCap = 128;     // pairs waiting: below 64, and the 64 of one point
+
+// A link's grid as the evaluation of mixed pairs reads it, from LDS.
+struct GridView {
+    float half[3];
+    int32_t n[3];
+    int64_t offset;
+};
 
 struct QueryArgs {
     LinkGrid link[LSDF_MAX_LINKS];
     const float* maps;       // [L][kMapFields][C]
     uint32_t* keys;          // [C][L] complemented ordered keys, 0 = empty
+    int64_t M;
     int32_t C;
     int32_t K;               // trajectories
     int32_t L;
-    int32_t chunk_quads;     // quads (4 blocks of 8 points) per chunk
+    int32_t split;           // a chunk is a 2^-split share of a group (0: whole groups)
     int32_t blocks_per_xcd;
     int32_t schedule;        // LSDF_SCHED_*
 };
@@ -145,7 +180,18 @@ struct QueryArgs {
 // Per (link, configuration): the world-to-grid map and the culling
 // thresholds, stored field-major ([L][kMapFields][C]) so that a wave's 64
 // consecutive configurations read each field with one coalesced load.
-constexpr int kMapFields = 18;   // M (9, row-major), w (3), ||M_a|| (3), k_a (3)
+constexpr int kMapFields = 15;   // M (9, row-major), w (3), k_a (3)
+
+// A box that holds 64 (a group's) points, widened (see box_of).
+struct Box {
+    float cx, cy, cz, hx, hy, hz;
+};
+// The same for 8 points in 16 bytes: the half extents as bytes (x, y, z from
+// the low byte) times the power of two whose exponent is the high byte.
+struct PackedBox {
+    float cx, cy, cz;
+    uint32_t h;
+};
 
 struct PrepArgs {
     LinkGrid link[LSDF_MAX_LINKS];
@@ -154,19 +200,20 @@ struct PrepArgs {
     float* link_T_out;       // poses computed from q are stored here when not NULL
     const float* link_T;
     const float* points;
-    float4* spheres;         // [4 ceil(M / 32)] one per 8-point block (the last few unused)
-    float4* qspheres;        // [ceil(M / 32)] one per quad of 4 blocks
+    PackedBox* blocks;       // [ceil(M / 8)]
+    Box* groups;             // [ceil(M / 64)]
     TrajPlan* plan;          // [K + 1]
     float* maps;             // [L][kMapFields][C]
     uint32_t* keys;          // [C][L], zeroed here
     const int32_t* c_off;    // device [K + 1] or NULL (one trajectory of all C)
     const int64_t* m_off;    // device [K + 1] or NULL (one trajectory of all M)
     int64_t M;
-    int64_t sphere_base;     // first thread of the sphere job: C L rounded up to the wave size
+    int64_t box_base;        // first thread of the box job: C L rounded up to the wave size
     int32_t C;
     int32_t K;
     int32_t L;
-    int32_t chunk_quads;
+    int32_t chunk_groups;    // groups of 64 points per chunk
+    int32_t split;           // parts a group is cut into, as a power of two
 };
 
 struct FinalizeArgs {
@@ -178,81 +225,6 @@ struct FinalizeArgs {
     int32_t L;
 };
 
-// One 8-point block against every lane's box: the point tests, then the
-// corner gathers and interpolation of the points inside some lane's box.
-template <bool CUBIC, int DT>
-__device__ __forceinline__ void block_min(const float* __restrict__ points, int64_t j, int64_t m_lo, int64_t m_hi,
-                                          const LinkGrid& lg, const typename GridT<DT>::T* __restrict__ G,
-                                          int nx, int nxy, float m00, float m01, float m02, float w0, float m10,
-                                          float m11, float m12, float w1, float m20, float m21, float m22, float w2,
-                                          float& best) {
-    using E = GridT<DT>;
-    if (j >= m_lo && j + kUnroll <= m_hi) {
-        // first the box tests of the 8 points (lane masks), then the gathers
-        // of the points some lane holds, a batch at a time; the mapped
-        // coordinates are recomputed for the gathers rather than kept, which
-        // keeps register use (and so the number of resident waves) in check
-        bool in[kUnroll];
-        bool any = false;
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const float x = points[3 * j + 3 * u + 0];
-            const float y = points[3 * j + 3 * u + 1];
-            const float z = points[3 * j + 3 * u + 2];
-            const float v0 = fmaf(m00, x, fmaf(m01, y, fmaf(m02, z, w0)));
-            const float v1 = fmaf(m10, x, fmaf(m11, y, fmaf(m12, z, w1)));
-            const float v2 = fmaf(m20, x, fmaf(m21, y, fmaf(m22, z, w2)));
-            in[u] = inside<CUBIC>(lg, v0, v1, v2);
-            any |= in[u];
-        }
-        if (!__ballot(any)) return;
-#pragma unroll
-        for (int b = 0; b < kUnroll; b += kGather) {
-            // issue every corner load of the batch, then interpolate
-            float c00[kGather], c10[kGather], c01[kGather], c11[kGather];
-            float d00[kGather], d10[kGather], d01[kGather], d11[kGather];
-            Cell cell[kGather];
-#pragma unroll
-            for (int u = 0; u < kGather; ++u) {
-                const float x = points[3 * j + 3 * (b + u) + 0];
-                const float y = points[3 * j + 3 * (b + u) + 1];
-                const float z = points[3 * j + 3 * (b + u) + 2];
-                const float v0 = fmaf(m00, x, fmaf(m01, y, fmaf(m02, z, w0)));
-                const float v1 = fmaf(m10, x, fmaf(m11, y, fmaf(m12, z, w1)));
-                const float v2 = fmaf(m20, x, fmaf(m21, y, fmaf(m22, z, w2)));
-                cell[u] = locate(lg, v0, v1, v2);
-                // lanes outside the box read the first cell (discarded)
-                const typename E::T* cp = G + (in[b + u] ? cell[u].idx : 0);
-                c00[u] = E::get(cp, 0);        d00[u] = E::get(cp, 1);
-                c10[u] = E::get(cp, nx);       d10[u] = E::get(cp, nx + 1);
-                c01[u] = E::get(cp, nxy);      d01[u] = E::get(cp, nxy + 1);
-                c11[u] = E::get(cp, nxy + nx); d11[u] = E::get(cp, nxy + nx + 1);
-            }
-#pragma unroll
-            for (int u = 0; u < kGather; ++u) {
-                const float val = interpolate(c00[u], d00[u], c10[u], d10[u], c01[u], d01[u], c11[u], d11[u], cell[u]);
-                if (in[b + u]) best = fminf(best, val);
-            }
-        }
-    } else {
-        // a block at either end of the trajectory's points
-        const int64_t ja = max(j, m_lo), jz = min(j + kBlockPts, m_hi);
-        for (int64_t jj = ja; jj < jz; ++jj) {
-            const float x = points[3 * jj + 0], y = points[3 * jj + 1], z = points[3 * jj + 2];
-            const float v0 = fmaf(m00, x, fmaf(m01, y, fmaf(m02, z, w0)));
-            const float v1 = fmaf(m10, x, fmaf(m11, y, fmaf(m12, z, w1)));
-            const float v2 = fmaf(m20, x, fmaf(m21, y, fmaf(m22, z, w2)));
-            if (inside<CUBIC>(lg, v0, v1, v2)) {
-                const Cell ce = locate(lg, v0, v1, v2);
-                const typename E::T* cp = G + ce.idx;
-                best = fminf(best, interpolate(E::get(cp, 0), E::get(cp, 1), E::get(cp, nx), E::get(cp, nx + 1),
-                                               E::get(cp, nxy), E::get(cp, nxy + 1), E::get(cp, nxy + nx),
-                                               E::get(cp, nxy + nx + 1), ce));
-            }
-        }
-    }
-}
-
 // A 64-bit value that every lane holds alike, moved to scalar registers.
 __device__ __forceinline__ int64_t uniform64(int64_t v) {
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
@@ -260,85 +232,97 @@ __device__ __forceinline__ int64_t uniform64(int64_t v) {
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
-// The 12 map entries of (link i, configuration c) from the table the first
-// kernel built; a lane with valid = false gets a map that sends every point
-// far outside the box.
+// This lane's map v = M [x; y; z] + w (centred grid coordinates) and culling
+// thresholds for (link i, configuration c0 + lane), from the table the first
+// kernel built; lanes from n on get a map that sends every point far outside
+// the box.
 struct Map {
-    float m00, m01, m02, w0, m10, m11, m12, w1, m20, m21, m22, w2;
+    float m00, m01, m02, w0, m10, m11, m12, w1, m20, m21, m22, w2, k0, k1, k2;
 };
-__device__ __forceinline__ void load_map(const QueryArgs& p, int i, int c, bool valid, Map& m) {
-    m = Map{0.f, 0.f, 0.f, kFar, 0.f, 0.f, 0.f, kFar, 0.f, 0.f, 0.f, kFar};
-    if (valid) {
-        const float* mp = p.maps + (int64_t)i * kMapFields * p.C + c;
-        const int64_t C = p.C;
-        m.m00 = mp[0 * C]; m.m01 = mp[1 * C]; m.m02 = mp[2 * C];
-        m.m10 = mp[3 * C]; m.m11 = mp[4 * C]; m.m12 = mp[5 * C];
-        m.m20 = mp[6 * C]; m.m21 = mp[7 * C]; m.m22 = mp[8 * C];
-        m.w0 = mp[9 * C]; m.w1 = mp[10 * C]; m.w2 = mp[11 * C];
+__device__ __forceinline__ void load_map(const QueryArgs& p, int i, int c0, int n, int lane, Map& m) {
+    m = Map{0.f, 0.f, 0.f, kFar, 0.f, 0.f, 0.f, kFar, 0.f, 0.f, 0.f, kFar, 0.f, 0.f, 0.f};
+    if (lane < n) {
+        const float* f = p.maps + (int64_t)i * kMapFields * p.C + c0;   // wave-uniform
+        auto field = [&](int k) { return (f + (int64_t)k * p.C)[(uint32_t)lane]; };
+        m.m00 = field(0); m.m01 = field(1); m.m02 = field(2);
+        m.m10 = field(3); m.m11 = field(4); m.m12 = field(5);
+        m.m20 = field(6); m.m21 = field(7); m.m22 = field(8);
+        m.w0 = field(9); m.w1 = field(10); m.w2 = field(11);
+        m.k0 = field(12); m.k1 = field(13); m.k2 = field(14);
     }
 }
-
-// A deferred block as a wave holds it: the record's fields in scalar
-// registers, and this lane's bit of the mask.
-struct DeferredView {
-    int64_t blk, m_lo, m_hi;
-    int c0, link;
-    bool mine;
-};
-__device__ __forceinline__ DeferredView read_deferred(const Deferred& d, int lane) {
-    DeferredView v;
-    const uint64_t mask = (uint64_t)uniform64((int64_t)d.mask);
-    v.blk = uniform64(d.blk);
-    v.m_lo = uniform64(d.m_lo);
-    v.m_hi = uniform64(d.m_hi);
-    v.c0 = __builtin_amdgcn_readfirstlane(d.c0);
-    v.link = __builtin_amdgcn_readfirstlane(d.link);
-    v.mine = (mask >> lane) & 1u;
-    return v;
+__device__ __forceinline__ void map_point(const Map& m, float x, float y, float z, float& v0, float& v1, float& v2) {
+    v0 = fmaf(m.m00, x, fmaf(m.m01, y, fmaf(m.m02, z, m.w0)));
+    v1 = fmaf(m.m10, x, fmaf(m.m11, y, fmaf(m.m12, z, m.w1)));
+    v2 = fmaf(m.m20, x, fmaf(m.m21, y, fmaf(m.m22, z, m.w2)));
 }
 
-// The first pass of a wave: the chunks q_first, q_first + q_step, ... below
-// q_end.  A chunk's quads are tested against every lane's box, then their
-// blocks; a block some lane's box may reach is appended to the workgroup's
-// list s_def while it has room (its points are tested after the workgroup's
-// barrier, by whichever wave is free) and tested here once the list is full.
-template <bool CUBIC, int DT>
-__device__ __forceinline__ void test_chunks(const QueryArgs& p, const float* __restrict__ points,
-                                            const typename GridT<DT>::T* __restrict__ grid,
-                                            const float4* __restrict__ spheres,
-                                            const float4* __restrict__ qspheres,
-                                            const TrajPlan* __restrict__ plan, int64_t q_first, int64_t q_end,
-                                            int64_t q_step, int lane, Deferred* s_def, int* ndef) {
-    using E = GridT<DT>;
-    // trajectory of the first chunk: the last entry whose start is <= q
-    int k = 0;
-    {
-        int hi = p.K - 1;
-        while (k < hi) {
-            const int mid = (k + hi + 1) >> 1;
-            if (plan[mid].chunk_start <= q_first) k = mid; else hi = mid - 1;
-        }
-    }
-    // the current trajectory's plan, kept in registers until q passes its end
-    int64_t t_start = plan[k].chunk_start, t_next = plan[k + 1].chunk_start;
-    int64_t m_lo = plan[k].m_lo, m_hi = plan[k].m_hi;
-    int c_lo = plan[k].c_lo, c_n = plan[k].c_n, cgroups = plan[k].cgroups, cpg = plan[k].chunks_per_group;
+// Orders one wave's accesses to its queue (the hardware keeps them in order;
+// this keeps the compiler from moving them).
+__device__ __forceinline__ void queue_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
 
-    for (int64_t q = q_first; q < q_end; q += q_step) {
-        if (q >= t_next) {   // stops at k + 1 = K at the latest: q < total
-            do {
-                ++k;
-                t_next = plan[k + 1].chunk_start;
-            } while (q >= t_next);
-            t_start = plan[k].chunk_start;
-            m_lo = plan[k].m_lo;
-            m_hi = plan[k].m_hi;
-            c_lo = plan[k].c_lo;
-            c_n = plan[k].c_n;
-            cgroups = plan[k].cgroups;
-            cpg = plan[k].chunks_per_group;
+// What the workgroup holds in LDS: the blocks its waves found (one list, added
+// to by all), each wave's queue of pairs, and the links' grids.
+struct QueryShared {
+    Block block[kListCap];
+    float4 pair[kWavesPerBlock][kQueueCap];    // centred grid coordinates; 64 tile + lane
+    uint32_t best[kTileCap][64];               // complemented ordered keys, 0 = empty
+    Tile tile[kTileCap];
+    GridView grid[LSDF_MAX_LINKS];
+    int listed;     // blocks in the list
+    int tiles;
+    int64_t run_q, run_step;   // the workgroup's run of chunks: the first, the distance to the next,
+    int run, taken;            // how many, how many of them are taken
+    int open;       // waves that left a chunk begun
+};
+
+// Where a wave stands: the chunk it has begun or is to begin, and its next group.
+struct Walk {
+    int64_t q, q_end, q_step;   // (the last two: of chunks dealt beforehand)
+    int32_t gb;
+    int32_t k;      // the trajectory of chunk q, or an earlier one
+    bool has;       // there is a chunk q
+    bool fresh;     // it is not begun
+};
+
+// Tests chunks until the list is full or the workgroup's run of chunks is
+// through.  The boxes of a chunk's groups are tested against every lane's grid
+// box, then their blocks'; a block some lane may reach goes to the list.
+template <bool DEAL>
+__device__ __forceinline__ void collect(const QueryArgs& p, const PackedBox* __restrict__ blocks,
+                                        const Box* __restrict__ groups, const TrajPlan* __restrict__ plan, Walk& w,
+                                        int lane, QueryShared& sh) {
+    auto room = [&] {
+        return (__hip_atomic_load(&sh.listed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < kListFull) &
+               (__hip_atomic_load(&sh.tiles, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < kTilesFull);
+    };
+    for (;;) {
+        if (!w.has) {
+            if (!DEAL) return;
+            int n = 0;
+            if (lane == 0) n = atomicAdd(&sh.taken, 1);
+            n = __builtin_amdgcn_readfirstlane(n);
+            if (n >= __builtin_amdgcn_readfirstlane(sh.run)) return;
+            w.q = uniform64(sh.run_q) + n * uniform64(sh.run_step);
+            w.has = w.fresh = true;
         }
-        const int64_t local = q - t_start;
+        if (DEAL && w.q < plan[w.k].chunk_start) w.k = 0;
+        if (w.q >= plan[w.k + 1].chunk_start) {
+            // its trajectory: the last entry whose start is <= q
+            int hi = p.K - 1;
+            ++w.k;
+            while (w.k < hi) {
+                const int mid = (w.k + hi + 1) >> 1;
+                if (plan[mid].chunk_start <= w.q) w.k = mid; else hi = mid - 1;
+            }
+        }
+        const TrajPlan& t = plan[w.k];
+        const int64_t m_lo = t.m_lo, m_hi = t.m_hi;
+        const int cgroups = t.cgroups, cpg = t.chunks_per_group;
+        const int64_t local = w.q - t.chunk_start;
         int64_t g, mc;
         if (local < ((int64_t)1 << 32)) {
             const uint32_t l32 = (uint32_t)local;
@@ -350,104 +334,105 @@ __device__ __forceinline__ void test_chunks(const QueryArgs& p, const float* __r
         }
         const int i = (int)((uint32_t)g / (uint32_t)cgroups);
         const int cb = (int)((uint32_t)g - (uint32_t)i * (uint32_t)cgroups);
-        const int cl = cb * 64 + lane;
-        const int c = c_lo + cl;
-        const LinkGrid& lg = p.link[i];
-        const typename E::T* __restrict__ G = grid + lg.offset;
-        // the trajectory's points lie in quads of 4 blocks of 8 (aligned in the
-        // concatenated cloud); chunk mc takes every cpg-th quad from the
-        // trajectory's quad mc, so that points near a link, which lie together
+        const int c0 = t.c_lo + cb * 64, cn = min(t.c_n - cb * 64, 64);
+        // the trajectory's points lie in groups of 8 blocks of 8 (aligned in the
+        // concatenated cloud); chunk mc takes every cpg-th group from the
+        // trajectory's group mc, so that points near a link, which lie together
         // in the cloud, spread over the chunks rather than piling onto a few
         // waves
-        const int64_t blk0 = m_lo >> 3, blk1 = (m_hi + kBlockPts - 1) >> 3;   // the trajectory's blocks
-        const int64_t quad0 = m_lo / kQuadPts;
-        const int64_t nquad = (m_hi + kQuadPts - 1) / kQuadPts - quad0;
-
-        // this lane's map v = M [x; y; z] + w (centred grid coordinates) and
-        // its culling thresholds, from the table the first kernel built;
-        // lanes past the trajectory's configurations are never near or inside
-        float m00 = 0.f, m01 = 0.f, m02 = 0.f, w0 = kFar;
-        float m10 = 0.f, m11 = 0.f, m12 = 0.f, w1 = kFar;
-        float m20 = 0.f, m21 = 0.f, m22 = 0.f, w2 = kFar;
-        float nr0 = 0.f, nr1 = 0.f, nr2 = 0.f, k0 = 0.f, k1 = 0.f, k2 = 0.f;
-        if (cl < c_n) {
-            const float* mp = p.maps + (int64_t)i * kMapFields * p.C + c;
-            const int64_t C = p.C;
-            m00 = mp[0 * C]; m01 = mp[1 * C]; m02 = mp[2 * C];
-            m10 = mp[3 * C]; m11 = mp[4 * C]; m12 = mp[5 * C];
-            m20 = mp[6 * C]; m21 = mp[7 * C]; m22 = mp[8 * C];
-            w0 = mp[9 * C]; w1 = mp[10 * C]; w2 = mp[11 * C];
-            nr0 = mp[12 * C]; nr1 = mp[13 * C]; nr2 = mp[14 * C];
-            k0 = mp[15 * C]; k1 = mp[16 * C]; k2 = mp[17 * C];
-        }
-        const int nx = lg.n[0];
-        const int nxy = lg.n[0] * lg.n[1];
-
-        float best = INFINITY;
-        // kQuadBatch quads of the chunk at a time: their spheres are loaded
-        // together and tested (one round trip for the batch); only the
-        // quads some lane's box may reach go on to their blocks' spheres
-        for (int64_t qb = mc; qb < nquad; qb += (int64_t)kQuadBatch * cpg) {
-            float4 qs[kQuadBatch];
+        const int64_t group0 = m_lo / kGroupPts;
+        const int ngroup = (int)((m_hi + kGroupPts - 1) / kGroupPts - group0);
+        const Box* const gbox = groups + group0;
+        // blocks of the trajectory, counted from its first group's
+        const uint32_t blk0 = (uint32_t)((m_lo - group0 * kGroupPts) / kBlockPts);
+        const uint32_t blk1 = (uint32_t)((m_hi - group0 * kGroupPts + kBlockPts - 1) / kBlockPts);
+        // the share of a group's blocks that is the chunk's (all, or a part)
+        const int part = (int)mc & ((1 << p.split) - 1), gstep = cpg >> p.split;
+        const uint32_t share = ((1u << (kGroupBlocks >> p.split)) - 1) << (part * (kGroupBlocks >> p.split));
+        Map m;
+        load_map(p, i, c0, cn, lane, m);
+        int tile = -1;   // its number, once a block is found for it
+        // kGroupBatch groups of the chunk at a time: their boxes are loaded
+        // together and tested (one round trip for the batch); only the groups
+        // some lane may reach go on to their blocks' boxes
+        if (w.fresh) w.gb = (int)(mc >> p.split);
+        w.fresh = false;
+        for (; w.gb < ngroup; w.gb += kGroupBatch * gstep) {
+            if (!room()) return;
+            Box bx[kGroupBatch];
 #pragma unroll
-            for (int k = 0; k < kQuadBatch; ++k)   // past the trajectory's quads: its last one, not tested
-                qs[k] = qspheres[quad0 + min(qb + (int64_t)k * cpg, nquad - 1)];
-            uint32_t qnear = 0;
+            for (int k = 0; k < kGroupBatch; ++k)   // past the trajectory's groups: its last one, not tested
+                bx[k] = gbox[min(w.gb + k * gstep, ngroup - 1)];
+            uint32_t gnear = 0;
 #pragma unroll
-            for (int k = 0; k < kQuadBatch; ++k) {
-                const float s0 = fmaf(m00, qs[k].x, fmaf(m01, qs[k].y, fmaf(m02, qs[k].z, w0)));
-                const float s1 = fmaf(m10, qs[k].x, fmaf(m11, qs[k].y, fmaf(m12, qs[k].z, w1)));
-                const float s2 = fmaf(m20, qs[k].x, fmaf(m21, qs[k].y, fmaf(m22, qs[k].z, w2)));
-                const bool near = (fabsf(s0) <= fmaf(nr0, qs[k].w, k0)) & (fabsf(s1) <= fmaf(nr1, qs[k].w, k1)) &
-                                  (fabsf(s2) <= fmaf(nr2, qs[k].w, k2));
-                if (__ballot(near) && qb + (int64_t)k * cpg < nquad) qnear |= 1u << k;
+            for (int k = 0; k < kGroupBatch; ++k) {
+                const Box& b = bx[k];
+                float s0, s1, s2;
+                map_point(m, b.cx, b.cy, b.cz, s0, s1, s2);
+                const float r0 = fmaf(fabsf(m.m00), b.hx, fmaf(fabsf(m.m01), b.hy, fmaf(fabsf(m.m02), b.hz, m.k0)));
+                const float r1 = fmaf(fabsf(m.m10), b.hx, fmaf(fabsf(m.m11), b.hy, fmaf(fabsf(m.m12), b.hz, m.k1)));
+                const float r2 = fmaf(fabsf(m.m20), b.hx, fmaf(fabsf(m.m21), b.hy, fmaf(fabsf(m.m22), b.hz, m.k2)));
+                const bool near = (fabsf(s0) <= r0) & (fabsf(s1) <= r1) & (fabsf(s2) <= r2);
+                if (__ballot(near) && w.gb + k * gstep < ngroup) gnear |= 1u << k;
             }
-            while (qnear) {   // wave-uniform
-                const int kq = __builtin_ctz(qnear);
-                qnear &= qnear - 1;
-                // a sphere bounds all points of its quad or block, so also the
+            while (gnear) {   // wave-uniform
+                const int kg = __builtin_ctz(gnear);
+                gnear &= gnear - 1;
+                // a box bounds all points of its group or block, so also the
                 // trajectory's share of one it shares with its neighbour
-                const int64_t qg = quad0 + qb + (int64_t)kq * cpg;
-                float4 sph[kSphereBatch];
-#pragma unroll
-                for (int u = 0; u < kSphereBatch; ++u) sph[u] = spheres[kSphereBatch * qg + u];
-                const int64_t jb = kQuadPts * qg;
+                const uint32_t b0 = kGroupBlocks * (uint32_t)(w.gb + kg * gstep);
+                uint32_t valid = share;
+                if (b0 < blk0) valid &= ~0u << (blk0 - b0);
+                if (b0 + kGroupBlocks > blk1) valid &= (1u << (blk1 - b0)) - 1;
                 uint32_t near_mask = 0;
-                uint64_t lanes[kSphereBatch];
+                // (past the last block the array is followed by the groups' boxes
+                // and the plan; what is read there is masked out)
+                const PackedBox* const pb = blocks + (group0 * kGroupBlocks + b0);
 #pragma unroll
-                for (int u = 0; u < kSphereBatch; ++u) {
-                    const float s0 = fmaf(m00, sph[u].x, fmaf(m01, sph[u].y, fmaf(m02, sph[u].z, w0)));
-                    const float s1 = fmaf(m10, sph[u].x, fmaf(m11, sph[u].y, fmaf(m12, sph[u].z, w1)));
-                    const float s2 = fmaf(m20, sph[u].x, fmaf(m21, sph[u].y, fmaf(m22, sph[u].z, w2)));
-                    const bool near = (fabsf(s0) <= fmaf(nr0, sph[u].w, k0)) &
-                                      (fabsf(s1) <= fmaf(nr1, sph[u].w, k1)) & (fabsf(s2) <= fmaf(nr2, sph[u].w, k2));
-                    const int64_t blk = kSphereBatch * qg + u;
-                    lanes[u] = __ballot(near);
-                    if (lanes[u] && blk >= blk0 && blk < blk1) near_mask |= 1u << u;
+                for (int u = 0; u < kGroupBlocks; ++u) {
+                    const PackedBox& b = pb[u];
+                    float s0, s1, s2;
+                    map_point(m, b.cx, b.cy, b.cz, s0, s1, s2);
+                    const float unit = __uint_as_float(b.h >> 24 << 23);
+                    const float hx = (float)(b.h & 255u), hy = (float)(b.h >> 8 & 255u), hz = (float)(b.h >> 16 & 255u);
+                    const float r0 = fmaf(fmaf(fabsf(m.m00), hx, fmaf(fabsf(m.m01), hy, fabsf(m.m02) * hz)), unit, m.k0);
+                    const float r1 = fmaf(fmaf(fabsf(m.m10), hx, fmaf(fabsf(m.m11), hy, fabsf(m.m12) * hz)), unit, m.k1);
+                    const float r2 = fmaf(fmaf(fabsf(m.m20), hx, fmaf(fabsf(m.m21), hy, fabsf(m.m22) * hz)), unit, m.k2);
+                    const bool near = (fabsf(s0) <= r0) & (fabsf(s1) <= r1) & (fabsf(s2) <= r2);
+                    if (__ballot(near)) near_mask |= 1u << u;
                 }
-                // the blocks some lane's box may reach: handed to the workgroup
-                // while it has room, else tested here
-                int slot = kDeferCap;
-                if (near_mask && lane == 0 && *ndef < kDeferCap) slot = atomicAdd(ndef, __builtin_popcount(near_mask));
-                slot = __builtin_amdgcn_readfirstlane(slot);
-                while (near_mask) {   // wave-uniform
-                    const int u = __builtin_ctz(near_mask);
-                    near_mask &= near_mask - 1;
-                    if (slot < kDeferCap) {
-                        if (lane == 0)
-                            s_def[slot] = Deferred{lanes[u], kSphereBatch * qg + u, m_lo, m_hi, c_lo + cb * 64, i};
-                        ++slot;
-                    } else {
-                        block_min<CUBIC, DT>(points, jb + u * kBlockPts, m_lo, m_hi, lg, G, nx, nxy, m00, m01, m02,
-                                             w0, m10, m11, m12, w1, m20, m21, m22, w2, best);
+                near_mask &= valid;
+                if (near_mask) {
+                    if (tile < 0) {
+                        if (lane == 0) tile = atomicAdd(&sh.tiles, 1);
+                        tile = __builtin_amdgcn_readfirstlane(tile);
+                        if (lane == 0) sh.tile[tile] = Tile{i, c0, cn};
+                        sh.best[tile][lane] = 0;
+                    }
+                    int slot = 0;
+                    if (lane == 0) slot = atomicAdd(&sh.listed, __builtin_popcount(near_mask));
+                    slot = __builtin_amdgcn_readfirstlane(slot);
+                    // lane u writes block u
+                    if (lane < kGroupBlocks && (near_mask >> lane & 1)) {
+                        const int64_t index = group0 * kGroupBlocks + b0 + lane, j = index * kBlockPts;
+                        uint32_t pts = (1u << kBlockPts) - 1;   // the trajectory's points of the block
+                        if (j < m_lo) pts &= pts << (m_lo - j);
+                        if (j + kBlockPts > m_hi) pts &= (1u << (m_hi - j)) - 1;
+                        sh.block[slot + __builtin_popcount(near_mask & ((1u << lane) - 1))] =
+                            Block{(uint32_t)index, (uint32_t)tile | pts << 16};
                     }
                 }
             }
         }
-        if (cl < c_n && best < INFINITY) atomicMax(&p.keys[(int64_t)c * p.L + i], ~lsdf::ordered_bits(best));
+        if (DEAL) {
+            w.has = false;
+        } else {
+            w.q += w.q_step;
+            w.has = w.q < w.q_end;
+            w.fresh = true;
+        }
     }
 }
-
 
 // Slot of workgroup b (of n) for its wave w: waves 2 and 3 shift by half
 // the grid and odd waves count from the other end, so that a workgroup's
@@ -459,115 +444,215 @@ __device__ __forceinline__ int mix_slot(int b, int n, int w) {
     return (w & 1) ? n - 1 - s : s;
 }
 
-template <bool CUBIC, int DT>
-__global__ __launch_bounds__(kBlock) void query_kernel(QueryArgs p, const float* __restrict__ points,
-                                                       const typename GridT<DT>::T* __restrict__ grid,
-                                                       const float4* __restrict__ spheres,
-                                                       const float4* __restrict__ qspheres,
-                                                       const TrajPlan* __restrict__ plan) {
+// (80 SGPRs let 8 workgroups be resident per CU; with the 106 it would take it
+// is 6, though the runtime's occupancy says 7, so that the grid's last seventh
+// began when the others ended: 64 paths 1.94 ms.  What spills goes to VGPR
+// lanes.)
+template <bool CUBIC, int DT, bool DEAL>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_num_sgpr(80))) void query_kernel(
+    QueryArgs p, const float* __restrict__ points, const typename GridT<DT>::T* __restrict__ grid,
+    const PackedBox* __restrict__ blocks, const Box* __restrict__ groups, TrajPlan* __restrict__ plan) {
+    __shared__ QueryShared sh;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t total = plan[p.K].chunk_start;
-    int64_t q_first, q_end, q_step;
-    if (p.schedule == LSDF_SCHED_XCD_SLICES) {
-        // each XCD (blocks b = x mod 8) takes a contiguous slice of chunks
-        // and deals it round-robin to its waves
-        const int xcd = blockIdx.x % kXcds;
-        const int slot = blockIdx.x / kXcds;
-        q_first = total * xcd / kXcds + (int64_t)wave * p.blocks_per_xcd + mix_slot(slot, p.blocks_per_xcd, wave);
-        q_end = total * (xcd + 1) / kXcds;
-        q_step = (int64_t)p.blocks_per_xcd * kWavesPerBlock;
-    } else {
-        // every wave of the grid takes every W-th chunk
-        q_first = (int64_t)wave * gridDim.x + mix_slot((int)blockIdx.x, (int)gridDim.x, wave);
-        q_end = total;
-        q_step = (int64_t)gridDim.x * kWavesPerBlock;
+    // The waves of one workgroup start a grid's (or slice's) width apart, on
+    // different links or tiles, so that the shared list evens them out.  From there every wave takes every n-th chunk, or (DEAL) the
+    // workgroups take the rest in runs from a counter per XCD.
+    const int xcd = blockIdx.x % kXcds;
+    const bool slices = p.schedule == LSDF_SCHED_XCD_SLICES;   // each XCD (blocks b = x mod 8) its own range of chunks
+    const int64_t lo = slices ? total * xcd / kXcds : 0, hi = slices ? total * (xcd + 1) / kXcds : total;
+    const int n0 = slices ? p.blocks_per_xcd : (int)gridDim.x;
+    Walk w{};
+    w.q = lo + (int64_t)wave * n0 + mix_slot(slices ? (int)blockIdx.x / kXcds : (int)blockIdx.x, n0, wave);
+    w.q_end = hi;
+    w.q_step = (int64_t)n0 * kWavesPerBlock;
+    w.has = w.fresh = w.q < hi;
+    // run r is chunks given + r, given + r + nruns, ...: far apart, as the
+    // chunks near a link, which cost the most, come together
+    const int64_t given = lo + w.q_step;
+    const int64_t run = min((int64_t)kMaxRun, max((int64_t)kWavesPerBlock, (hi - given) / (kRunsPerBlock * n0)));
+    const int64_t nruns = (hi - given + run - 1) / run;
+    if (threadIdx.x == 0) {
+        sh.listed = 0;
+        sh.tiles = 0;
+        sh.run = sh.taken = sh.open = 0;
+        sh.run_step = nruns;
     }
-    // (the waves of one workgroup start a grid's width apart, on different
-    // links or configuration groups, so that their loads differ and the
-    // deferred blocks even them out; mix_slot shuffles which workgroup each
-    // wave index lands in)
-    __shared__ Deferred s_def[kDeferCap];
-    __shared__ int s_ndef;
-    if (threadIdx.x == 0) s_ndef = 0;
-    __syncthreads();
-    if (q_first < q_end)
-        test_chunks<CUBIC, DT>(p, points, grid, spheres, qspheres, plan, q_first, q_end, q_step, lane, s_def, &s_ndef);
+    if (threadIdx.x < (unsigned)p.L) {
+        const LinkGrid& lg = p.link[threadIdx.x];
+        sh.grid[threadIdx.x] = GridView{{lg.half[0], lg.half[1], lg.half[2]}, {lg.n[0], lg.n[1], lg.n[2]}, (int64_t)lg.offset};
+    }
     __syncthreads();
 
-    // the deferred blocks, dealt round-robin to the workgroup's waves
-    const int nd = min(s_ndef, kDeferCap);
-    for (int it = wave; it < nd; it += kWavesPerBlock) {
-        const DeferredView d = read_deferred(s_def[it], lane);
-        const int c = d.c0 + lane;
-        const LinkGrid& lg = p.link[d.link];
-        Map mp;
-        load_map(p, d.link, c, d.mine, mp);
-        float best = INFINITY;
-        block_min<CUBIC, DT>(points, d.blk * kBlockPts, d.m_lo, d.m_hi, lg, grid + lg.offset, lg.n[0],
-                             lg.n[0] * lg.n[1], mp.m00, mp.m01, mp.m02, mp.w0, mp.m10, mp.m11, mp.m12, mp.w1, mp.m20,
-                             mp.m21, mp.m22, mp.w2, best);
-        if (d.mine && best < INFINITY) atomicMax(&p.keys[(int64_t)c * p.L + d.link], ~lsdf::ordered_bits(best));
+    float4* const queue = sh.pair[wave];
+    int waiting = 0;   // pairs in the wave's queue
+    // the grid values of the queue's last n pairs, one per lane
+    auto evaluate = [&](int n) {
+        queue_fence();
+        waiting -= n;
+        if (lane < n) {
+            const float4 e = queue[waiting + lane];
+            const int at = __float_as_int(e.w);
+            const GridView gv = sh.grid[sh.tile[at >> 6].link];
+            LinkGrid lg;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                lg.half[a] = gv.half[a];
+                lg.n[a] = gv.n[a];
+            }
+            const float val = lsdf::cell_value<DT>(grid + gv.offset, lg, e.x, e.y, e.z);
+            if (val < INFINITY) atomicMax(&sh.best[at >> 6][at & 63], ~lsdf::ordered_bits(val));
+        }
+        queue_fence();
+    };
+
+    for (;;) {
+        collect<DEAL>(p, blocks, groups, plan, w, lane, sh);
+        if (w.has && lane == 0) atomicAdd(&sh.open, 1);
+        __syncthreads();
+        const int nd = sh.listed, nt = sh.tiles;
+        const bool left = sh.open > 0;
+        const bool dry = DEAL && sh.taken >= sh.run;   // the run is through
+        int64_t next_q = hi;
+        if (dry && given < hi && threadIdx.x == 0) {   // fetched while the list is worked off
+            const int64_t n = atomicAdd(&reinterpret_cast<PlanEnd*>(&plan[p.K])->next[xcd], 1);
+            next_q = given + (slices ? n : n * kXcds + xcd);
+        }
+        // the list's blocks, dealt to the workgroup's waves in runs; a long
+        // list's runs are longer, so that its map is loaded once for several
+        const int take = nd >= kLongList ? kTake : 1;
+        int tile = -1;
+        Tile t{};
+        Map m;
+        for (int r = wave * take; r < nd; r += kWavesPerBlock * take) {
+            for (int it = r; it < min(r + take, nd); ++it) {
+                const uint32_t index = __builtin_amdgcn_readfirstlane(sh.block[it].index);
+                const uint32_t tp = __builtin_amdgcn_readfirstlane(sh.block[it].tile_points);
+                if ((int)(tp & 0xffffu) != tile) {
+                    tile = (int)(tp & 0xffffu);
+                    t.link = __builtin_amdgcn_readfirstlane(sh.tile[tile].link);
+                    t.c0 = __builtin_amdgcn_readfirstlane(sh.tile[tile].c0);
+                    t.n = __builtin_amdgcn_readfirstlane(sh.tile[tile].n);
+                    load_map(p, t.link, t.c0, t.n, lane, m);
+                }
+                const LinkGrid& lg = p.link[t.link];
+                const int64_t j = (int64_t)index * kBlockPts;
+                uint32_t any = (1u << kBlockPts) - 1;   // the points inside some lane's box
+                // the block's coordinates, one per lane
+                const float* const at = points + 3 * j;
+                const float xl = at[(uint32_t)min(lane, j + kBlockPts <= p.M ? 3 * kBlockPts - 1 : 3 * (int)(p.M - j) - 1)];
+                if (j + kBlockPts <= p.M) {
+                    any = 0;
+#pragma unroll
+                    for (int u = 0; u < kBlockPts; ++u) {
+                        float v0, v1, v2;
+                        map_point(m, at[3 * u], at[3 * u + 1], at[3 * u + 2], v0, v1, v2);
+                        if (__ballot(inside<CUBIC>(lg, v0, v1, v2))) any |= 1u << u;
+                    }
+                }
+                any &= tp >> 16;
+                while (any) {   // wave-uniform
+                    const int u = 3 * __builtin_ctz(any);
+                    any &= any - 1;
+                    auto coord = [&](int k) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(xl), k)); };
+                    float v0, v1, v2;
+                    map_point(m, coord(u), coord(u + 1), coord(u + 2), v0, v1, v2);
+                    const bool is = inside<CUBIC>(lg, v0, v1, v2);
+                    const uint64_t lanes = __ballot(is);
+                    if (is)
+                        queue[waiting + __builtin_amdgcn_mbcnt_hi((uint32_t)(lanes >> 32),
+                                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)lanes, 0))] =
+                            make_float4(v0, v1, v2, __int_as_float(64 * tile + lane));
+                    waiting += __builtin_popcountll(lanes);
+                    if (waiting >= 64) evaluate(64);
+                }
+            }
+        }
+        if (waiting > 0) evaluate(waiting);
+        __syncthreads();
+        for (int g = wave; g < nt; g += kWavesPerBlock) {
+            const uint32_t kv = sh.best[g][lane];
+            if (kv) atomicMax(&p.keys[(int64_t)(sh.tile[g].c0 + lane) * p.L + sh.tile[g].link], kv);
+        }
+        if (!left && (!DEAL || (dry && given >= hi))) break;
+        __syncthreads();   // the list, the table and the counters are read
+        if (threadIdx.x == 0) {
+            sh.listed = sh.tiles = sh.open = 0;
+            if (DEAL && dry) {
+                sh.run_q = next_q;
+                sh.run = next_q < min(given + nruns, hi) ? (int)((hi - next_q + nruns - 1) / nruns) : 0;
+                sh.taken = 0;
+            }
+        }
+        __syncthreads();
+        if (DEAL && dry && sh.run == 0 && !left) break;
     }
 }
 
-// Culling spheres of block b (8 points from 8 b) and, for b = 4 q, of quad
-// q (blocks 4 q to 4 q + 3), from the thread of block b; the four threads of
-// a quad are adjacent lanes and combine their boxes and radii by shuffles.
-// A sphere's centre is the centre of its points' box and its radius the
-// largest distance to it, widened by a relative 1e-5, by 1e-4 of the sum of
-// the coordinates' magnitudes (which bounds FP32 rounding of the mapped
-// coordinates) and by 1e-6 m.  Past the end of the cloud the last point
-// repeats, which changes neither a box nor a radius.  Every lane of a quad
+// The widened box of points in [lo, hi]: its half extents grow by a relative
+// 1e-5, by 1e-4 of the largest coordinate magnitude on their axis (which
+// bounds FP32 rounding of the mapped coordinates many times over) and by
+// 1e-6 m.  Where that is not finite the box is one that reaches everything.
+__device__ __forceinline__ Box box_of(const float (&lo)[3], const float (&hi)[3]) {
+    float c[3], h[3];
+    bool finite = true;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        c[a] = 0.5f * lo[a] + 0.5f * hi[a];
+        const float r = fmaxf(hi[a] - c[a], c[a] - lo[a]);
+        h[a] = fmaf(r, 1.00001f, fmaf(1e-4f, fabsf(c[a]) + r, 1e-6f));
+        finite &= h[a] < 1e30f;   // false for NaN
+    }
+    if (!finite) return Box{0.f, 0.f, 0.f, 1e30f, 1e30f, 1e30f};
+    return Box{c[0], c[1], c[2], h[0], h[1], h[2]};
+}
+
+__device__ __forceinline__ PackedBox pack_box(const Box& b) {
+    // the power of two from hmax / 255 up, and the half extents in units of it,
+    // rounded up (hmax >= 1e-6 keeps both it and its inverse normal)
+    const float hmax = fmaxf(b.hx, fmaxf(b.hy, b.hz));
+    const uint32_t unit = (__float_as_uint(hmax * (1.0001f / 255.0f)) + 0x7fffffu) & 0x7f800000u;
+    const float inv = __uint_as_float((254u << 23) - unit);
+    const uint32_t x = (uint32_t)ceilf(b.hx * inv), y = (uint32_t)ceilf(b.hy * inv), z = (uint32_t)ceilf(b.hz * inv);
+    return PackedBox{b.cx, b.cy, b.cz, unit << 1 | z << 16 | y << 8 | x};
+}
+
+// The boxes of block b (8 points from 8 b) and, for b = 8 g, of group g
+// (blocks 8 g to 8 g + 7), from the thread of block b; the eight threads of a
+// group are adjacent lanes and combine their boxes by shuffles.  Past the end
+// of the cloud the last point repeats, which changes no box; NaN coordinates
+// are left out (such a point is inside no grid's box).  Every lane of a group
 // must call this together.
-__device__ __forceinline__ float4 widen(float cx, float cy, float cz, float r2) {
-    const float r = sqrtf(r2);
-    const float e = fabsf(cx) + fabsf(cy) + fabsf(cz) + 3.0f * r;
-    return make_float4(cx, cy, cz, fmaf(r, 1.00001f, fmaf(1e-4f, e, 1e-6f)));
-}
-
-__device__ __forceinline__ void block_and_quad_spheres(const float* __restrict__ points, int64_t b, int64_t M,
-                                                       float4* block_out, float4* quad_out) {
-    float x[kBlockPts], y[kBlockPts], z[kBlockPts];
+__device__ __forceinline__ void block_and_group_boxes(const float* __restrict__ points, int64_t b, int64_t M,
+                                                      PackedBox* block_out, Box* group_out) {
+    float x[kBlockPts][3];
 #pragma unroll
     for (int k = 0; k < kBlockPts; ++k) {
         const int64_t j = min(b * kBlockPts + k, M - 1);
-        x[k] = points[3 * j + 0];
-        y[k] = points[3 * j + 1];
-        z[k] = points[3 * j + 2];
-    }
-    float lo0 = x[0], lo1 = y[0], lo2 = z[0], hi0 = x[0], hi1 = y[0], hi2 = z[0];
 #pragma unroll
-    for (int k = 1; k < kBlockPts; ++k) {
-        lo0 = fminf(lo0, x[k]); hi0 = fmaxf(hi0, x[k]);
-        lo1 = fminf(lo1, y[k]); hi1 = fmaxf(hi1, y[k]);
-        lo2 = fminf(lo2, z[k]); hi2 = fmaxf(hi2, z[k]);
+        for (int a = 0; a < 3; ++a) x[k][a] = points[3 * j + a];
     }
-    auto radius2 = [&](float cx, float cy, float cz) {
-        float r2 = 0.0f;
+    float lo[3], hi[3];
 #pragma unroll
-        for (int k = 0; k < kBlockPts; ++k) {
-            const float dx = x[k] - cx, dy = y[k] - cy, dz = z[k] - cz;
-            r2 = fmaxf(r2, fmaf(dx, dx, fmaf(dy, dy, dz * dz)));
+    for (int a = 0; a < 3; ++a) {
+        lo[a] = hi[a] = x[0][a];
+#pragma unroll
+        for (int k = 1; k < kBlockPts; ++k) {
+            lo[a] = fminf(lo[a], x[k][a]);
+            hi[a] = fmaxf(hi[a], x[k][a]);
         }
-        return r2;
-    };
-    {
-        const float cx = 0.5f * (lo0 + hi0), cy = 0.5f * (lo1 + hi1), cz = 0.5f * (lo2 + hi2);
-        const float4 sb = widen(cx, cy, cz, radius2(cx, cy, cz));
-        if (b * kBlockPts < M) *block_out = sb;
     }
+    if (b * kBlockPts < M) *block_out = pack_box(box_of(lo, hi));
 #pragma unroll
-    for (int o = 1; o < kSphereBatch; o <<= 1) {
-        lo0 = fminf(lo0, __shfl_xor(lo0, o, 64)); hi0 = fmaxf(hi0, __shfl_xor(hi0, o, 64));
-        lo1 = fminf(lo1, __shfl_xor(lo1, o, 64)); hi1 = fmaxf(hi1, __shfl_xor(hi1, o, 64));
-        lo2 = fminf(lo2, __shfl_xor(lo2, o, 64)); hi2 = fmaxf(hi2, __shfl_xor(hi2, o, 64));
+    for (int o = 1; o < kGroupBlocks; o <<= 1) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            lo[a] = fminf(lo[a], __shfl_xor(lo[a], o, 64));
+            hi[a] = fmaxf(hi[a], __shfl_xor(hi[a], o, 64));
+        }
     }
-    const float cx = 0.5f * (lo0 + hi0), cy = 0.5f * (lo1 + hi1), cz = 0.5f * (lo2 + hi2);
-    float r2 = radius2(cx, cy, cz);
-#pragma unroll
-    for (int o = 1; o < kSphereBatch; o <<= 1) r2 = fmaxf(r2, __shfl_xor(r2, o, 64));
-    if ((b & (kSphereBatch - 1)) == 0) *quad_out = widen(cx, cy, cz, r2);
+    if ((b & (kGroupBlocks - 1)) == 0) *group_out = box_of(lo, hi);
 }
 
 // The plan of the batched queries (in one workgroup of 256 threads).
@@ -589,9 +674,9 @@ __device__ __forceinline__ void build_plan(const PrepArgs& a) {
             e.c_lo = c0;
             e.c_n = c1 - c0;
             e.cgroups = (e.c_n + 63) / 64;
-            // the quads (aligned in the concatenated cloud) that hold a point of [m0, m1)
-            const int64_t nq = m1 > m0 ? (m1 + kQuadPts - 1) / kQuadPts - m0 / kQuadPts : 0;
-            e.chunks_per_group = (int32_t)((nq + a.chunk_quads - 1) / a.chunk_quads);
+            // the groups (aligned in the concatenated cloud) that hold a point of [m0, m1)
+            const int64_t ng = m1 > m0 ? (m1 + kGroupPts - 1) / kGroupPts - m0 / kGroupPts : 0;
+            e.chunks_per_group = (int32_t)((ng + a.chunk_groups - 1) / a.chunk_groups) << a.split;
             n = (int64_t)a.L * e.cgroups * e.chunks_per_group;
         }
         scan[t] = n;
@@ -610,9 +695,9 @@ __device__ __forceinline__ void build_plan(const PrepArgs& a) {
         __syncthreads();
     }
     if (t == 0) {
-        TrajPlan e{};
+        PlanEnd e{};
         e.chunk_start = carry;
-        a.plan[a.K] = e;
+        *reinterpret_cast<PlanEnd*>(&a.plan[a.K]) = e;
     }
 }
 
@@ -620,10 +705,10 @@ __device__ __forceinline__ void build_plan(const PrepArgs& a) {
 // that their latencies overlap.  Thread t < C L zeroes key t and writes the
 // map table entry of (link t / C, configuration t mod C), from the given pose
 // or, in the fused form, from the pose it computes from the joint angles.
-// Thread sphere_base + s bounds block s of 8 consecutive points of the
-// concatenated cloud by a sphere, and with its quad's three other lanes quad
-// s / 4 (blocks s - s mod 4 to s - s mod 4 + 3) by another (sphere_base is
-// a multiple of the wave size, so every wave holds whole quads).  The last
+// Thread box_base + s bounds block s of 8 consecutive points of the
+// concatenated cloud by a box, and with its group's seven other lanes group
+// s / 8 by another (box_base is a multiple of the wave size, so every wave
+// holds whole groups).  The last
 // workgroup builds the plan: each trajectory's ranges clamped into [0, C)
 // and [0, M) (so a bad offset table gives wrong ranges, never an access out
 // of bounds), its chunk count and the exclusive prefix sum of the counts.
@@ -633,19 +718,19 @@ __global__ __launch_bounds__(256) void prep_kernel(PrepArgs a) {
         build_plan(a);
         return;
     }
-    if (b >= a.sphere_base) {
-        const int64_t sb = b - a.sphere_base;
-        // uniform over the four lanes of a quad
-        if (sb / kSphereBatch * kQuadPts < a.M)
-            block_and_quad_spheres(a.points, sb, a.M, &a.spheres[sb], &a.qspheres[sb / kSphereBatch]);
+    if (b >= a.box_base) {
+        const int64_t sb = b - a.box_base;
+        // uniform over the eight lanes of a group
+        if (sb / kGroupBlocks * kGroupPts < a.M)
+            block_and_group_boxes(a.points, sb, a.M, &a.blocks[sb], &a.groups[sb / kGroupBlocks]);
         return;
     }
     if (b < (int64_t)a.C * a.L) {
         a.keys[b] = 0u;
         // map of link i at configuration c: row a of R^T scaled by invh_a,
         // offset -invh_a (R^T t)_a + cen_a (the inverse pose of Eq. 4 with
-        // the grid scaling folded in); then the culling thresholds: the
-        // row norms (x (1 + 1e-6)) and half_a plus a bound on FP32 rounding
+        // the grid scaling folded in); then the culling thresholds: half_a
+        // plus a bound on FP32 rounding
         const int i = (int)(b / a.C);
         const int64_t c = b - (int64_t)i * a.C;
         const LinkGrid& lg = a.link[i];
@@ -675,11 +760,7 @@ __global__ __launch_bounds__(256) void prep_kernel(PrepArgs a) {
         f[10] = fmaf(-lg.invh[1], fmaf(r01, t0, fmaf(r11, t1, r21 * t2)), lg.cen[1]);
         f[11] = fmaf(-lg.invh[2], fmaf(r02, t0, fmaf(r12, t1, r22 * t2)), lg.cen[2]);
 #pragma unroll
-        for (int ax = 0; ax < 3; ++ax) {
-            const float* m = f + 3 * ax;
-            f[12 + ax] = sqrtf(fmaf(m[0], m[0], fmaf(m[1], m[1], m[2] * m[2]))) * 1.000001f;
-            f[15 + ax] = lg.half[ax] + fmaf(1e-4f, fabsf(f[9 + ax]), 1e-3f);
-        }
+        for (int ax = 0; ax < 3; ++ax) f[12 + ax] = lg.half[ax] + fmaf(1e-4f, fabsf(f[9 + ax]), 1e-3f);
         float* out = a.maps + (int64_t)i * kMapFields * a.C + c;
 #pragma unroll
         for (int k = 0; k < kMapFields; ++k) out[(int64_t)k * a.C] = f[k];
@@ -735,40 +816,57 @@ int lsdf::launch_zero_words(uint32_t* w, int64_t n, hipStream_t s) {
 namespace {
 
 size_t keys_bytes(int64_t C, int64_t L) { return ((size_t)(C * L) * 4 + 255) / 256 * 256; }
-// Block spheres for whole quads (the query loads a quad's four together and
-// ignores those past the cloud's last block), then the quad spheres.
-int64_t quad_count(int64_t M) { return (M + kQuadPts - 1) / kQuadPts; }
-size_t sphere_bytes(int64_t M) { return ((size_t)quad_count(M) * (kSphereBatch + 1) * 16 + 255) / 256 * 256; }
+// The blocks' boxes (16 bytes each), then the groups' (24), in 80 bytes per 32
+// points: callers hold workspaces of that size and the scratch array's limit
+// follows from it, so it stays; with q = ceil(M / 32) the boxes take at most
+// 64 q + 24 ceil(q / 2) bytes, no more than that but for q = 1, whose 88 bytes
+// round up to the same 256.
+int64_t block_count(int64_t M) { return (M + kBlockPts - 1) / kBlockPts; }
+int64_t group_count(int64_t M) { return (M + kGroupPts - 1) / kGroupPts; }
+size_t box_bytes(int64_t M) { return ((size_t)((M + 31) / 32) * 80 + 255) / 256 * 256; }
 size_t plan_bytes(int64_t K) { return ((size_t)(K + 1) * sizeof(TrajPlan) + 255) / 256 * 256; }
-size_t map_bytes(int64_t C, int64_t L) { return ((size_t)(C * L) * kMapFields * 4 + 255) / 256 * 256; }
+// (72 bytes per link and configuration likewise; the map table takes 60)
+size_t map_bytes(int64_t C, int64_t L) { return ((size_t)(C * L) * 72 + 255) / 256 * 256; }
+static_assert(kMapFields * 4 <= 72, "the map table's share of the workspace");
 
-// Workspace: keys | block and quad spheres | plan | maps, each 256-byte aligned.
+// Workspace: keys | block and group boxes | plan | maps, each 256-byte aligned.
 size_t workspace_bytes(int64_t K, int64_t C, int64_t L, int64_t M) {
-    return keys_bytes(C, L) + sphere_bytes(M) + plan_bytes(K) + map_bytes(C, L);
+    return keys_bytes(C, L) + box_bytes(M) + plan_bytes(K) + map_bytes(C, L);
 }
 
 // Workgroups of the query kernel variant that fit on one CU at once.
-template <bool CUBIC, int DT>
+template <bool CUBIC, int DT, bool DEAL>
 int resident_blocks_of() {
     static std::atomic<int> cached{0};
     int v = cached.load(std::memory_order_relaxed);
     if (v > 0) return v;
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, query_kernel<CUBIC, DT>, kBlock, 0) != hipSuccess || n < 1)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, query_kernel<CUBIC, DT, DEAL>, kBlock, 0) != hipSuccess || n < 1)
         n = kDefaultBlocksPerCu;
     n = std::min(n, kMaxBlocksPerCu);
     cached.store(n, std::memory_order_relaxed);
     return n;
 }
 
-int resident_blocks(int dtype, bool cubic) {
+// Calls f with the kernel's template arguments.
+template <bool CUBIC, int DT, bool DEAL>
+struct Variant {
+    static constexpr bool cubic = CUBIC, deal = DEAL;
+    static constexpr int dtype = DT;
+};
+template <bool CUBIC, int DT, class F>
+auto with_deal(bool deal, F&& f) {
+    return deal ? f(Variant<CUBIC, DT, true>{}) : f(Variant<CUBIC, DT, false>{});
+}
+template <class F>
+auto with_variant(int dtype, bool cubic, bool deal, F&& f) {
     switch (dtype * 2 + (cubic ? 1 : 0)) {
-        case LSDF_F32 * 2 + 1: return resident_blocks_of<true, LSDF_F32>();
-        case LSDF_F32 * 2: return resident_blocks_of<false, LSDF_F32>();
-        case LSDF_BF16 * 2 + 1: return resident_blocks_of<true, LSDF_BF16>();
-        case LSDF_BF16 * 2: return resident_blocks_of<false, LSDF_BF16>();
-        case LSDF_F16 * 2 + 1: return resident_blocks_of<true, LSDF_F16>();
-        default: return resident_blocks_of<false, LSDF_F16>();
+        case LSDF_F32 * 2 + 1: return with_deal<true, LSDF_F32>(deal, f);
+        case LSDF_F32 * 2: return with_deal<false, LSDF_F32>(deal, f);
+        case LSDF_BF16 * 2 + 1: return with_deal<true, LSDF_BF16>(deal, f);
+        case LSDF_BF16 * 2: return with_deal<false, LSDF_BF16>(deal, f);
+        case LSDF_F16 * 2 + 1: return with_deal<true, LSDF_F16>(deal, f);
+        default: return with_deal<false, LSDF_F16>(deal, f);
     }
 }
 
@@ -848,21 +946,30 @@ int run_query(const char* who, int32_t K, const int32_t* c_off, const int64_t* m
     }
     const int cus = device_cus();
     if (cus <= 0) return fail(LSDF_E_DEVICE, "%s: cannot read the device's compute-unit count", who);
-    if (!(tuning && tuning->blocks_per_cu != 0)) blocks_per_cu = resident_blocks(dtype, cubic);
+    if (!(tuning && tuning->blocks_per_cu != 0)) 
+        blocks_per_cu = with_variant(dtype, cubic, false, [](auto v) {
+            using V = decltype(v);
+            return resident_blocks_of<V::cubic, V::dtype, V::deal>();
+        });
     if (!(tuning && tuning->chunk_points != 0))   // from the capacities C and M when offsets are given
         chunk_blocks = default_chunk_blocks(C, L, M, (int64_t)cus * blocks_per_cu * kWavesPerBlock);
+    const bool deal = (double)L * ((C + 63) / 64) * ((M + kBlockPts * chunk_blocks - 1) / (kBlockPts * chunk_blocks)) >=
+                      (double)K * kDealChunks * cus * blocks_per_cu * kWavesPerBlock;
     hipStream_t s = as_stream(stream);
     char* ws = static_cast<char*>(workspace);
-    float4* spheres = reinterpret_cast<float4*>(ws + keys_bytes(C, L));
-    float4* qspheres = spheres + kSphereBatch * quad_count(M);
-    TrajPlan* plan = reinterpret_cast<TrajPlan*>(ws + keys_bytes(C, L) + sphere_bytes(M));
-    float* maps = reinterpret_cast<float*>(ws + keys_bytes(C, L) + sphere_bytes(M) + plan_bytes(K));
+    PackedBox* block_box = reinterpret_cast<PackedBox*>(ws + keys_bytes(C, L));
+    Box* group_box = reinterpret_cast<Box*>(block_box + block_count(M));
+    TrajPlan* plan = reinterpret_cast<TrajPlan*>(ws + keys_bytes(C, L) + box_bytes(M));
+    float* maps = reinterpret_cast<float*>(ws + keys_bytes(C, L) + box_bytes(M) + plan_bytes(K));
     p.maps = maps;
     p.keys = reinterpret_cast<uint32_t*>(ws);
+    p.M = M;
     p.C = C;
     p.K = K;
     p.L = L;
-    p.chunk_quads = (chunk_blocks + kSphereBatch - 1) / kSphereBatch;
+    // chunks of whole groups, or of a half or quarter of one
+    const int chunk_groups = (chunk_blocks + kGroupBlocks - 1) / kGroupBlocks;
+    p.split = chunk_blocks >= kGroupBlocks ? 0 : chunk_blocks >= kGroupBlocks / 2 ? 1 : 2;
     p.schedule = schedule;
     // the first kernel runs when there are points to test, or when poses
     // computed from joint angles are asked for
@@ -876,8 +983,8 @@ int run_query(const char* who, int32_t K, const int32_t* c_off, const int64_t* m
         }
         a.link_T = link_T;
         a.points = points;
-        a.spheres = spheres;
-        a.qspheres = qspheres;
+        a.blocks = block_box;
+        a.groups = group_box;
         a.plan = plan;
         a.maps = maps;
         a.keys = p.keys;
@@ -887,11 +994,12 @@ int run_query(const char* who, int32_t K, const int32_t* c_off, const int64_t* m
         a.C = C;
         a.K = K;
         a.L = L;
-        a.chunk_quads = p.chunk_quads;
+        a.chunk_groups = chunk_groups;
+        a.split = p.split;
         // map threads, then (from a wave boundary) one thread per block of
-        // every quad, then the plan's workgroup
-        a.sphere_base = ((int64_t)C * L + 63) / 64 * 64;
-        const int64_t threads = a.sphere_base + kSphereBatch * quad_count(M);
+        // every group, then the plan's workgroup
+        a.box_base = ((int64_t)C * L + 63) / 64 * 64;
+        const int64_t threads = a.box_base + kGroupBlocks * group_count(M);
         hipLaunchKernelGGL(prep_kernel, dim3((unsigned)((threads + 255) / 256 + 1)), dim3(256), 0, s, a);
         rc = check_launch(who);
         if (rc != LSDF_OK) return rc;
@@ -902,27 +1010,23 @@ int run_query(const char* who, int32_t K, const int32_t* c_off, const int64_t* m
         // given by C and M), no more waves than chunks
         int64_t blocks = (int64_t)cus * blocks_per_cu;
         if (!c_off) {
-            const int64_t nq = quad_count(M);
-            const int64_t chunks = (int64_t)L * ((C + 63) / 64) * ((nq + p.chunk_quads - 1) / p.chunk_quads);
+            const int64_t chunks = (int64_t)L * ((C + 63) / 64) * (((group_count(M) + chunk_groups - 1) / chunk_groups) << p.split);
             blocks = std::min<int64_t>(blocks, (chunks + kWavesPerBlock - 1) / kWavesPerBlock);
         }
         blocks = (blocks + kXcds - 1) / kXcds * kXcds;
         p.blocks_per_xcd = (int32_t)(blocks / kXcds);
-        const float4* sph = spheres;
-        const float4* qsph = qspheres;
-        const TrajPlan* pl = plan;
+        const PackedBox* bb = block_box;
+        const Box* gb = group_box;
+        TrajPlan* pl = plan;
         const dim3 gd((unsigned)blocks), bd(kBlock);
         hipEvent_t ev0, ev1;
         take_kernel_events(&ev0, &ev1);
         if (ev0 && hipEventRecord(ev0, s) != hipSuccess) return fail(LSDF_E_DEVICE, "%s: event record failed", who);
-        switch (dtype * 2 + (cubic ? 1 : 0)) {
-            case LSDF_F32 * 2 + 1: hipLaunchKernelGGL((query_kernel<true, LSDF_F32>), gd, bd, 0, s, p, points, static_cast<const float*>(grid_buf), sph, qsph, pl); break;
-            case LSDF_F32 * 2: hipLaunchKernelGGL((query_kernel<false, LSDF_F32>), gd, bd, 0, s, p, points, static_cast<const float*>(grid_buf), sph, qsph, pl); break;
-            case LSDF_BF16 * 2 + 1: hipLaunchKernelGGL((query_kernel<true, LSDF_BF16>), gd, bd, 0, s, p, points, static_cast<const uint16_t*>(grid_buf), sph, qsph, pl); break;
-            case LSDF_BF16 * 2: hipLaunchKernelGGL((query_kernel<false, LSDF_BF16>), gd, bd, 0, s, p, points, static_cast<const uint16_t*>(grid_buf), sph, qsph, pl); break;
-            case LSDF_F16 * 2 + 1: hipLaunchKernelGGL((query_kernel<true, LSDF_F16>), gd, bd, 0, s, p, points, static_cast<const _Float16*>(grid_buf), sph, qsph, pl); break;
-            default: hipLaunchKernelGGL((query_kernel<false, LSDF_F16>), gd, bd, 0, s, p, points, static_cast<const _Float16*>(grid_buf), sph, qsph, pl); break;
-        }
+        with_variant(dtype, cubic, deal, [&](auto v) {
+            using V = decltype(v);
+            hipLaunchKernelGGL((query_kernel<V::cubic, V::dtype, V::deal>), gd, bd, 0, s, p, points,
+                               static_cast<const typename GridT<V::dtype>::T*>(grid_buf), bb, gb, pl);
+        });
         rc = check_launch(who);
         if (rc != LSDF_OK) return rc;
         if (ev1 && hipEventRecord(ev1, s) != hipSuccess) return fail(LSDF_E_DEVICE, "%s: event record failed", who);
