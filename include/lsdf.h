@@ -196,14 +196,16 @@ int lsdf_query_min_distance_noalloc(const float* link_T, int32_t C, int32_t L,
 #define LSDF_SCHED_XCD_SLICES  1   /* each XCD takes a contiguous slice of
                                       the work (its L2 sees few link grids) */
 #define LSDF_SCHED_INTERLEAVED 2   /* every wave of the grid takes every W-th
-                                      chunk (balances uneven work) */
+                                      chunk, or of many chunks the next ones
+                                      as it needs them (balances uneven work) */
 typedef struct {
     int32_t chunk_points;   /* points per work chunk: a multiple of 8 in
-                               [8, 8192], rounded up to a multiple of 32
-                               (a chunk takes every n-th run of 32 points of
-                               its trajectory's cloud); 0 = default (at
-                               most about one chunk per wave of the grid
-                               for C and M, 32 to 1024 points) */
+                               [8, 8192], rounded up to 16, 32 or a
+                               multiple of 64 (a chunk takes every n-th run
+                               of 64 points of its trajectory's cloud, or a
+                               part of a run); 0 = default (at most about
+                               one chunk per wave of the grid for C and M,
+                               16 to 1024 points) */
     int32_t blocks_per_cu;  /* workgroups of the persistent grid per compute
                                unit, in [1, 16]; 0 = default (as many as fit
                                on a CU at once) */

@@ -188,8 +188,13 @@ def last_error() -> str:
 
 def _stream_handle(stream, device):
     if stream is None:
+        # the raw handle, without a Stream object around it (4 us of a call's
+        # 24 were spent on that)
+        index = device.index if isinstance(device, torch.device) and device.index is not None else None
+        if index is not None:
+            return torch._C._cuda_getCurrentRawStream(index)
         stream = torch.cuda.current_stream(device)
-    return ct.c_void_p(stream.cuda_stream)
+    return stream.cuda_stream
 
 
 def _require(t: torch.Tensor, name: str, dtype, shape=None):
@@ -260,8 +265,7 @@ class GridSet:
 def fk_batch(dh, q: torch.Tensor, base_T=None, out: torch.Tensor | None = None, stream=None) -> torch.Tensor:
     """Link poses [C][dof+1][3][4] for joint angles q [C][dof] (lsdf_fk_batch)."""
     lib = load_library()
-    dh = np.asarray(dh, dtype=np.float64).reshape(-1, 4)
-    dof = dh.shape[0]
+    rows, dof = _dh_rows(dh)
     if q.dim() != 2 or q.shape[1] != dof:
         raise ValueError(f"q must be [C][{dof}]")
     _require(q, "q", torch.float32)
@@ -269,7 +273,6 @@ def fk_batch(dh, q: torch.Tensor, base_T=None, out: torch.Tensor | None = None, 
     if out is None:
         out = torch.empty((C, dof + 1, 3, 4), dtype=torch.float32, device=q.device)
     _require(out, "out", torch.float32, (C, dof + 1, 3, 4))
-    rows = (lsdf_dh * dof)(*[lsdf_dh(*map(float, r)) for r in dh])
     base_p = None
     if base_T is not None:
         b = np.ascontiguousarray(np.asarray(base_T, dtype=np.float32).reshape(12))
@@ -340,8 +343,8 @@ def _query_outputs(out, C, L, dev, link_dist):
         dist = torch.empty(C, dtype=torch.float32, device=dev)
         link = torch.empty(C, dtype=torch.int32, device=dev)
         ld = torch.empty((C, L), dtype=torch.float32, device=dev) if link_dist else None
-    else:
-        dist, link, ld = out
+        return dist, link, ld
+    dist, link, ld = out
     _require(dist, "out_dist", torch.float32, (C,))
     _require(link, "out_link", torch.int32, (C,))
     if ld is not None:
@@ -363,7 +366,8 @@ def query_min_distance(link_T: torch.Tensor, grids: GridSet, points: torch.Tenso
     dist, link, ld = _query_outputs(out, C, L, dev, link_dist)
     if workspace is None:
         workspace = query_workspace(C, L, M, dev)
-    _require(workspace, "workspace", torch.uint8)
+    else:
+        _require(workspace, "workspace", torch.uint8)
     _check(lib.lsdf_query_min_distance(
         link_T.data_ptr(), C, L, grids.desc, grids.buf.data_ptr(),
         points.data_ptr() if M > 0 else None, M, dist.data_ptr(), link.data_ptr(),
@@ -410,7 +414,8 @@ def query_min_distance_batched(link_T: torch.Tensor, grids: GridSet, points: tor
     dist, link, ld = _query_outputs(out, C, L, dev, link_dist)
     if workspace is None:
         workspace = query_workspace(C, L, M, dev, K=K)
-    _require(workspace, "workspace", torch.uint8)
+    else:
+        _require(workspace, "workspace", torch.uint8)
     tun = ct.byref(tuning) if tuning is not None else None
     _check(lib.lsdf_query_min_distance_batched(
         K, c_offsets.data_ptr(), m_offsets.data_ptr(), link_T.data_ptr(), C, L, grids.desc, grids.buf.data_ptr(),
@@ -422,7 +427,7 @@ def query_min_distance_batched(link_T: torch.Tensor, grids: GridSet, points: tor
 
 def _dh_rows(dh):
     dh = np.asarray(dh, dtype=np.float64).reshape(-1, 4)
-    return (lsdf_dh * dh.shape[0])(*[lsdf_dh(*map(float, r)) for r in dh]), dh.shape[0]
+    return (lsdf_dh * dh.shape[0]).from_buffer_copy(dh.astype(np.float32, order="C")), dh.shape[0]
 
 
 def _base_ptr(base_T):
@@ -462,7 +467,8 @@ def query_from_joints(dh, q: torch.Tensor, grids: GridSet, points: torch.Tensor,
     dist, link, ld = _query_outputs(out, C, L, dev, link_dist)
     if workspace is None:
         workspace = query_workspace(C, L, M, dev, K=K)
-    _require(workspace, "workspace", torch.uint8)
+    else:
+        _require(workspace, "workspace", torch.uint8)
     b, base_p = _base_ptr(base_T)
     tun = ct.byref(tuning) if tuning is not None else None
     _check(lib.lsdf_query_from_joints(
@@ -816,7 +822,8 @@ def query_min_distance_mlp(link_T: torch.Tensor, grids: GridSet, mlp_params: tor
         _require(ld, "out_link_dist", torch.float32, (C, L))
     if workspace is None:
         workspace = query_workspace(C, L, M, dev)
-    _require(workspace, "workspace", torch.uint8)
+    else:
+        _require(workspace, "workspace", torch.uint8)
     _check(lib.lsdf_query_min_distance_mlp(
         link_T.data_ptr(), C, L, grids.desc, grids.buf.data_ptr(), mlp_params.data_ptr(), d, float(margin),
         points.data_ptr() if M > 0 else None, M, dist.data_ptr(), link.data_ptr(),

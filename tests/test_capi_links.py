@@ -26,3 +26,15 @@ def test_links_arguments(n, bad, code):
     want = getattr(B, code)
     assert lib.lsdf_build_link_sdfs(n, verts, nv, ptrs, nt, comps, ncomp, grids, ptr, None) == want
     assert lib.lsdf_sdf_labels_links(n, verts, nv, ptrs, nt, comps, ncomp, grids, ptr, ptrs, 5, ptrs, None) == want
+
+
+@pytest.mark.parametrize("order", ["C", "F", "list"])
+def test_dh_rows_hold_the_table(order):
+    import numpy as np
+    from paper_2309_12543_amd import lsdf as B
+    table = np.random.default_rng(3).uniform(-2, 2, size=(5, 4))
+    given = table.tolist() if order == "list" else np.array(table, order=order)
+    rows, dof = B._dh_rows(given)
+    assert dof == 5
+    for r, want in zip(rows, table.astype(np.float32)):
+        assert [r.a, r.alpha, r.d, r.theta_offset] == want.tolist()
