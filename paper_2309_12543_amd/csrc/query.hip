@@ -94,27 +94,32 @@ constexpr int kGroupBatch = LSDF_QUERY_GROUP_BATCH;
 // that no wave of the persistent grid waits for another to finish; 8 if
 // the runtime cannot say), chunks dealt over the whole grid, at most about
 // one chunk per wave of the grid for the call's sizes (with offset arrays,
-// the capacities C and M): the smallest power of two of blocks of 8 points
-// between 8 (a group) and 128 that gives no more chunks than waves; a quarter
-// of a group where the call is so small that an eighth of the waves would
-// have a group (C = 50, M = 2,000, L = 7: 15.1 us with quarters, 16.3 with
-// halves, 18.2 with whole ones; C = 200, M = 8,000 near the arm, halves where
-// the rule takes whole groups: 59 us, not 49).
+// the capacities C and M, as if every trajectory had its share of both): the
+// smallest power of two of blocks of 8 points between 8 (a group) and 64 that
+// gives no more chunks than waves; a quarter of a group where the call is so
+// small that an eighth of the waves would have a group (C = 50, M = 2,000,
+// L = 7: 15.1 us with quarters, 16.3 with halves, 18.2 with whole ones; C = 200,
+// M = 8,000 near the arm, halves where the rule takes whole groups: 59 us, not
+// 49); 128 blocks where chunks are dealt (64 paths: 1.46 ms, with 64 blocks
+// 1.60), where a wave has a few chunks at most no more than 64 (128: 500 x
+// 100,000 51.6 us, not 48.6; 16 paths 110, not 101).
 constexpr int kDefaultChunkPoints = 1024;
 constexpr int kDefaultBlocksPerCu = 8;
 constexpr int kDefaultSchedule = LSDF_SCHED_INTERLEAVED;
 
-int default_chunk_blocks(int64_t C, int64_t L, int64_t M, int64_t waves) {
-    const int64_t units = L * ((C + 63) / 64) * ((M + kBlockPts - 1) / kBlockPts);
-    if (units <= waves) return kGroupBlocks / 4;
-    int64_t cb = kGroupBlocks;
-    while (cb < 128 && cb * waves <= units) cb *= 2;
-    return (int)cb;
-}
 // From this many chunks per wave on, all but each wave's first are dealt as
 // the workgroups come for them: 64 paths, 55 chunks a wave, 1.43 ms against
 // 1.72 dealt beforehand; 16 paths, 2 chunks a wave, 120 us against 111.
 constexpr int kDealChunks = 16;
+
+int default_chunk_blocks(int64_t K, int64_t C, int64_t L, int64_t M, int64_t waves) {
+    const int64_t units = L * ((C + 63) / 64) * ((M + kBlockPts - 1) / kBlockPts) / K;
+    if (units >= kDealChunks * 128 * waves) return 128;
+    if (units <= waves) return kGroupBlocks / 4;
+    int64_t cb = kGroupBlocks;
+    while (cb < 64 && cb * waves <= units) cb *= 2;
+    return (int)cb;
+}
 constexpr int kRunsPerBlock = 24;   // runs of chunks a workgroup comes for, about (8: 1.62 ms, 16: 1.48)
 constexpr int kMaxRun = 64;         // chunks of a run, at most
 constexpr int kMaxChunkPoints = 8192;
@@ -952,7 +957,7 @@ int run_query(const char* who, int32_t K, const int32_t* c_off, const int64_t* m
             return resident_blocks_of<V::cubic, V::dtype, V::deal>();
         });
     if (!(tuning && tuning->chunk_points != 0))   // from the capacities C and M when offsets are given
-        chunk_blocks = default_chunk_blocks(C, L, M, (int64_t)cus * blocks_per_cu * kWavesPerBlock);
+        chunk_blocks = default_chunk_blocks(K, C, L, M, (int64_t)cus * blocks_per_cu * kWavesPerBlock);
     const bool deal = (double)L * ((C + 63) / 64) * ((M + kBlockPts * chunk_blocks - 1) / (kBlockPts * chunk_blocks)) >=
                       (double)K * kDealChunks * cus * blocks_per_cu * kWavesPerBlock;
     hipStream_t s = as_stream(stream);
