@@ -205,7 +205,7 @@ typedef struct {
                                of 64 points of its trajectory's cloud, or a
                                part of a run); 0 = default (at most about
                                one chunk per wave of the grid for C and M,
-                               16 to 512, or 1024 in large batches) */
+                               16 to 1024) */
     int32_t blocks_per_cu;  /* workgroups of the persistent grid per compute
                                unit, in [1, 16]; 0 = default (as many as fit
                                on a CU at once) */

@@ -92,17 +92,17 @@ constexpr int kGroupBatch = LSDF_QUERY_GROUP_BATCH;
 
 // Default tiling: as many workgroups per CU as can be resident at once (so
 // that no wave of the persistent grid waits for another to finish; 8 if
-// the runtime cannot say), chunks dealt over the whole grid, at most about
-// one chunk per wave of the grid for the call's sizes (with offset arrays,
-// the capacities C and M, as if every trajectory had its share of both): the
-// smallest power of two of blocks of 8 points between 8 (a group) and 64 that
-// gives no more chunks than waves; a quarter of a group where the call is so
-// small that an eighth of the waves would have a group (C = 50, M = 2,000,
-// L = 7: 15.1 us with quarters, 16.3 with halves, 18.2 with whole ones; C = 200,
-// M = 8,000 near the arm, halves where the rule takes whole groups: 59 us, not
-// 49); 128 blocks where chunks are dealt (64 paths: 1.46 ms, with 64 blocks
-// 1.60), where a wave has a few chunks at most no more than 64 (128: 500 x
-// 100,000 51.6 us, not 48.6; 16 paths 110, not 101).
+// the runtime cannot say), chunks dealt over the whole grid, one chunk per
+// wave of the grid at most: the fewest groups per chunk that give no more
+// chunks than waves for the call's sizes (with offset arrays, the capacities C
+// and M, as if every trajectory had its share of both), as the waves with two
+// chunks would end last (C = 500, M = 100,000, L = 7: 11 groups 45.7 us, 8
+// groups and 1.3 chunks a wave 48.6).  Where that takes more than 16, 8 (16
+// paths: 101 us, with 16 groups 110), and 16 where the chunks are dealt (64
+// paths: 1.46 ms, with 8 groups 1.60); a quarter of a group where the call is
+// so small that an eighth of the waves would have a group (C = 50, M = 2,000:
+// 15.1 us with quarters, 16.3 with halves, 18.2 with whole ones; C = 200, M =
+// 8,000 near the arm, halves where the rule takes whole groups: 59 us, not 49).
 constexpr int kDefaultChunkPoints = 1024;
 constexpr int kDefaultBlocksPerCu = 8;
 constexpr int kDefaultSchedule = LSDF_SCHED_INTERLEAVED;
@@ -113,12 +113,13 @@ constexpr int kDefaultSchedule = LSDF_SCHED_INTERLEAVED;
 constexpr int kDealChunks = 16;
 
 int default_chunk_blocks(int64_t K, int64_t C, int64_t L, int64_t M, int64_t waves) {
-    const int64_t units = L * ((C + 63) / 64) * ((M + kBlockPts - 1) / kBlockPts) / K;
-    if (units >= kDealChunks * 128 * waves) return 128;
-    if (units <= waves) return kGroupBlocks / 4;
-    int64_t cb = kGroupBlocks;
-    while (cb < 64 && cb * waves <= units) cb *= 2;
-    return (int)cb;
+    const int64_t tiles = L * std::max(K, (C + 63) / 64), groups = ((M + K - 1) / K + kGroupPts - 1) / kGroupPts;
+    if (tiles * groups * kGroupBlocks <= waves) return kGroupBlocks / 4;
+    if (tiles * groups >= kDealChunks * 16 * waves) return 16 * kGroupBlocks;
+    const int64_t most = K == 1 ? 16 : 8;   // (the trajectories of a batch differ: 12 groups 107 us, 8 101)
+    int64_t g = std::max<int64_t>(1, tiles * groups / waves);
+    while (g <= most && tiles * ((groups + g - 1) / g) > waves) ++g;
+    return (int)(g <= most ? g : 8) * kGroupBlocks;
 }
 constexpr int kRunsPerBlock = 24;   // runs of chunks a workgroup comes for, about (8: 1.62 ms, 16: 1.48)
 constexpr int kMaxRun = 64;         // chunks of a run, at most
