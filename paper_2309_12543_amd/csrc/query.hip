@@ -55,9 +55,9 @@
 // Bound by the VALU and by the latency of its dependent loads.  GPU time of a
 // call on one MI355X, all three kernels, before (spheres, a gather per point
 // and lane, minima straight to global memory) and now: 50 waypoints, 2,000
-// points 17.2 -> 15.1 us; 500, 20,000 32 -> 25 us; 500, 100,000, 128^3 bf16
-// 76 -> 54 us; 333, 12,345 all near the arm 190 -> 71 us; 64 paths of 50 to
-// 1,000 with clouds of 5,000 to 200,000 2.16 -> 1.43 ms.
+// points 17.3 -> 14.9 us; 500, 20,000 31 -> 24 us; 500, 100,000, 128^3 bf16
+// 77 -> 46 us; 333, 12,345 all near the arm 191 -> 70 us; 64 paths of 50 to
+// 1,000 with clouds of 5,000 to 200,000 2.16 -> 1.46 ms.
 #include <algorithm>
 #include <atomic>
 #include <mutex>
@@ -338,6 +338,12 @@ __device__ __forceinline__ void collect(const QueryArgs& p, const PackedBox* __r
             g = local / cpg;
             mc = local - g * cpg;
         }
+        // places are turned by 0.618 cpg from tile to tile: a workgroup's waves take
+        // chunks half a grid or more apart, which would test the same part of the
+        // cloud where that is near a multiple of cpg (500 x 100,000 on 128^3 grids
+        // beside a table, 2,008 workgroups, cpg 143: 67 us, 53 with the turn)
+        mc += __umulhi((uint32_t)g * 2654435769u, (uint32_t)cpg);
+        if (mc >= cpg) mc -= cpg;
         const int i = (int)((uint32_t)g / (uint32_t)cgroups);
         const int cb = (int)((uint32_t)g - (uint32_t)i * (uint32_t)cgroups);
         const int c0 = t.c_lo + cb * 64, cn = min(t.c_n - cb * 64, 64);
@@ -477,17 +483,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_num_sgpr(80))) void q
     // run r is chunks given + r, given + r + nruns, ...: far apart, as the
     // chunks near a link, which cost the most, come together
     const int64_t given = lo + w.q_step;
-    const int64_t run = min((int64_t)kMaxRun, max((int64_t)kWavesPerBlock, (hi - given) / (kRunsPerBlock * n0)));
-    const int64_t nruns = (hi - given + run - 1) / run;
+    const int64_t run = DEAL ? min((int64_t)kMaxRun, max((int64_t)kWavesPerBlock, (hi - given) / (kRunsPerBlock * n0))) : 1;
+    const int64_t nruns = DEAL ? (hi - given + run - 1) / run : 0;
     if (threadIdx.x == 0) {
-        sh.listed = 0;
-        sh.tiles = 0;
-        sh.run = sh.taken = sh.open = 0;
-        sh.run_step = nruns;
-    }
-    if (threadIdx.x < (unsigned)p.L) {
-        const LinkGrid& lg = p.link[threadIdx.x];
-        sh.grid[threadIdx.x] = GridView{{lg.half[0], lg.half[1], lg.half[2]}, {lg.n[0], lg.n[1], lg.n[2]}, (int64_t)lg.offset};
+        sh.listed = sh.tiles = sh.open = 0;
+        if (DEAL) {
+            sh.run = sh.taken = 0;
+            sh.run_step = nruns;
+        }
     }
     __syncthreads();
 
@@ -516,10 +519,16 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_num_sgpr(80))) void q
     for (;;) {
         collect<DEAL>(p, blocks, groups, plan, w, lane, sh);
         if (w.has && lane == 0) atomicAdd(&sh.open, 1);
+        if (threadIdx.x < (unsigned)p.L) {
+            const LinkGrid& lg = p.link[threadIdx.x];
+            sh.grid[threadIdx.x] =
+                GridView{{lg.half[0], lg.half[1], lg.half[2]}, {lg.n[0], lg.n[1], lg.n[2]}, (int64_t)lg.offset};
+        }
         __syncthreads();
         const int nd = sh.listed, nt = sh.tiles;
         const bool left = sh.open > 0;
         const bool dry = DEAL && sh.taken >= sh.run;   // the run is through
+        if (nd == 0 && !left && (!DEAL || (dry && given >= hi))) break;
         int64_t next_q = hi;
         if (dry && given < hi && threadIdx.x == 0) {   // fetched while the list is worked off
             const int64_t n = atomicAdd(&reinterpret_cast<PlanEnd*>(&plan[p.K])->next[xcd], 1);
