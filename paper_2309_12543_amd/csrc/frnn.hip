@@ -9,15 +9,17 @@
 //   target_o = sum_b R[b][a] P_j[b],  P_j = (j + 1/2) / m - 1 per axis.
 //   Parameters: W1[32][9], b1[32], W2[3V][32], b2[3V] (FP32).
 //
-// Training step (all FP32, deterministic: no floating-point atomics), two
-// kernels:
-//   step kernel    every wave takes 16 outputs at a time: their values, their errors against the exact target,
-//                  dW2 and db2 and their Adam update, and the wave's share of
-//                  the loss and of dh = sum_o g_o W2[o] (g_o = sign(error) /
+// Training step (all FP32, deterministic: no floating-point atomics), three
+// kernels, every sum in the order of the rows or rotations it runs over (a step
+// from other bits, an ulp in a parameter, now and then turns a sign of the next
+// step's errors):
+//   step kernel    every wave takes blocks of 128 outputs, 16 at a time: their values, their errors
+//                  against the exact target, dW2 and db2 and their Adam update, the wave's share
+//                  of the loss and the block's of dh = sum_o g_o W2[o] (g_o = sign(error) /
 //                  (B 3V)), with every product on FP32 MFMA;
-//   finish kernel  a workgroup per hidden unit sums the shares in order:
-//                  loss, dh, then dW1, db1 through the ReLU and their Adam
-//                  update.
+//   slice kernel   sums the blocks' shares of dh in 64 interleaved slices;
+//   finish kernel  a workgroup per hidden unit sums the slices, then dW1, db1
+//                  through the ReLU and their Adam update; one more the loss.
 // Max-error kernel: max |f(R) - R^T P| over rotations and outputs (the
 // paper's 10^7-transformation test), one thread per output row, rotations
 // in tiles of 64 whose hidden layers are computed once per workgroup.
@@ -33,7 +35,8 @@ constexpr int kMaxB = 64;           // rotations per training step
 constexpr int kTile = 64;           // rotations per tile in the max-error kernel
 constexpr int kStepBlock = 256;     // threads of the step kernel's workgroups
 constexpr int kStepGroups = 512;    // its workgroups at most: two a CU
-constexpr int kFinishBlock = 1024;  // threads of the finish kernel's workgroups
+constexpr int kBlockUnits = 8;      // units of 16 outputs whose share of dh is summed by itself
+constexpr int kSlices = 64;         // first level of the sum of these shares
 
 struct Layout {
     int64_t V, O;                   // voxels, outputs (3 V)
@@ -71,14 +74,16 @@ struct TrainArgs {
     float* grad;             // [n]
     float* adam_m;           // [n], or NULL: the gradient only
     float* adam_v;
-    float* part_dh;          // [groups][kH][kMaxB], without the factor 1 / (B 3V)
+    float* part_dh;          // [blocks][kH][B]
+    float* slice_dh;         // [kSlices][kH][B]
     float* part_loss;        // [groups]
     float* loss_out;         // [1] or NULL
     Layout lay;
     int32_t m;
     int32_t B;
+    int32_t blocks;          // of 128 outputs
     int32_t groups;          // workgroups of the step kernel
-    float lr, b1, b2, eps, c1, c2;   // c1 = 1 / (1 - b1^t), c2 = 1 / (1 - b2^t)
+    float lr, b1, b2, eps, c1, c2, r1, r2;   // c1 = 1 - b1^t, c2 = 1 - b2^t, r1 = 1 / c1, r2 = 1 / c2
 };
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -88,10 +93,17 @@ typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 struct AdamState {
     float p, m, v;
 };
+// x / c, rounded as a division, from r = 1 / c rounded (Markstein): the quotient's
+// error is exact in one multiply-add, and adding it times r rounds once.
+// Where that is not finite the product stands.
+__device__ inline float divide(float x, float c, float r) {
+    const float q = x * r, t = fmaf(fmaf(-q, c, x), r, q);
+    return t == t ? t : q;
+}
 __device__ inline AdamState adam(const TrainArgs& a, AdamState s, float g) {
     const float m = fmaf(a.b1, s.m, (1.0f - a.b1) * g);
     const float v = fmaf(a.b2, s.v, (1.0f - a.b2) * g * g);
-    return {s.p - a.lr * (m * a.c1) / (sqrtf(v * a.c2) + a.eps), m, v};
+    return {s.p - a.lr * divide(m, a.c1, a.r1) / (sqrtf(divide(v, a.c2, a.r2)) + a.eps), m, v};
 }
 
 // Gradient g of parameter k, and its Adam update when there are moments.
@@ -116,39 +128,47 @@ __device__ inline float hidden(const TrainArgs& a, int u, const float* r) {
 __device__ inline float masked(float e, uint32_t mask) { return __uint_as_float(__float_as_uint(e) & mask); }
 __device__ inline float sign_of(float e) { return e > 0.0f ? 1.0f : (e < 0.0f ? -1.0f : 0.0f); }
 
-// What a wave reads of its 16 outputs (lane: c, g as below).
+// Row or column i of a product stands for output or rotation turned(i) of its
+// 16, so that the four values a lane holds (rows 4 g + r) are those of 4 r + g: the
+// next product takes one from each g, 4 r, 4 r + 1, .. in order.
+__device__ inline int turned(int i) { return 4 * (i & 3) + (i >> 2); }
+
+// What a wave reads of its 16 outputs (lane: c, g as below): for the products,
+// a unit ahead, and for Adam, at its unit's start.
 struct Unit {
-    float wo[kH / 4];         // W2[o][4 s + g], o the unit's output c
-    float wu[4][2];           // W2[output 4 g + r][16 ut + c]
-    f32x4 p[2], m[2], v[2];   // W2[o][16 ut + 4 g ..] and its moments
-    float bias, bias_m, bias_v;   // b2[o] and its moments
+    float wo[kH / 4];         // W2[o][4 s + g], o the unit's output turned(c)
+    float wu[4][2];           // W2[output 4 r + g][16 ut + c]
+    float bias;               // b2[o]
 };
-template <bool ADAM>
 __device__ inline Unit load_unit(const TrainArgs& a, int q, int c, int g) {
     const float* W2 = a.params + a.lay.w2;
-    const int64_t last = a.lay.O - 1, o = min((int64_t)16 * q + c, last);
+    const int64_t last = a.lay.O - 1, o = min((int64_t)16 * q + turned(c), last);
     Unit u;
 #pragma unroll
     for (int s = 0; s < kH / 4; ++s) u.wo[s] = W2[o * kH + 4 * s + g];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int64_t ok = min((int64_t)16 * q + 4 * g + r, last);
+        const int64_t ok = min((int64_t)16 * q + 4 * r + g, last);
 #pragma unroll
         for (int ut = 0; ut < 2; ++ut) u.wu[r][ut] = W2[ok * kH + 16 * ut + c];
     }
     u.bias = a.params[a.lay.b2 + o];
-    if (ADAM) {
-        u.bias_m = a.adam_m[a.lay.b2 + o];
-        u.bias_v = a.adam_v[a.lay.b2 + o];
-    }
+    return u;
+}
+struct UnitState {
+    f32x4 p[2], m[2], v[2];   // W2[o][16 ut + 4 g ..] and its moments
+    float bias_m, bias_v;
+};
+__device__ inline UnitState load_state(const TrainArgs& a, int64_t o, int g) {
+    UnitState u;
+    u.bias_m = a.adam_m[a.lay.b2 + o];
+    u.bias_v = a.adam_v[a.lay.b2 + o];
 #pragma unroll
     for (int ut = 0; ut < 2; ++ut) {
-        const int64_t k = o * kH + 16 * ut + 4 * g;
-        if (ADAM) {
-            u.p[ut] = *reinterpret_cast<const f32x4_any*>(W2 + k);
-            u.m[ut] = *reinterpret_cast<const f32x4_any*>(a.adam_m + a.lay.w2 + k);
-            u.v[ut] = *reinterpret_cast<const f32x4_any*>(a.adam_v + a.lay.w2 + k);
-        }
+        const int64_t k = a.lay.w2 + o * kH + 16 * ut + 4 * g;
+        u.p[ut] = *reinterpret_cast<const f32x4_any*>(a.params + k);
+        u.m[ut] = *reinterpret_cast<const f32x4_any*>(a.adam_m + k);
+        u.v[ut] = *reinterpret_cast<const f32x4_any*>(a.adam_v + k);
     }
     return u;
 }
@@ -162,32 +182,34 @@ __device__ inline Unit load_unit(const TrainArgs& a, int q, int c, int g) {
 // through LDS they are formed both ways, from the same registers: W H^T gives
 // lane l the outputs 4 g + r at rotation c, H W^T the output c at rotations
 // 4 g + r, each already in the next product's operand layout (its K index
-// permuted alike on both sides).  Signs stand for g; the factor 1 / (B 3V) is
-// applied to the sums.
-// Two waves a SIMD (244 registers) share 27 us of MFMA, about as much VALU and
+// permuted on both sides so that it runs in order: turned()).
+// Two waves a SIMD (256 registers) share 30 us of MFMA, about as much VALU and
 // the memory traffic (parameters and moments read and written, the gradient
 // written: 236 MB at 44^3 voxels, 42 us at the rate the separate Adam kernel
-// reached), which overlap in part: 80 us for a step of 64 rotations.  Separate
-// kernels for the hidden layer, the outputs (FP32 VALU, 107 us), two levels of
-// sums and Adam (42 us) took 154 us a step, the two kernels here 91 to 97.  At 3
-// and 4 waves a SIMD (spills) 105 to 184 us; 16 voxels of one component a unit
-// instead of 16 adjacent outputs, and 1,024 workgroups, measured the same; the
-// gradient's stores past the caches 1 to 7 us faster.
+// reached; 16 MB of shares), which overlap in part: 98 us for a step of 64
+// rotations, back to back with the slice and finish kernels 107 us.  Separate kernels for the
+// hidden layer, the outputs (FP32 VALU, 107 us), two levels of sums and Adam (42
+// us) took 154 us a step.  With dh summed over all of a wave's outputs, signs
+// for g and reciprocals for Adam's quotients it was 88 us, but in other bits:
+// in 3 of 20 second steps an error's sign differed.  At 3 and 4 waves a SIMD
+// (spills) 105 to 184 us; the gradient's stores past the caches 1 to 7 us faster.
 template <bool ADAM>
 __global__ __launch_bounds__(kStepBlock, 2) void frnn_step_kernel(TrainArgs a) {
     constexpr int kTilesB = kMaxB / 16, kSteps = kH / 4, kStride = kH + 1;
     __shared__ float hs[kMaxB][kStride];                // hidden layer, 0 past the batch
-    __shared__ __align__(16) float rt[9][kMaxB];        // rotations, transposed
-    __shared__ float share[kH * kMaxB];
+    __shared__ __align__(16) float rt[9][kMaxB];        // rotations, transposed; place 16 bt + i holds 16 bt + turned(i)
     __shared__ float share_loss[kStepBlock / 64];
     const int tid = threadIdx.x, lane = tid & 63, c = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int B = a.B;
     const int O = (int)a.lay.O, w = 2 * a.m;
     const int units = (O + 15) / 16;
-    int q = blockIdx.x * (kStepBlock / 64) + wave;
-    Unit u = load_unit<ADAM>(a, min(q, units - 1), c, g);   // on its way during the hidden layer
-    for (int k = tid; k < 9 * kMaxB; k += kStepBlock) rt[k / kMaxB][k % kMaxB] = k % kMaxB < B ? a.R[k % kMaxB * 9 + k / kMaxB] : 0.0f;
+    int blk = blockIdx.x * (kStepBlock / 64) + wave;
+    Unit u = load_unit(a, min(kBlockUnits * blk, units - 1), c, g);   // on its way during the hidden layer
+    for (int k = tid; k < 9 * kMaxB; k += kStepBlock) {
+        const int b = k % kMaxB / 16 * 16 + turned(k % 16);
+        rt[k / kMaxB][k % kMaxB] = b < B ? a.R[b * 9 + k / kMaxB] : 0.0f;
+    }
     __syncthreads();
     {
         // thread t: unit t mod 32 at rotations t / 32, t / 32 + 8, ..
@@ -200,25 +222,31 @@ __global__ __launch_bounds__(kStepBlock, 2) void frnn_step_kernel(TrainArgs a) {
         for (int b = tid / kH; b < kMaxB; b += kStepBlock / kH) {
             float acc = b1;
 #pragma unroll
-            for (int k = 0; k < 9; ++k) acc = fmaf(w1[k], rt[k][b], acc);
+            for (int k = 0; k < 9; ++k) acc = fmaf(w1[k], rt[k][b / 16 * 16 + turned(b % 16)], acc);
             hs[b][u] = b < B ? fmaxf(acc, 0.0f) : 0.0f;
         }
     }
     __syncthreads();
-    f32x4 dh[2][kTilesB];   // units 16 ut + 4 g + r, rotation 16 bt + c
-#pragma unroll
-    for (int bt = 0; bt < kTilesB; ++bt) dh[0][bt] = dh[1][bt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    f32x4 dh[2][kTilesB];   // units 16 ut + 4 g + r, rotation 16 bt + turned(c)
     const float scale = 1.0f / ((float)B * (float)a.lay.O);
     const float inv = 1.0f / (float)a.m;
     float loss = 0.0f;
     const int stride = gridDim.x * (kStepBlock / 64);
-    for (; q < units; q += stride) {
+    for (; blk < a.blocks; blk += stride)
+    for (int q = kBlockUnits * blk; q < min(kBlockUnits * (blk + 1), units); ++q) {
+        if (q == kBlockUnits * blk) {
+#pragma unroll
+            for (int bt = 0; bt < kTilesB; ++bt) dh[0][bt] = dh[1][bt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        }
         // the next unit's rows are on their way while this one's are used
-        const Unit next = load_unit<ADAM>(a, min(q + stride, units - 1), c, g);
-        // this lane's output with the outputs along columns or rows (c), and
-        // with them along K (4 g + r); past the last one that stands in, its
+        const bool last = q + 1 == min(kBlockUnits * (blk + 1), units);
+        UnitState st;
+        if (ADAM) st = load_state(a, min((int64_t)16 * q + turned(c), a.lay.O - 1), g);
+        const Unit next = load_unit(a, min(last ? kBlockUnits * (blk + stride) : q + 1, units - 1), c, g);
+        // this lane's output with the outputs along columns or rows (turned(c)),
+        // and with them along K (4 r + g); past the last one that stands in, its
         // signs 0 where sums are formed
-        const int of = 16 * q + c, o = min(of, O - 1), j = o / 3, comp = o - 3 * j;
+        const int of = 16 * q + turned(c), o = min(of, O - 1), j = o / 3, comp = o - 3 * j;
         const uint32_t live = of < O ? ~0u : 0u;
         const float bias = u.bias;
         const int jz = j / (w * w), jy = (j - jz * w * w) / w, jx = j - (jz * w + jy) * w;
@@ -229,22 +257,21 @@ __global__ __launch_bounds__(kStepBlock, 2) void frnn_step_kernel(TrainArgs a) {
         int comp_k[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            live_k[r] = 16 * q + 4 * g + r < O ? ~0u : 0u;
-            comp_k[r] = (uint32_t)(16 * q + 4 * g + r) % 3u;
+            live_k[r] = 16 * q + 4 * r + g < O ? ~0u : 0u;
+            comp_k[r] = (uint32_t)(16 * q + 4 * r + g) % 3u;
             bias_k[r] = __shfl(bias, 4 * g + r, 64);
             px_k[r] = __shfl(px, 4 * g + r, 64);
             py_k[r] = __shfl(py, 4 * g + r, 64);
             pz_k[r] = __shfl(pz, 4 * g + r, 64);
         }
-        f32x4 dw[2] = {};   // dW2[o][16 ut + 4 g + r] / scale
-        float db = 0.0f;
+        f32x4 dw[3] = {};   // dW2[o][16 ut + 4 g + r]; db2[o] in every row
         // the outputs of rotations 16 bt .., rotations along columns (y) and along K (z)
         auto outputs = [&](int bt, f32x4& y, f32x4& z) {
             y = bias_k;
             z = f32x4{bias, bias, bias, bias};
 #pragma unroll
             for (int s = 0; s < kSteps; ++s) {
-                const float h = hs[16 * bt + c][4 * s + g];
+                const float h = hs[16 * bt + turned(c)][4 * s + g];
                 y = __builtin_amdgcn_mfma_f32_16x16x4f32(u.wo[s], h, y, 0, 0, 0);
                 z = __builtin_amdgcn_mfma_f32_16x16x4f32(h, u.wo[s], z, 0, 0, 0);
             }
@@ -256,7 +283,7 @@ __global__ __launch_bounds__(kStepBlock, 2) void frnn_step_kernel(TrainArgs a) {
             if (16 * bt >= B) break;
             // the next rotations' products run under this one's errors
             if (bt + 1 < kTilesB) outputs(bt + 1, yn, zn);
-            const int b = 16 * bt + c;
+            const int at = 16 * bt + c, b = 16 * bt + turned(c);
             const f32x4 r0 = *reinterpret_cast<const f32x4*>(&rt[comp][16 * bt + 4 * g]);
             const f32x4 r1 = *reinterpret_cast<const f32x4*>(&rt[3 + comp][16 * bt + 4 * g]);
             const f32x4 r2 = *reinterpret_cast<const f32x4*>(&rt[6 + comp][16 * bt + 4 * g]);
@@ -264,26 +291,25 @@ __global__ __launch_bounds__(kStepBlock, 2) void frnn_step_kernel(TrainArgs a) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 // outputs along K: dh
-                const float ty = fmaf(rt[comp_k[r]][b], px_k[r], fmaf(rt[3 + comp_k[r]][b], py_k[r], rt[6 + comp_k[r]][b] * pz_k[r]));
-                const float sy = sign_of(masked(y[r] - ty, live_k[r] & in_c));
+                const float ty = fmaf(rt[comp_k[r]][at], px_k[r], fmaf(rt[3 + comp_k[r]][at], py_k[r], rt[6 + comp_k[r]][at] * pz_k[r]));
+                const float gy = sign_of(masked(y[r] - ty, live_k[r] & in_c)) * scale;
                 // rotations along K: the loss, dW2 and db2
-                const uint32_t in_k = 16 * bt + 4 * g + r < B ? ~0u : 0u;
+                const uint32_t in_k = 16 * bt + 4 * r + g < B ? ~0u : 0u;
                 const float tz = fmaf(r0[r], px, fmaf(r1[r], py, r2[r] * pz));
                 const float e = masked(z[r] - tz, in_k);
                 loss += fabsf(masked(e, live));
-                const float sz = sign_of(e);
-                db += sz;
+                const float gz = sign_of(e) * scale;
+                dw[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(1.0f, gz, dw[2], 0, 0, 0);
 #pragma unroll
                 for (int ut = 0; ut < 2; ++ut) {
-                    dh[ut][bt] = __builtin_amdgcn_mfma_f32_16x16x4f32(u.wu[r][ut], sy, dh[ut][bt], 0, 0, 0);
-                    dw[ut] = __builtin_amdgcn_mfma_f32_16x16x4f32(hs[16 * bt + 4 * g + r][16 * ut + c], sz, dw[ut], 0, 0, 0);
+                    dh[ut][bt] = __builtin_amdgcn_mfma_f32_16x16x4f32(u.wu[r][ut], gy, dh[ut][bt], 0, 0, 0);
+                    dw[ut] = __builtin_amdgcn_mfma_f32_16x16x4f32(hs[16 * bt + 4 * r + g][16 * ut + c], gz, dw[ut], 0, 0, 0);
                 }
             }
             y = yn;
             z = zn;
         }
-        db += __shfl_xor(db, 16, 64);
-        db += __shfl_xor(db, 32, 64);
+        const float db = dw[2][0];
         // no branches from here to the next unit: a wait for its rows then only
         // counts the stores behind them instead of waiting for those too
         // (lanes past the block hold the last voxel's values, and the four
@@ -291,50 +317,47 @@ __global__ __launch_bounds__(kStepBlock, 2) void frnn_step_kernel(TrainArgs a) {
 #pragma unroll
         for (int ut = 0; ut < 2; ++ut) {
             const int64_t k = a.lay.w2 + (int64_t)o * kH + 16 * ut + 4 * g;
-            const f32x4 gr = dw[ut] * scale;
+            const f32x4 gr = dw[ut];
             __builtin_nontemporal_store(gr, reinterpret_cast<f32x4_any*>(a.grad + k));
             if (ADAM) {
                 f32x4 p4, m4, v4;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const AdamState st = adam(a, {u.p[ut][r], u.m[ut][r], u.v[ut][r]}, gr[r]);
-                    p4[r] = st.p;
-                    m4[r] = st.m;
-                    v4[r] = st.v;
+                    const AdamState x = adam(a, {st.p[ut][r], st.m[ut][r], st.v[ut][r]}, gr[r]);
+                    p4[r] = x.p;
+                    m4[r] = x.m;
+                    v4[r] = x.v;
                 }
                 *reinterpret_cast<f32x4_any*>(a.params + k) = p4;
                 *reinterpret_cast<f32x4_any*>(a.adam_m + k) = m4;
                 *reinterpret_cast<f32x4_any*>(a.adam_v + k) = v4;
             }
         }
-        a.grad[a.lay.b2 + o] = db * scale;
+        a.grad[a.lay.b2 + o] = db;
         if (ADAM) {
-            const AdamState st = adam(a, {u.bias, u.bias_m, u.bias_v}, db * scale);
-            a.params[a.lay.b2 + o] = st.p;
-            a.adam_m[a.lay.b2 + o] = st.m;
-            a.adam_v[a.lay.b2 + o] = st.v;
+            const AdamState x = adam(a, {u.bias, st.bias_m, st.bias_v}, db);
+            a.params[a.lay.b2 + o] = x.p;
+            a.adam_m[a.lay.b2 + o] = x.m;
+            a.adam_v[a.lay.b2 + o] = x.v;
         }
         u = next;
-    }
-    // the workgroup's shares, its waves in order
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) loss += __shfl_xor(loss, off, 64);
-    if (lane == 0) share_loss[wave] = loss;
-    for (int v = 0; v < kStepBlock / 64; ++v) {
-        if (wave == v) {
+        if (last) {
+            // the block's share of dh
 #pragma unroll
             for (int ut = 0; ut < 2; ++ut)
 #pragma unroll
                 for (int bt = 0; bt < kTilesB; ++bt)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        float& t = share[(16 * ut + 4 * g + r) * kMaxB + 16 * bt + c];
-                        t = v == 0 ? dh[ut][bt][r] : t + dh[ut][bt][r];
+                        const int b = 16 * bt + turned(c);
+                        if (b < B) a.part_dh[((int64_t)blk * kH + 16 * ut + 4 * g + r) * B + b] = dh[ut][bt][r];
                     }
         }
-        __syncthreads();
     }
-    for (int k = tid; k < kH * kMaxB; k += kStepBlock) a.part_dh[(int64_t)blockIdx.x * kH * kMaxB + k] = share[k];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) loss += __shfl_xor(loss, off, 64);
+    if (lane == 0) share_loss[wave] = loss;
+    __syncthreads();
     if (tid == 0) {
         float s = 0.0f;
         for (int v = 0; v < kStepBlock / 64; ++v) s += share_loss[v];
@@ -342,40 +365,44 @@ __global__ __launch_bounds__(kStepBlock, 2) void frnn_step_kernel(TrainArgs a) {
     }
 }
 
-// The finish kernel: workgroup u sums dh of hidden unit u over the step
-// kernel's workgroups (16 interleaved runs, each in order, then the runs in
-// order) and forms dW1[u], db1[u] through the ReLU; workgroup 0 also the loss.
-__global__ __launch_bounds__(kFinishBlock) void frnn_finish_kernel(TrainArgs a) {
-    constexpr int kRuns = kFinishBlock / kMaxB;
-    static_assert(kMaxB == 64, "a lane per rotation");
-    __shared__ float run[kRuns][kMaxB];
-    const int u = blockIdx.x, b = threadIdx.x & 63, part = threadIdx.x >> 6;
+// First level of the sum of the blocks' shares of dh: slice sl sums blocks sl,
+// sl + kSlices, .. in order.
+__global__ __launch_bounds__(256) void frnn_slice_kernel(TrainArgs a) {
+    const int sl = blockIdx.y, n = a.B * kH, p = blockIdx.x * 256 + threadIdx.x;
+    if (p >= n) return;
     float s = 0.0f;
 #pragma unroll 8
-    for (int k = part; k < a.groups; k += kRuns) s += a.part_dh[((int64_t)k * kH + u) * kMaxB + b];
-    run[part][b] = s;
-    __syncthreads();
-    const float scale = 1.0f / ((float)a.B * (float)a.lay.O);
-    if (part == 0) {
-        float d = 0.0f;
-        for (int k = 0; k < kRuns; ++k) d += run[k][b];
-        const float* r = a.R + min(b, a.B - 1) * 9;
-        d = b < a.B && hidden(a, u, r) > 0.0f ? d * scale : 0.0f;
-        float mine = 0.0f;   // lane k < 9: dW1[u][k], lane 9: db1[u]
-#pragma unroll
-        for (int k = 0; k < 10; ++k) {
-            float t = k < 9 ? d * r[k] : d;
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
-            if (b == k) mine = t;
-        }
-        if (b < 10) update(a, b < 9 ? a.lay.w1 + u * 9 + b : a.lay.b1 + u, mine);
-    } else if (part == 1 && u == 0 && a.loss_out) {
+    for (int k = sl; k < a.blocks; k += kSlices) s += a.part_dh[(int64_t)k * n + p];
+    a.slice_dh[(int64_t)sl * n + p] = s;
+}
+
+// The finish kernel: workgroup u < kH sums dh of hidden unit u over the slices
+// in order and forms dW1[u], db1[u] through the ReLU, the rotations in order;
+// workgroup kH sums the loss.
+__global__ __launch_bounds__(64) void frnn_finish_kernel(TrainArgs a) {
+    static_assert(kMaxB == 64, "a lane per rotation");
+    __shared__ float dz[kMaxB];
+    __shared__ float rs[kMaxB * 9];
+    const int u = blockIdx.x, b = threadIdx.x;
+    if (u == kH) {
         float l = 0.0f;
         for (int k = b; k < a.groups; k += 64) l += a.part_loss[k];
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off, 64);
-        if (b == 0) a.loss_out[0] = l / ((float)a.B * (float)a.lay.O);
+        if (b == 0 && a.loss_out) a.loss_out[0] = l / ((float)a.B * (float)a.lay.O);
+        return;
+    }
+    const int n = a.B * kH, bb = min(b, a.B - 1);
+    for (int k = b; k < a.B * 9; k += 64) rs[k] = a.R[k];
+    float s = 0.0f;
+#pragma unroll
+    for (int sl = 0; sl < kSlices; ++sl) s += a.slice_dh[(int64_t)sl * n + u * a.B + bb];
+    dz[b] = hidden(a, u, a.R + bb * 9) > 0.0f ? s : 0.0f;
+    __syncthreads();
+    if (b < 10) {
+        float t = 0.0f;
+        for (int k = 0; k < a.B; ++k) t = b < 9 ? fmaf(dz[k], rs[k * 9 + b], t) : t + dz[k];
+        update(a, b < 9 ? a.lay.w1 + u * 9 + b : a.lay.b1 + u, t);
     }
 }
 
@@ -442,11 +469,12 @@ int check_m(const char* who, int32_t m) {
 
 size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 
-// Workgroups of the step kernel: a wave per 16 voxels and component, two
-// workgroups a CU at most.
+// Blocks of 128 outputs, and workgroups of the step kernel: a wave per block,
+// two workgroups a CU at most.
+int64_t step_blocks(const Layout& l) { return (l.O + 16 * kBlockUnits - 1) / (16 * kBlockUnits); }
 int64_t step_groups(const Layout& l) {
-    const int64_t units = (l.O + 15) / 16, waves = kStepBlock / 64;
-    return std::min<int64_t>(kStepGroups, (units + waves - 1) / waves);
+    const int64_t waves = kStepBlock / 64;
+    return std::min<int64_t>(kStepGroups, (step_blocks(l) + waves - 1) / waves);
 }
 
 }  // namespace
@@ -468,8 +496,9 @@ LSDF_API int lsdf_frnn_train_workspace_size(int32_t m, int32_t B, size_t* bytes)
     if (rc != LSDF_OK) return rc;
     if (B < 1 || B > kMaxB) return fail(LSDF_E_SHAPE, "frnn_train_workspace_size: B = %d out of [1, %d]", (int)B, kMaxB);
     if (!bytes) return fail(LSDF_E_INVALID_ARG, "frnn_train_workspace_size: bytes is NULL");
-    const int64_t groups = step_groups(layout(m));
-    *bytes = align256((size_t)groups * kH * kMaxB * 4) + align256((size_t)groups * 4);
+    const Layout l = layout(m);
+    *bytes = align256((size_t)step_blocks(l) * kH * B * 4) + align256((size_t)kSlices * kH * B * 4) +
+             align256((size_t)step_groups(l) * 4);
     return LSDF_OK;
 }
 
@@ -502,21 +531,30 @@ LSDF_API int lsdf_frnn_train_step(float* params, float* adam_m, float* adam_v, i
     a.m = m;
     a.B = B;
     a.groups = (int32_t)step_groups(a.lay);
-    a.part_dh = static_cast<float*>(workspace);
-    a.part_loss = reinterpret_cast<float*>(static_cast<char*>(workspace) + align256((size_t)a.groups * kH * kMaxB * 4));
+    a.blocks = (int32_t)step_blocks(a.lay);
+    char* ws = static_cast<char*>(workspace);
+    a.part_dh = reinterpret_cast<float*>(ws);
+    ws += align256((size_t)a.blocks * kH * B * 4);
+    a.slice_dh = reinterpret_cast<float*>(ws);
+    ws += align256((size_t)kSlices * kH * B * 4);
+    a.part_loss = reinterpret_cast<float*>(ws);
     a.lr = lr;
     a.b1 = beta1;
     a.b2 = beta2;
     a.eps = eps;
-    a.c1 = (float)(1.0 / (1.0 - std::pow((double)beta1, (double)t)));
-    a.c2 = (float)(1.0 / (1.0 - std::pow((double)beta2, (double)t)));
+    a.c1 = (float)(1.0 - std::pow((double)beta1, (double)t));
+    a.c2 = (float)(1.0 - std::pow((double)beta2, (double)t));
+    a.r1 = (float)(1.0 / (double)a.c1);
+    a.r2 = (float)(1.0 / (double)a.c2);
     hipStream_t s = as_stream(stream);
     if (adam_m)
         hipLaunchKernelGGL(frnn_step_kernel<true>, dim3((unsigned)a.groups), dim3(kStepBlock), 0, s, a);
     else
         hipLaunchKernelGGL(frnn_step_kernel<false>, dim3((unsigned)a.groups), dim3(kStepBlock), 0, s, a);
     if ((rc = check_launch("frnn_train_step (step)")) != LSDF_OK) return rc;
-    hipLaunchKernelGGL(frnn_finish_kernel, dim3(kH), dim3(kFinishBlock), 0, s, a);
+    hipLaunchKernelGGL(frnn_slice_kernel, dim3((unsigned)((B * kH + 255) / 256), kSlices), dim3(256), 0, s, a);
+    if ((rc = check_launch("frnn_train_step (slices)")) != LSDF_OK) return rc;
+    hipLaunchKernelGGL(frnn_finish_kernel, dim3(kH + 1), dim3(64), 0, s, a);
     return check_launch("frnn_train_step (finish)");
 }
 
