@@ -13,7 +13,8 @@
 // kernels, every sum in the order of the rows or rotations it runs over (a step
 // from other bits, an ulp in a parameter, now and then turns a sign of the next
 // step's errors):
-//   step kernel    every wave takes blocks of 128 outputs, 16 at a time: their values, their errors
+//   step kernel    (from 512 blocks of 128 outputs on; below that the row kernel, one thread per
+//                  output, and an Adam kernel at the end) every wave takes blocks of 128 outputs, 16 at a time: their values, their errors
 //                  against the exact target, dW2 and db2 and their Adam update, the wave's share
 //                  of the loss and the block's of dh = sum_o g_o W2[o] (g_o = sign(error) /
 //                  (B 3V)), with every product on FP32 MFMA;
@@ -30,11 +31,12 @@
 namespace {
 
 constexpr int kH = LSDF_FRNN_HIDDEN;
-constexpr int kRows = 128;          // output rows per workgroup of the max-error kernel
+constexpr int kRows = 128;          // output rows per workgroup of the row and max-error kernels
 constexpr int kMaxB = 64;           // rotations per training step
 constexpr int kTile = 64;           // rotations per tile in the max-error kernel
 constexpr int kStepBlock = 256;     // threads of the step kernel's workgroups
 constexpr int kStepGroups = 512;    // its workgroups at most: two a CU
+constexpr int kRowBlocks = 512;     // with fewer blocks of 128 outputs the row kernel takes the step (its comment)
 constexpr int kBlockUnits = 8;      // units of 16 outputs whose share of dh is summed by itself
 constexpr int kSlices = 64;         // first level of the sum of these shares
 
@@ -76,13 +78,13 @@ struct TrainArgs {
     float* adam_v;
     float* part_dh;          // [blocks][kH][B]
     float* slice_dh;         // [kSlices][kH][B]
-    float* part_loss;        // [groups]
+    float* part_loss;        // [groups], or [blocks] of the row kernel
     float* loss_out;         // [1] or NULL
     Layout lay;
     int32_t m;
     int32_t B;
     int32_t blocks;          // of 128 outputs
-    int32_t groups;          // workgroups of the step kernel
+    int32_t groups;          // workgroups of the step kernel, or of the row kernel
     float lr, b1, b2, eps, c1, c2, r1, r2;   // c1 = 1 - b1^t, c2 = 1 - b2^t, r1 = 1 / c1, r2 = 1 / c2
 };
 
@@ -365,6 +367,132 @@ __global__ __launch_bounds__(kStepBlock, 2) void frnn_step_kernel(TrainArgs a) {
     }
 }
 
+// The step of a network of fewer than 512 blocks of 128 outputs: one thread per
+// output row, a workgroup per block, on FP32 VALU; the step kernel's sums in the
+// step kernel's order. Latency bounds both. A wave of the step kernel takes the
+// 8 units of a block one after another, a chain of 29 to 61 us where there are
+// too few blocks to hide it; here two waves share a block and Adam follows as a
+// kernel of its own, whose traffic costs more than the chain from 512 blocks on.
+// A training step (us, step kernel and this one) at 1, 16 and 64 rotations:
+//    5,184 outputs (12^3)   37, 39, 62    21, 26, 42
+//   24,000 outputs (20^3)   39, 41, 64    25, 31, 49
+//   41,472 outputs (24^3)   41, 42, 66    33, 39, 58
+//   65,856 outputs (28^3)   41, 43, 68    41, 48, 68 (hidden layer in a launch of its own)
+//   98,304 outputs (32^3)   43, 45, 71    50, 55, 75 (so too)
+__global__ __launch_bounds__(kRows) void frnn_row_kernel(TrainArgs a) {
+    static_assert(kRows == (kMaxB / 4) * (kH / 4), "one 4 x 4 tile of dh per thread");
+    __shared__ float hs[kMaxB][kH];
+    __shared__ float rs[kMaxB][9];
+    // sign of g[row][b] (g is +scale, -scale or 0), transposed: rows contiguous,
+    // the pad staggers the rotations over the banks
+    __shared__ __align__(16) int8_t sgT[kMaxB][kRows + 4];
+    __shared__ float4 ws4[kRows][kH / 4];       // W2 rows in 16 B chunks, chunk c stored at c ^ (row mod 8)
+    __shared__ float ls[kRows / 64];
+    const int tid = threadIdx.x;
+    const int B = a.B;
+    for (int k = tid; k < B * kH; k += kRows) hs[k / kH][k % kH] = fmaxf(hidden(a, k % kH, a.R + k / kH * 9), 0.0f);
+    for (int k = tid; k < B * 9; k += kRows) rs[k / 9][k % 9] = a.R[k];
+    const int64_t o = (int64_t)blockIdx.x * kRows + tid;
+    const bool live = o < a.lay.O;
+    float wrow[kH];
+    const float* W2 = a.params + a.lay.w2;
+#pragma unroll
+    for (int u = 0; u < kH; ++u) wrow[u] = live ? W2[o * kH + u] : 0.0f;
+#pragma unroll
+    for (int c = 0; c < kH / 4; ++c)
+        ws4[tid][c ^ (tid & 7)] = make_float4(wrow[4 * c], wrow[4 * c + 1], wrow[4 * c + 2], wrow[4 * c + 3]);
+    const float bias = live ? a.params[a.lay.b2 + o] : 0.0f;
+    // this row's block voxel and component (the target is R^T P_j, component a)
+    int comp = 0;
+    float px = 0.0f, py = 0.0f, pz = 0.0f;
+    if (live) {
+        const int64_t j = o / 3;
+        comp = (int)(o - 3 * j);
+        const int w = 2 * a.m;
+        const int jx = (int)(j % w), jy = (int)((j / w) % w), jz = (int)(j / ((int64_t)w * w));
+        const float inv = 1.0f / (float)a.m;
+        px = fmaf((float)jx + 0.5f, inv, -1.0f);
+        py = fmaf((float)jy + 0.5f, inv, -1.0f);
+        pz = fmaf((float)jz + 0.5f, inv, -1.0f);
+    }
+    __syncthreads();
+    const float scale = 1.0f / ((float)B * (float)a.lay.O);
+    float dw[kH];
+#pragma unroll
+    for (int u = 0; u < kH; ++u) dw[u] = 0.0f;
+    float db = 0.0f, loss = 0.0f;
+    for (int b = 0; b < B; ++b) {
+        float y = bias;
+#pragma unroll
+        for (int u = 0; u < kH; ++u) y = fmaf(wrow[u], hs[b][u], y);
+        float g = 0.0f;
+        int8_t sg = 0;
+        if (live) {
+            const float* r = rs[b];
+            const float t = fmaf(r[comp], px, fmaf(r[3 + comp], py, r[6 + comp] * pz));
+            const float e = y - t;
+            loss += fabsf(e);
+            sg = e > 0.0f ? 1 : (e < 0.0f ? -1 : 0);
+            g = e > 0.0f ? scale : (e < 0.0f ? -scale : 0.0f);
+        }
+        sgT[b][tid] = sg;
+#pragma unroll
+        for (int u = 0; u < kH; ++u) dw[u] = fmaf(g, hs[b][u], dw[u]);
+        db += g;
+    }
+    if (live) {
+        float* gW2 = a.grad + a.lay.w2 + o * kH;
+#pragma unroll
+        for (int u = 0; u < kH; ++u) gW2[u] = dw[u];
+        a.grad[a.lay.b2 + o] = db;
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) loss += __shfl_xor(loss, off, 64);
+    if ((tid & 63) == 0) ls[tid >> 6] = loss;
+    __syncthreads();
+    // this workgroup's share of dh[b][u] = sum over its rows of g W2[o][u],
+    // rows in order; thread t holds b = 4 (t / 8) + i, u = 4 (t mod 8) + k
+    const int bt = tid >> 3, ut = tid & 7;
+    float acc[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc[i][k] = 0.0f;
+    for (int r0 = 0; r0 < kRows; r0 += 4) {
+        uint32_t sg4[4];   // the signs of rows r0 .. r0 + 3, one byte each
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sg4[i] = *reinterpret_cast<const uint32_t*>(&sgT[4 * bt + i][r0]);
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr) {
+            const float4 wv = ws4[r0 + rr][ut ^ ((r0 + rr) & 7)];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                // g itself, rebuilt exactly from its sign
+                const float gi = (float)(int8_t)(sg4[i] >> (8 * rr)) * scale;
+                acc[i][0] = fmaf(gi, wv.x, acc[i][0]);
+                acc[i][1] = fmaf(gi, wv.y, acc[i][1]);
+                acc[i][2] = fmaf(gi, wv.z, acc[i][2]);
+                acc[i][3] = fmaf(gi, wv.w, acc[i][3]);
+            }
+        }
+    }
+    float* pd = a.part_dh + (int64_t)blockIdx.x * kH * B;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int b = 4 * bt + i;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (b < B) pd[(4 * ut + k) * B + b] = acc[i][k];
+    }
+    if (tid == 0) a.part_loss[blockIdx.x] = ls[0] + ls[1];
+}
+
+// Adam of the output layer, after the row kernel.
+__global__ __launch_bounds__(256) void frnn_adam_kernel(TrainArgs a) {
+    const int64_t k = a.lay.w2 + (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (k < a.lay.n) update(a, k, a.grad[k]);
+}
+
 // First level of the sum of the blocks' shares of dh: slice sl sums blocks sl,
 // sl + kSlices, .. in order.
 __global__ __launch_bounds__(256) void frnn_slice_kernel(TrainArgs a) {
@@ -498,7 +626,7 @@ LSDF_API int lsdf_frnn_train_workspace_size(int32_t m, int32_t B, size_t* bytes)
     if (!bytes) return fail(LSDF_E_INVALID_ARG, "frnn_train_workspace_size: bytes is NULL");
     const Layout l = layout(m);
     *bytes = align256((size_t)step_blocks(l) * kH * B * 4) + align256((size_t)kSlices * kH * B * 4) +
-             align256((size_t)step_groups(l) * 4);
+             align256((size_t)step_blocks(l) * 4);
     return LSDF_OK;
 }
 
@@ -547,15 +675,23 @@ LSDF_API int lsdf_frnn_train_step(float* params, float* adam_m, float* adam_v, i
     a.r1 = (float)(1.0 / (double)a.c1);
     a.r2 = (float)(1.0 / (double)a.c2);
     hipStream_t s = as_stream(stream);
-    if (adam_m)
+    static_assert(kRows == 16 * kBlockUnits, "a row workgroup's share is a block's");
+    const bool rows = a.blocks < kRowBlocks;
+    if (rows) {
+        a.groups = a.blocks;
+        hipLaunchKernelGGL(frnn_row_kernel, dim3((unsigned)a.blocks), dim3(kRows), 0, s, a);
+    } else if (adam_m) {
         hipLaunchKernelGGL(frnn_step_kernel<true>, dim3((unsigned)a.groups), dim3(kStepBlock), 0, s, a);
-    else
+    } else {
         hipLaunchKernelGGL(frnn_step_kernel<false>, dim3((unsigned)a.groups), dim3(kStepBlock), 0, s, a);
+    }
     if ((rc = check_launch("frnn_train_step (step)")) != LSDF_OK) return rc;
     hipLaunchKernelGGL(frnn_slice_kernel, dim3((unsigned)((B * kH + 255) / 256), kSlices), dim3(256), 0, s, a);
     if ((rc = check_launch("frnn_train_step (slices)")) != LSDF_OK) return rc;
     hipLaunchKernelGGL(frnn_finish_kernel, dim3(kH + 1), dim3(64), 0, s, a);
-    return check_launch("frnn_train_step (finish)");
+    if ((rc = check_launch("frnn_train_step (finish)")) != LSDF_OK || !rows || !adam_m) return rc;
+    hipLaunchKernelGGL(frnn_adam_kernel, dim3((unsigned)((a.lay.n - a.lay.w2 + 255) / 256)), dim3(256), 0, s, a);
+    return check_launch("frnn_train_step (adam)");
 }
 
 LSDF_API int lsdf_frnn_max_error(const float* params, int32_t m, const float* R, int64_t N, float* out_max,
