@@ -104,26 +104,35 @@ __device__ float solid_angle(V3 p, V3 a, V3 b, V3 c) {
     return 2.0f * atan2f(det, den);
 }
 
+// u x v in the plane, within 2 units in the last place whatever cancels (Kahan's
+// difference of products): its sign, and where it is 0, are exact.
+__device__ inline double cross2(double ux, double uy, double vx, double vy) {
+    const double w = uy * vx;
+    return fma(ux, vy, -w) + fma(-uy, vx, w);
+}
+
 // Crossings of triangle (a, b, c) by the ray from p along +z, signed: +1
 // leaving through it, -1 entering.  The planar winding of the triangle's
-// shadow around p uses the half-open rule and an edge term that only changes
-// sign when its ends are swapped, so two triangles that share an edge agree
-// on it whatever the rounding, and the crossings of a closed part add up to
-// its winding number; only the side of the triangle's plane can round the
-// wrong way, within rounding of the surface itself.
-__device__ inline float crossing(V3 p, V3 a, V3 b, V3 c) {
-    const V3 A = sub(a, p), B = sub(b, p), C = sub(c, p);
-    const float la = A.y <= 0.0f ? 1.0f : 0.0f, lb = B.y <= 0.0f ? 1.0f : 0.0f, lc = C.y <= 0.0f ? 1.0f : 0.0f;
+// shadow around p uses the half-open rule and an edge term whose sign is exact,
+// so two triangles that share an edge agree on it and the crossings of a closed
+// part add up to its winding number.  Where it is not 0 the three terms are of
+// one sign, and the height at which the ray crosses the triangle's plane is the
+// corners' mean weighted by them, a sum without cancellation among the weights:
+// however thin the shadow, only within rounding of the surface itself can its
+// sign be wrong.  (In FP32 the shadow of a vertical triangle is a sliver of
+// rounding width, in which a point level with the triangle but beside it was
+// called inside the part, by up to 15 cm on a wedge's end.)  The differences
+// round in double at most, alike for every triangle at a vertex.
+__device__ inline int crossing(V3 p, V3 a, V3 b, V3 c) {
+    const double px = p.x, py = p.y, pz = p.z;
+    const double ax = a.x - px, ay = a.y - py, bx = b.x - px, by = b.y - py, cx = c.x - px, cy = c.y - py;
+    const double ab = cross2(ax, ay, bx, by), bc = cross2(bx, by, cx, cy), ca = cross2(cx, cy, ax, ay);
+    const int la = ay <= 0.0, lb = by <= 0.0, lc = cy <= 0.0;
     // +1 for an edge that passes p on its right going up, -1 going down
-    auto edge = [](const V3& u, const V3& v, float turn) {
-        const float e = u.x * v.y - u.y * v.x;
-        return e * turn > 0.0f ? turn : 0.0f;
-    };
-    float w = edge(A, B, la - lb) + edge(B, C, lb - lc) + edge(C, A, lc - la);
-    const float side = dot(cross(sub(B, A), sub(C, A)), A);   // > 0: p is behind the triangle
-    const float above = fminf(A.z, fminf(B.z, C.z)) > 0.0f ? 1.0f : w * side;
-    w = above > 0.0f ? w : 0.0f;
-    return fmaxf(A.z, fmaxf(B.z, C.z)) < 0.0f ? 0.0f : w;
+    auto edge = [](double e, int turn) { return e * turn > 0.0 ? turn : 0; };
+    const int w = edge(ab, la - lb) + edge(bc, lb - lc) + edge(ca, lc - la);
+    const double height = fma(bc, a.z - pz, fma(ca, b.z - pz, ab * (c.z - pz)));
+    return w * height > 0.0 ? w : 0;
 }
 
 constexpr int kStage = 1024;           // triangle slots in LDS (a larger mesh takes several rounds)
@@ -490,15 +499,15 @@ __device__ inline float mesh_sdf(const BuildArgs& p, MeshLds& s, V3 pt, bool wan
                 [&](const uint16_t* queue, int n) {
                     const int e = lane < n ? queue[lane] : lane;
                     const V3 q = point_of(pt, e & 63);
-                    float w = 0.0f;
+                    int w = 0;
 #pragma unroll
                     for (int k = 0; k < kGroup; ++k) {
                         const int slot = kGroup * (e >> 6) + k;
                         const Tri t = read_triangle(s, slot);
-                        const float x = crossing(q, t.a, t.b, t.c);
-                        w += slot < at + cnt ? x : 0.0f;   // not the repeated last triangle
+                        const int x = crossing(q, t.a, t.b, t.c);
+                        w += slot < at + cnt ? x : 0;   // not the repeated last triangle
                     }
-                    if (lane < n && w != 0.0f) atomicAdd(&s.count[wave][e & 63], (int)w);
+                    if (lane < n && w != 0) atomicAdd(&s.count[wave][e & 63], w);
                 });
             crossed += s.count[wave][lane];
         }
