@@ -312,7 +312,8 @@ __global__ __launch_bounds__(kBlock) void build_nn_kernel(BuildNNArgs a, const t
                                  j0 + 4 * g + r < V;
             if (covered && lsdf::inside<CUBIC>(lg, v0, v1, v2)) {
                 const float val = lsdf::cell_value<DT>(G, lg, v0, v1, v2);
-                atomic_min(&a.rs[(int64_t)c * env_v + ((int64_t)vz * a.n[1] + vy) * a.n[0] + vx], val);
+                // (a NaN, from a NaN or infinite node, is no value, as in build_kernel)
+                if (val < INFINITY) atomic_min(&a.rs[(int64_t)c * env_v + ((int64_t)vz * a.n[1] + vy) * a.n[0] + vx], val);
             }
         }
     }
