@@ -49,6 +49,15 @@ struct LinkBlock {   // per (configuration, link): the voxels to look at and the
 };
 static_assert(sizeof(LinkBlock) == 64, "LinkBlock layout");
 
+struct LinkBlockNN {   // per (configuration, link) of the network build
+    int32_t k[3];
+    uint32_t held_lo;                // (both of the first entry's: held_voxels)
+    float h[LSDF_FRNN_HIDDEN];       // hidden layer of f at this rotation, unit 4 s + g at 8 g + s
+    float dtinv[3];
+    uint32_t held_hi;
+};
+static_assert(sizeof(LinkBlockNN) == 160, "LinkBlockNN layout");
+
 struct BuildArgs {
     LinkGrid link[LSDF_MAX_LINKS];
     int32_t halfw[LSDF_MAX_LINKS];   // m_i
@@ -115,28 +124,81 @@ __global__ __launch_bounds__(kBlock) void align_kernel(BuildArgs a) {
     a.blocks[t] = b;
 }
 
+// What held_voxels needs of a network build; no blocks: another build.
+struct HeldArgs {
+    LinkBlockNN* blocks;
+    int64_t count;       // C L
+    int32_t n[3], w;     // the environment, 2 m
+};
+
+// Per axis, the block voxels that the environment holds in any configuration
+// and link: lo to hi - 1, a byte per axis from the low one (hi = 0: none).
+__device__ inline void held_voxels(const HeldArgs& a) {
+    __shared__ int range[kBlock / 64][6];
+    int r[6] = {a.w, a.w, a.w, 0, 0, 0};
+#pragma unroll 4
+    for (int64_t t = threadIdx.x; t < a.count; t += kBlock) {
+        int l[3], h[3];
+#pragma unroll
+        for (int ax = 0; ax < 3; ++ax) {
+            const int k = min(max(a.blocks[t].k[ax], -a.w), a.n[ax]);
+            l[ax] = max(-k, 0);
+            h[ax] = min(a.n[ax] - k, a.w);
+        }
+        const bool some = l[0] < h[0] && l[1] < h[1] && l[2] < h[2];
+#pragma unroll
+        for (int ax = 0; ax < 3; ++ax) {
+            r[ax] = min(r[ax], some ? l[ax] : a.w);
+            r[3 + ax] = max(r[3 + ax], some ? h[ax] : 0);
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+        for (int ax = 0; ax < 3; ++ax) {
+            r[ax] = min(r[ax], __shfl_xor(r[ax], o, 64));
+            r[3 + ax] = max(r[3 + ax], __shfl_xor(r[3 + ax], o, 64));
+        }
+#pragma unroll
+    for (int k = 0; k < 6; ++k)
+        if ((threadIdx.x & 63) == 0) range[threadIdx.x >> 6][k] = r[k];
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+#pragma unroll
+    for (int k = 0; k < 6; ++k)
+        for (int v = 1; v < kBlock / 64; ++v) r[k] = k < 3 ? min(r[k], range[v][k]) : max(r[k], range[v][k]);
+    a.blocks->held_lo = (uint32_t)(r[0] | r[1] << 8 | r[2] << 16);
+    a.blocks->held_hi = (uint32_t)(r[3] | r[4] << 8 | r[5] << 16);
+}
+
 // Every value of the Robot SDFs to +inf, before the minima: one 16 B store a
 // thread, so that the resident workgroups sweep the memory in order (1.68 GB in
 // 243 us, 6.9 TB/s; 4 stores a thread 276 us, a grid-stride loop 290 to 410 us,
-// non-temporal stores no better).
-__global__ __launch_bounds__(kBlock) void fill_inf_kernel(float* out, int64_t n, int64_t head, int64_t quads) {
+// non-temporal stores no better).  Beside it, in a workgroup of its own, the
+// network build's held_voxels.
+__global__ __launch_bounds__(kBlock) void fill_inf_kernel(float* out, int64_t n, int64_t head, int64_t quads, HeldArgs held) {
+    if (held.blocks && blockIdx.x == 0) {
+        held_voxels(held);
+        return;
+    }
     // out[head] is 16-byte aligned; the odd values at either end go one by one
-    const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t t = (int64_t)(blockIdx.x - (held.blocks ? 1 : 0)) * kBlock + threadIdx.x;
     const f32x4 inf = {INFINITY, INFINITY, INFINITY, INFINITY};
     if (t < quads) reinterpret_cast<f32x4*>(out + head)[t] = inf;
     if (t < head) out[t] = INFINITY;
     if (t < 4 && head + 4 * quads + t < n) out[head + 4 * quads + t] = INFINITY;
 }
 
-int launch_fill_inf(const char* who, float* out, int64_t n, hipStream_t s) {
+int launch_fill_inf(const char* who, float* out, int64_t n, HeldArgs held, hipStream_t s) {
     // launches of at most 2^30 quads each (2^22 workgroups)
     constexpr int64_t kMost = (int64_t)1 << 32;
-    for (int64_t at = 0; at < n; at += kMost) {
+    for (int64_t at = 0; at < n; at += kMost, held.blocks = nullptr) {
         float* p = out + at;
         const int64_t cnt = std::min(kMost, n - at);
         const int64_t head = std::min<int64_t>(cnt, (4 - (int64_t)((reinterpret_cast<uintptr_t>(p) >> 2) & 3)) & 3);
         const int64_t quads = (cnt - head) / 4;
-        hipLaunchKernelGGL(fill_inf_kernel, dim3((unsigned)(quads / kBlock + 1)), dim3(kBlock), 0, s, p, cnt, head, quads);
+        const dim3 grid((unsigned)(quads / kBlock + (held.blocks ? 2 : 1)));
+        hipLaunchKernelGGL(fill_inf_kernel, grid, dim3(kBlock), 0, s, p, cnt, head, quads, held);
         const int rc = lsdf::check_launch(who);
         if (rc != LSDF_OK) return rc;
     }
@@ -185,15 +247,6 @@ __global__ __launch_bounds__(kBlock) void build_kernel(BuildArgs a, const typena
 // link-frame position comes from the grid-transformation network,
 // G = f(R) + dt_inv with dt_inv = -R^T dt / e_r, l = e_r G, e_r = m r, for a
 // block half-width m shared by all links (the network's).
-struct LinkBlockNN {
-    int32_t k[3];
-    int32_t pad;
-    float h[LSDF_FRNN_HIDDEN];       // hidden layer of f at this rotation, unit 4 s + g at 8 g + s
-    float dtinv[3];
-    float pad2;
-};
-static_assert(sizeof(LinkBlockNN) == 160, "LinkBlockNN layout");
-
 struct BuildNNArgs {
     LinkGrid link[LSDF_MAX_LINKS];
     double lo[3];
@@ -253,8 +306,12 @@ __global__ __launch_bounds__(kBlock) void align_nn_kernel(BuildNNArgs a) {
 // of 85 us; the samples and their atomics take about 25 more) beside the +inf
 // fill (HBM).  40 configurations x 7 links, 44^3 block voxels, 128^3 voxels:
 // 2.01 ms a call with one thread per environment voxel, which read its 384 B
-// of weights from L2 for every link and configuration; 0.143 ms now.  The four
+// of weights from L2 for every link and configuration; 0.140 ms now.  The four
 // points' gathers issued together, and 5 or 6 waves a SIMD, measured the same.
+// A wave whose voxels no configuration has in the environment (held_voxels)
+// leaves before it loads any weights: 40 x 7 blocks all outside 64^3 voxels 73
+// -> 17 us (26 with a thread per environment voxel) for 1.5 us of the 140; a
+// ballot over each group's own voxels costs 8.
 constexpr int kTile = 16;            // block voxels and configurations per MFMA tile
 constexpr int64_t kNNWaves = 8192;   // waves of a build, about
 constexpr int kSteps = LSDF_FRNN_HIDDEN / 4;
@@ -263,8 +320,17 @@ template <bool CUBIC, int DT>
 __global__ __launch_bounds__(kBlock) void build_nn_kernel(BuildNNArgs a, const typename GridT<DT>::T* __restrict__ grid) {
     const int lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
     const int w = 2 * a.m, V = w * w * w;   // at most 128^3
-    const int j0 = ((int)blockIdx.x * (kBlock / 64) + (int)(threadIdx.x >> 6)) * kTile;
+    const int j0 = ((int)blockIdx.x * (kBlock / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))) * kTile;
     if (j0 >= V) return;
+    {
+        // an environment that the blocks stick out of holds few of their voxels,
+        // or none: a wave with none of them has nothing to do
+        const int last = min(j0 + kTile, V) - 1;
+        const uint32_t lo = a.blocks->held_lo, hi = a.blocks->held_hi;
+        const int z0 = j0 / (w * w), z1 = last / (w * w), y0 = j0 / w - z0 * w, y1 = last / w - z1 * w;
+        if (z1 < (int)(lo >> 16) || z0 >= (int)(hi >> 16)) return;
+        if (z0 == z1 && (y1 < (int)(lo >> 8 & 0xff) || y0 >= (int)(hi >> 8 & 0xff))) return;
+    }
     const float* W2 = a.params + LSDF_FRNN_HIDDEN * 10;
     const float* b2 = W2 + (int64_t)3 * V * LSDF_FRNN_HIDDEN;
     float wt[3][kSteps];
@@ -523,7 +589,7 @@ LSDF_API int lsdf_robot_sdf_build(const float* link_T, int32_t C, int32_t L, con
     const int64_t CL = (int64_t)C * L;
     hipLaunchKernelGGL(align_kernel, dim3((unsigned)((CL + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, a);
     if ((rc = check_launch("robot_sdf_build (align)")) != LSDF_OK) return rc;
-    if ((rc = launch_fill_inf("robot_sdf_build (fill)", robot_sdf, (int64_t)C * V, s)) != LSDF_OK) return rc;
+    if ((rc = launch_fill_inf("robot_sdf_build (fill)", robot_sdf, (int64_t)C * V, HeldArgs{}, s)) != LSDF_OK) return rc;
     // x: (configuration, link) pairs, y: shares of a pair's voxels
     const dim3 gd((unsigned)std::min<int64_t>(CL, 1 << 20), kBuildShares), bd(kBlock);
     switch (dtype * 2 + (cubic ? 1 : 0)) {
@@ -586,7 +652,8 @@ LSDF_API int lsdf_robot_sdf_build_frnn(const float* link_T, int32_t C, int32_t L
     const int64_t CL = (int64_t)C * L;
     hipLaunchKernelGGL(align_nn_kernel, dim3((unsigned)((CL * LSDF_FRNN_HIDDEN + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, a);
     if ((rc = check_launch("robot_sdf_build_frnn (align)")) != LSDF_OK) return rc;
-    if ((rc = launch_fill_inf("robot_sdf_build_frnn (fill)", robot_sdf, (int64_t)C * V, s)) != LSDF_OK) return rc;
+    const HeldArgs held{a.blocks, CL, {a.n[0], a.n[1], a.n[2]}, 2 * m};
+    if ((rc = launch_fill_inf("robot_sdf_build_frnn (fill)", robot_sdf, (int64_t)C * V, held, s)) != LSDF_OK) return rc;
     // x: 64 block voxels, y: shares of the groups, about 8 waves a SIMD in all
     // (a wave's weights, loaded once, serve its whole share: 16 a SIMD 5 us
     // slower, 32 a SIMD 37 us)
