@@ -75,8 +75,7 @@ struct BuildArgs {
 // mapped back to the world with the inverse of the grid map, the box widened by
 // 1e-3 + 1e-5 half + 1e-4 |w| grid steps, far beyond the FP32 rounding of a mapped centre.
 // A map with no sound inverse (no pose of a rigid link) keeps the whole block.
-__global__ __launch_bounds__(kBlock) void align_kernel(BuildArgs a) {
-    const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+__device__ inline void align(const BuildArgs& a, int64_t t) {
     if (t >= (int64_t)a.C * a.L) return;
     const int i = (int)(t % a.L);
     const LinkGrid& lg = a.link[i];
@@ -124,7 +123,7 @@ __global__ __launch_bounds__(kBlock) void align_kernel(BuildArgs a) {
     a.blocks[t] = b;
 }
 
-// What held_voxels needs of a network build; no blocks: another build.
+// What held_voxels needs of a network build.
 struct HeldArgs {
     LinkBlockNN* blocks;
     int64_t count;       // C L
@@ -174,31 +173,56 @@ __device__ inline void held_voxels(const HeldArgs& a) {
 // Every value of the Robot SDFs to +inf, before the minima: one 16 B store a
 // thread, so that the resident workgroups sweep the memory in order (1.68 GB in
 // 243 us, 6.9 TB/s; 4 stores a thread 276 us, a grid-stride loop 290 to 410 us,
-// non-temporal stores no better).  Beside it, in a workgroup of its own, the
-// network build's held_voxels.
-__global__ __launch_bounds__(kBlock) void fill_inf_kernel(float* out, int64_t n, int64_t head, int64_t quads, HeldArgs held) {
-    if (held.blocks && blockIdx.x == 0) {
-        held_voxels(held);
+// non-temporal stores no better).
+// What goes beside a fill, in workgroups of its own before the fill's: it needs
+// no launch then (40 x 7 blocks outside 64^3 voxels, nothing but the fill to do:
+// 16.4 us with the alignment in a launch before it, 13.0 beside it; 8^3 voxels
+// 8.0 and 6.6 us).  At the alignment's 78 registers the fill keeps its rate; held
+// to 64 it spills, 14.1 us.
+struct NoneBeside {
+    unsigned groups() const { return 0; }
+    __device__ void run() const {}
+};
+struct HeldBeside {
+    HeldArgs held;
+    unsigned groups() const { return 1; }
+    __device__ void run() const { held_voxels(held); }
+};
+struct AlignBeside {
+    BuildArgs a;
+    unsigned groups() const { return (unsigned)(((int64_t)a.C * a.L + kBlock - 1) / kBlock); }
+    __device__ void run() const { align(a, (int64_t)blockIdx.x * kBlock + threadIdx.x); }
+};
+
+template <class Beside>
+__global__ __launch_bounds__(kBlock) void fill_inf_kernel(float* out, int64_t n, int64_t head, int64_t quads, unsigned first,
+                                                          Beside beside) {
+    if (blockIdx.x < first) {
+        beside.run();
         return;
     }
     // out[head] is 16-byte aligned; the odd values at either end go one by one
-    const int64_t t = (int64_t)(blockIdx.x - (held.blocks ? 1 : 0)) * kBlock + threadIdx.x;
+    const int64_t t = (int64_t)(blockIdx.x - first) * kBlock + threadIdx.x;
     const f32x4 inf = {INFINITY, INFINITY, INFINITY, INFINITY};
     if (t < quads) reinterpret_cast<f32x4*>(out + head)[t] = inf;
     if (t < head) out[t] = INFINITY;
     if (t < 4 && head + 4 * quads + t < n) out[head + 4 * quads + t] = INFINITY;
 }
 
-int launch_fill_inf(const char* who, float* out, int64_t n, HeldArgs held, hipStream_t s) {
+template <class Beside>
+int launch_fill_inf(const char* who, float* out, int64_t n, const Beside& beside, hipStream_t s) {
     // launches of at most 2^30 quads each (2^22 workgroups)
     constexpr int64_t kMost = (int64_t)1 << 32;
-    for (int64_t at = 0; at < n; at += kMost, held.blocks = nullptr) {
+    for (int64_t at = 0; at < n; at += kMost) {
         float* p = out + at;
         const int64_t cnt = std::min(kMost, n - at);
         const int64_t head = std::min<int64_t>(cnt, (4 - (int64_t)((reinterpret_cast<uintptr_t>(p) >> 2) & 3)) & 3);
         const int64_t quads = (cnt - head) / 4;
-        const dim3 grid((unsigned)(quads / kBlock + (held.blocks ? 2 : 1)));
-        hipLaunchKernelGGL(fill_inf_kernel, grid, dim3(kBlock), 0, s, p, cnt, head, quads, held);
+        const unsigned first = at == 0 ? beside.groups() : 0, groups = (unsigned)(quads / kBlock + 1);
+        if (first)
+            hipLaunchKernelGGL(fill_inf_kernel<Beside>, dim3(first + groups), dim3(kBlock), 0, s, p, cnt, head, quads, first, beside);
+        else
+            hipLaunchKernelGGL(fill_inf_kernel<NoneBeside>, dim3(groups), dim3(kBlock), 0, s, p, cnt, head, quads, 0u, NoneBeside{});
         const int rc = lsdf::check_launch(who);
         if (rc != LSDF_OK) return rc;
     }
@@ -587,9 +611,7 @@ LSDF_API int lsdf_robot_sdf_build(const float* link_T, int32_t C, int32_t L, con
     a.rs = robot_sdf;
     hipStream_t s = as_stream(stream);
     const int64_t CL = (int64_t)C * L;
-    hipLaunchKernelGGL(align_kernel, dim3((unsigned)((CL + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, a);
-    if ((rc = check_launch("robot_sdf_build (align)")) != LSDF_OK) return rc;
-    if ((rc = launch_fill_inf("robot_sdf_build (fill)", robot_sdf, (int64_t)C * V, HeldArgs{}, s)) != LSDF_OK) return rc;
+    if ((rc = launch_fill_inf("robot_sdf_build (align and fill)", robot_sdf, (int64_t)C * V, AlignBeside{a}, s)) != LSDF_OK) return rc;
     // x: (configuration, link) pairs, y: shares of a pair's voxels
     const dim3 gd((unsigned)std::min<int64_t>(CL, 1 << 20), kBuildShares), bd(kBlock);
     switch (dtype * 2 + (cubic ? 1 : 0)) {
@@ -652,7 +674,7 @@ LSDF_API int lsdf_robot_sdf_build_frnn(const float* link_T, int32_t C, int32_t L
     const int64_t CL = (int64_t)C * L;
     hipLaunchKernelGGL(align_nn_kernel, dim3((unsigned)((CL * LSDF_FRNN_HIDDEN + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, a);
     if ((rc = check_launch("robot_sdf_build_frnn (align)")) != LSDF_OK) return rc;
-    const HeldArgs held{a.blocks, CL, {a.n[0], a.n[1], a.n[2]}, 2 * m};
+    const HeldBeside held{{a.blocks, CL, {a.n[0], a.n[1], a.n[2]}, 2 * m}};
     if ((rc = launch_fill_inf("robot_sdf_build_frnn (fill)", robot_sdf, (int64_t)C * V, held, s)) != LSDF_OK) return rc;
     // x: 64 block voxels, y: shares of the groups, about 8 waves a SIMD in all
     // (a wave's weights, loaded once, serve its whole share: 16 a SIMD 5 us
