@@ -376,8 +376,7 @@ __device__ __forceinline__ void collect(const QueryArgs& p, const PackedBox* __r
             for (int k = 0; k < kGroupBatch; ++k)   // past the trajectory's groups: its last one, not tested
                 bx[k] = gbox[min(w.gb + k * gstep, ngroup - 1)];
             uint32_t gnear = 0;
-#pragma unroll
-            for (int k = 0; k < kGroupBatch; ++k) {
+            auto test = [&](int k) {
                 const Box& b = bx[k];
                 float s0, s1, s2;
                 map_point(m, b.cx, b.cy, b.cz, s0, s1, s2);
@@ -385,7 +384,21 @@ __device__ __forceinline__ void collect(const QueryArgs& p, const PackedBox* __r
                 const float r1 = fmaf(fabsf(m.m10), b.hx, fmaf(fabsf(m.m11), b.hy, fmaf(fabsf(m.m12), b.hz, m.k1)));
                 const float r2 = fmaf(fabsf(m.m20), b.hx, fmaf(fabsf(m.m21), b.hy, fmaf(fabsf(m.m22), b.hz, m.k2)));
                 const bool near = (fabsf(s0) <= r0) & (fabsf(s1) <= r1) & (fabsf(s2) <= r2);
-                if (__ballot(near) && w.gb + k * gstep < ngroup) gnear |= 1u << k;
+                if (__ballot(near)) gnear |= 1u << k;
+            };
+            // a full batch with no branch between its tests; of the last one, which
+            // is all a small call's wave has, only the groups there are (363 x 8,248
+            // x 7 that meet nothing, a group a wave: 13.0 us with all four tested,
+            // 12.5; 1,000 x 100,000 x 7, 12 a wave, 25.8 and 25.2)
+            if (w.gb + (kGroupBatch - 1) * gstep < ngroup) {
+#pragma unroll
+                for (int k = 0; k < kGroupBatch; ++k) test(k);
+            } else {
+#pragma unroll
+                for (int k = 0; k < kGroupBatch - 1; ++k) {
+                    if (w.gb + k * gstep >= ngroup) break;
+                    test(k);
+                }
             }
             while (gnear) {   // wave-uniform
                 const int kg = __builtin_ctz(gnear);
