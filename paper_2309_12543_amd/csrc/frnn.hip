@@ -13,11 +13,12 @@
 // kernels, every sum in the order of the rows or rotations it runs over (a step
 // from other bits, an ulp in a parameter, now and then turns a sign of the next
 // step's errors):
-//   step kernel    (from 512 blocks of 128 outputs on; below that the row kernel, one thread per
-//                  output, and an Adam kernel at the end) every wave takes blocks of 128 outputs, 16 at a time: their values, their errors
-//                  against the exact target, dW2 and db2 and their Adam update, the wave's share
-//                  of the loss and the block's of dh = sum_o g_o W2[o] (g_o = sign(error) /
-//                  (B 3V)), with every product on FP32 MFMA;
+//   step kernel    every wave takes blocks of 128 outputs, 16 at a time: their
+//                  values, their errors against the exact target, dW2 and db2 and
+//                  their Adam update, the wave's share of the loss and the block's
+//                  of dh = sum_o g_o W2[o] (g_o = sign(error) / (B 3V)), with every
+//                  product on FP32 MFMA (of few blocks the row kernel takes them, a
+//                  thread per output, and an Adam kernel at the end: takes_rows);
 //   slice kernel   sums the blocks' shares of dh in 64 interleaved slices;
 //   finish kernel  a workgroup per hidden unit sums the slices, then dW1, db1
 //                  through the ReLU and their Adam update; one more the loss.
@@ -36,7 +37,6 @@ constexpr int kMaxB = 64;           // rotations per training step
 constexpr int kTile = 64;           // rotations per tile in the max-error kernel
 constexpr int kStepBlock = 256;     // threads of the step kernel's workgroups
 constexpr int kStepGroups = 512;    // its workgroups at most: two a CU
-constexpr int kRowBlocks = 512;     // with fewer blocks of 128 outputs the row kernel takes the step (its comment)
 constexpr int kBlockUnits = 8;      // units of 16 outputs whose share of dh is summed by itself
 constexpr int kSlices = 64;         // first level of the sum of these shares
 
@@ -367,18 +367,23 @@ __global__ __launch_bounds__(kStepBlock, 2) void frnn_step_kernel(TrainArgs a) {
     }
 }
 
-// The step of a network of fewer than 512 blocks of 128 outputs: one thread per
-// output row, a workgroup per block, on FP32 VALU; the step kernel's sums in the
-// step kernel's order. Latency bounds both. A wave of the step kernel takes the
-// 8 units of a block one after another, a chain of 29 to 61 us where there are
-// too few blocks to hide it; here two waves share a block and Adam follows as a
-// kernel of its own, whose traffic costs more than the chain from 512 blocks on.
-// A training step (us, step kernel and this one) at 1, 16 and 64 rotations:
-//    5,184 outputs (12^3)   37, 39, 62    21, 26, 42
-//   24,000 outputs (20^3)   39, 41, 64    25, 31, 49
-//   41,472 outputs (24^3)   41, 42, 66    33, 39, 58
-//   65,856 outputs (28^3)   41, 43, 68    41, 48, 68 (hidden layer in a launch of its own)
-//   98,304 outputs (32^3)   43, 45, 71    50, 55, 75 (so too)
+// The step of a network of few blocks (takes_rows): one thread per output row, a
+// workgroup per block, on FP32 VALU; the step kernel's sums in the step kernel's
+// order.  Latency bounds both.  A wave of the step kernel takes the 8 units of a
+// block one after another, a chain of 29 to 61 us, longer by 8 for every 16
+// rotations begun, where there are too few blocks to hide it; here two waves
+// share a block and Adam follows as a kernel of its own, whose traffic grows with
+// the blocks.  A training step (us, step kernel and this one):
+//   outputs (blocks)         1 rotation    16            17            33            64
+//     5,184 (41)             37.2  20.8    38.4  26.1                                61.7  42.0
+//    24,000 (188)            38.9  24.8    40.5  30.4                                64.0  46.5
+//    52,728 (412)            41.2  35.6    43.6  41.1    51.7  41.2    60.0  47.0    67.6  58.4
+//    65,856 (515)            40.8  37.7    43.1  43.3    50.7  43.7    58.9  49.5    67.6  61.4
+//    81,000 (633)            41.4  42.4    43.7  48.3    50.1  48.3    60.3  54.9    68.8  67.1
+//    98,304 (768)            42.1  48.0    44.3  53.0    52.4  52.4    61.2  58.9    69.8  71.8
+//   117,912 (922)            43.4  53.9    45.9  59.7    53.2  59.0    62.4  65.2    70.6  79.2
+inline bool takes_rows(int64_t blocks, int B) { return blocks < (B <= 16 ? 576 : 704); }
+
 __global__ __launch_bounds__(kRows) void frnn_row_kernel(TrainArgs a) {
     static_assert(kRows == (kMaxB / 4) * (kH / 4), "one 4 x 4 tile of dh per thread");
     __shared__ float hs[kMaxB][kH];
@@ -676,7 +681,7 @@ LSDF_API int lsdf_frnn_train_step(float* params, float* adam_m, float* adam_v, i
     a.r2 = (float)(1.0 / (double)a.c2);
     hipStream_t s = as_stream(stream);
     static_assert(kRows == 16 * kBlockUnits, "a row workgroup's share is a block's");
-    const bool rows = a.blocks < kRowBlocks;
+    const bool rows = takes_rows(a.blocks, B);
     if (rows) {
         a.groups = a.blocks;
         hipLaunchKernelGGL(frnn_row_kernel, dim3((unsigned)a.blocks), dim3(kRows), 0, s, a);
