@@ -750,8 +750,9 @@ LSDF_API int lsdf_build_link_sdfs(int32_t n, const float* const* verts, const in
         p.out = static_cast<char*>(grid_buf) + desc.elem_offset * (desc.dtype == LSDF_F32 ? 4 : 2);
         const int64_t nodes = (int64_t)p.n[0] * p.n[1] * p.n[2];
         // bricks unless their padding would leave more than half the lanes idle (thin grids)
+        // or take 2^32 threads, which no launch may have (2 x 1,024 x 2^20 nodes)
         const int64_t bricks = (int64_t)((p.n[0] + 3) / 4) * ((p.n[1] + 3) / 4) * ((p.n[2] + 3) / 4);
-        p.bricks = bricks * 64 <= 2 * nodes;
+        p.bricks = bricks * 64 <= 2 * nodes && bricks * 64 < (int64_t)1 << 32;
         const int64_t blocks = ((p.bricks ? bricks * 64 : nodes) + kBlock - 1) / kBlock;
         p.blocks = (int32_t)blocks;   // nodes <= 2^31
         most = std::max(most, blocks);
