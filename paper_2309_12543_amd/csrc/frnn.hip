@@ -96,8 +96,9 @@ struct AdamState {
     float p, m, v;
 };
 // x / c, rounded as a division, from r = 1 / c rounded (Markstein): the quotient's
-// error is exact in one multiply-add, and adding it times r rounds once.
-// Where that is not finite the product stands.
+// error is exact in one multiply-add, and adding it times r rounds once (below
+// 2^-102 that error underflows, and the quotient is within one unit in the last
+// place).  Where that is not finite the product stands.
 __device__ inline float divide(float x, float c, float r) {
     const float q = x * r, t = fmaf(fmaf(-q, c, x), r, q);
     return t == t ? t : q;

@@ -69,10 +69,7 @@ namespace {
 
 using lsdf::GridT;
 using lsdf::LinkGrid;
-using lsdf::Cell;
 using lsdf::inside;
-using lsdf::interpolate;
-using lsdf::locate;
 
 #ifndef LSDF_QUERY_BLOCK
 #define LSDF_QUERY_BLOCK 256         // threads per workgroup of the query kernel
@@ -103,7 +100,6 @@ constexpr int kGroupBatch = LSDF_QUERY_GROUP_BATCH;
 // so small that an eighth of the waves would have a group (C = 50, M = 2,000:
 // 15.1 us with quarters, 16.3 with halves, 18.2 with whole ones; C = 200, M =
 // 8,000 near the arm, halves where the rule takes whole groups: 59 us, not 49).
-constexpr int kDefaultChunkPoints = 1024;
 constexpr int kDefaultBlocksPerCu = 8;
 constexpr int kDefaultSchedule = LSDF_SCHED_INTERLEAVED;
 
@@ -482,8 +478,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_num_sgpr(80))) void q
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t total = plan[p.K].chunk_start;
     // The waves of one workgroup start a grid's (or slice's) width apart, on
-    // different links or tiles, so that the shared list evens them out.  From there every wave takes every n-th chunk, or (DEAL) the
-    // workgroups take the rest in runs from a counter per XCD.
+    // different links or tiles, so that the shared list evens them out.  From
+    // there every wave takes every n-th chunk, or (DEAL) the workgroups take the
+    // rest in runs from a counter per XCD.
     const int xcd = blockIdx.x % kXcds;
     const bool slices = p.schedule == LSDF_SCHED_XCD_SLICES;   // each XCD (blocks b = x mod 8) its own range of chunks
     const int64_t lo = slices ? total * xcd / kXcds : 0, hi = slices ? total * (xcd + 1) / kXcds : total;
@@ -905,11 +902,12 @@ int device_cus() {
     return cus;
 }
 
+// (chunk_blocks and blocks_per_cu: 0 where the call's sizes are to choose)
 int check_tuning(const char* who, const lsdf_query_tuning* t, int* chunk_blocks, int* blocks_per_cu,
                  int* schedule) {
     using lsdf::fail;
-    *chunk_blocks = kDefaultChunkPoints / kBlockPts;
-    *blocks_per_cu = kDefaultBlocksPerCu;
+    *chunk_blocks = 0;
+    *blocks_per_cu = 0;
     *schedule = kDefaultSchedule;
     if (!t) return LSDF_OK;
     if (t->chunk_points != 0) {
@@ -974,15 +972,19 @@ int run_query(const char* who, int32_t K, const int32_t* c_off, const int64_t* m
     }
     const int cus = device_cus();
     if (cus <= 0) return fail(LSDF_E_DEVICE, "%s: cannot read the device's compute-unit count", who);
-    if (!(tuning && tuning->blocks_per_cu != 0)) 
-        blocks_per_cu = with_variant(dtype, cubic, false, [](auto v) {
+    auto resident = [&](bool deal) {
+        return with_variant(dtype, cubic, deal, [](auto v) {
             using V = decltype(v);
             return resident_blocks_of<V::cubic, V::dtype, V::deal>();
         });
-    if (!(tuning && tuning->chunk_points != 0))   // from the capacities C and M when offsets are given
+    };
+    const bool fill_device = blocks_per_cu == 0;
+    if (fill_device) blocks_per_cu = resident(false);
+    if (chunk_blocks == 0)   // from the capacities C and M when offsets are given
         chunk_blocks = default_chunk_blocks(K, C, L, M, (int64_t)cus * blocks_per_cu * kWavesPerBlock);
     const bool deal = (double)L * ((C + 63) / 64) * ((M + kBlockPts * chunk_blocks - 1) / (kBlockPts * chunk_blocks)) >=
                       (double)K * kDealChunks * cus * blocks_per_cu * kWavesPerBlock;
+    if (fill_device && deal) blocks_per_cu = resident(true);
     hipStream_t s = as_stream(stream);
     char* ws = static_cast<char*>(workspace);
     PackedBox* block_box = reinterpret_cast<PackedBox*>(ws + keys_bytes(C, L));
