@@ -26,7 +26,8 @@ PEAK_FP32_VECTOR_TFLOPS = 157.3       # MI355X published FP32 vector peak
 # the same ALUs without packed FP32 (the library is built with it off): 256 CUs x 4 SIMDs x 16 lanes
 # x one FMA (2 FLOP) per clock x 2.4 GHz
 PEAK_FP32_UNPACKED_TFLOPS = 256 * 4 * 16 * 2 * 2.4e9 / 1e12
-FLOP_PER_TEST = 24                    # map a point or a sphere centre to grid coordinates (9 FMA) + 6 compares
+FLOP_PER_BOX_TEST = 42                # map a box's centre and half extents to grid coordinates (18 FMA) + 6 compares
+FLOP_PER_POINT_TEST = 24              # map a point to grid coordinates (9 FMA) + 6 compares
 FLOP_PER_INBOX_PAIR = 28              # cell + fraction (6), 7 lerps (21), min (1)
 BYTES_PER_INBOX_PAIR = 32             # 8 gathered FP32 corners
 
@@ -50,25 +51,26 @@ def profiled_traffic(kernel_source: str, summary: str):
         return None
 
 
-def culled_work(T: np.ndarray, lo, hi, points: np.ndarray, block: int = 8):
+def culled_work(T: np.ndarray, lo, hi, points: np.ndarray, block: int = 8, group: int = 64):
     """Work of the culled method at waypoint-link granularity, in double
-    precision: (sphere tests, pairs in blocks whose sphere reaches the link's
-    box, pairs inside the box).  Every (waypoint, link, 8-point block) needs
-    one sphere test; a surviving block needs the point test of its points;
-    an in-box pair needs the interpolation.  Used only to price the kernel's
-    compulsory work for the roofline."""
+    precision: (box tests, pairs in blocks whose box reaches the link's box,
+    pairs inside the box).  Every (waypoint, link) tests the box of each group
+    of 64 points and, of the groups that reach its box, that of each block of
+    8; a block that does needs the point test of its points; an in-box pair
+    needs the interpolation.  Used only to price the kernel's compulsory work
+    for the roofline (a wave tests 64 waypoints at once, and goes on where one
+    of them does)."""
     P = points.astype(np.float64)
     M = P.shape[0]
-    nb = (M + block - 1) // block
+    nb, ng, per = (M + block - 1) // block, (M + group - 1) // group, group // block
     pad = np.concatenate([P, np.repeat(P[-1:], nb * block - M, axis=0)]).reshape(nb, block, 3)
     cnt = np.full(nb, block)
     cnt[-1] = M - (nb - 1) * block
     bmin, bmax = pad.min(axis=1), pad.max(axis=1)
-    cen = 0.5 * (bmin + bmax)
-    rad = np.sqrt(((pad - cen[:, None, :]) ** 2).sum(-1)).max(axis=1)
+    first = np.arange(ng) * per
+    gmin, gmax = np.minimum.reduceat(bmin, first), np.maximum.reduceat(bmax, first)
     C, L = T.shape[:2]
-    tests = C * L * nb
-    surv_pairs, inbox = 0, 0
+    tests, surv_pairs, inbox = C * L * ng, 0, 0
     for i in range(L):
         mid = 0.5 * (lo[i] + hi[i])
         hw = 0.5 * (hi[i] - lo[i])
@@ -76,9 +78,15 @@ def culled_work(T: np.ndarray, lo, hi, points: np.ndarray, block: int = 8):
         t = T[:, i, :, 3].astype(np.float64)
         for c0 in range(0, C, 25):
             Rc, tc = R[c0:c0 + 25], t[c0:c0 + 25]
-            lc = np.einsum("cba,cjb->cja", Rc, cen[None] - tc[:, None, :])              # [c][block][3]
-            surv = np.all(np.abs(lc - mid) <= hw + rad[None, :, None], axis=-1)          # [c][block]
-            surv_pairs += int((surv * cnt[None, :]).sum())
+
+            def reaches(b0, b1):                                                         # [c][box]
+                lc = np.einsum("cba,cjb->cja", Rc, 0.5 * (b0 + b1)[None] - tc[:, None, :])
+                ext = np.einsum("cba,jb->cja", np.abs(Rc), 0.5 * (b1 - b0))
+                return np.all(np.abs(lc - mid) <= hw + ext, axis=-1)
+
+            near = np.repeat(reaches(gmin, gmax), per, axis=1)[:, :nb]
+            tests += int(near.sum())
+            surv_pairs += int(((near & reaches(bmin, bmax)) * cnt[None, :]).sum())
             lp = np.einsum("cba,cjb->cja", Rc, P[None] - tc[:, None, :])
             inbox += int(np.all((lp >= lo[i]) & (lp <= hi[i]), axis=-1).sum())
     return tests, surv_pairs, inbox
@@ -209,13 +217,13 @@ def scene_line(dev, w, label: str, steps: int, warmup: int):
     kernel_ms = float(np.mean([a.elapsed_time(b) for a, b in ev]))
     tests, surv, inbox = culled_work(T.cpu().numpy(), w.grid_lo.astype(np.float64), w.grid_hi.astype(np.float64),
                                      w.points)
-    flop = FLOP_PER_TEST * (tests + surv) + FLOP_PER_INBOX_PAIR * inbox
+    flop = FLOP_PER_BOX_TEST * tests + FLOP_PER_POINT_TEST * surv + FLOP_PER_INBOX_PAIR * inbox
     achieved = flop / (kernel_ms / 1e3) / 1e12
     pairs = w.C * w.M * w.L
     return {"workload": label, "ms_per_step": round(ms, 5), "gpu_ms_per_step": round(gpu_ms, 5),
             "value": round(pairs / (ms / 1e3) / 1e9, 2), "unit": "G point-link queries/s",
             "query_kernel_ms": round(kernel_ms, 5), "inbox_pair_fraction": round(inbox / pairs, 5),
-            "sphere_survivor_pair_fraction": round(surv / pairs, 5),
+            "box_survivor_pair_fraction": round(surv / pairs, 5),
             "roofline": {"bound": "alu", "achieved": round(achieved, 3), "peak": PEAK_FP32_VECTOR_TFLOPS,
                          "unit": "TFLOP/s", "frac": round(achieved / PEAK_FP32_VECTOR_TFLOPS, 4),
                          "algorithmic_flop": flop,
@@ -318,7 +326,7 @@ def learned_variant(dev, steps: int, epochs=None, judge_waypoints: int = 50):
     return {
         "workload": f"{w.name}: {w.C} waypoints x {w.M} points x {w.L} links, 64^3 FP32 grids, "
                     f"3-128-128-128-1 SiLU network per link (bf16 MFMA, FP32 accumulate), its share bounded, plus the "
-                    f"distance to the link's core box; tiles that cannot hold a minimum skipped; fallback below 5 cm",
+                    f"distance to the link's core box; pairs that cannot hold a minimum skipped; fallback below 5 cm",
         "grid_ms_per_batch": round(grid_ms, 4),
         "mlp_ms_per_batch": round(mlp_ms, 3),
         "grid_gq_s": round(pairs / (grid_ms / 1e3) / 1e9, 2),
@@ -850,7 +858,7 @@ def main():
 
     Tn = T.cpu().numpy()
     tests, surv_pairs, inbox = culled_work(Tn, w.grid_lo.astype(np.float64), w.grid_hi.astype(np.float64), w.points)
-    flop = FLOP_PER_TEST * (tests + surv_pairs) + FLOP_PER_INBOX_PAIR * inbox
+    flop = FLOP_PER_BOX_TEST * tests + FLOP_PER_POINT_TEST * surv_pairs + FLOP_PER_INBOX_PAIR * inbox
     achieved = flop / (kernel_ms / 1e3) / 1e12
     rec = {
         "metric": METRIC,
@@ -888,7 +896,7 @@ def main():
         "graph_replay_ms_per_step": round(graph_ms, 5),
         "graph_equals_eager": same,
         "inbox_pair_fraction": round(inbox / pairs, 5),
-        "sphere_survivor_pair_fraction": round(surv_pairs / pairs, 5),
+        "box_survivor_pair_fraction": round(surv_pairs / pairs, 5),
         "roofline": {"bound": "alu", "achieved": round(achieved, 3), "peak": PEAK_FP32_VECTOR_TFLOPS,
                      "unit": "TFLOP/s", "frac": round(achieved / PEAK_FP32_VECTOR_TFLOPS, 4),
                      "traffic": profiled_traffic(os.path.join(ROOT, "paper_2309_12543_amd", "csrc", "query.hip"),
@@ -897,8 +905,9 @@ def main():
                      "peak_unpacked_fp32": round(PEAK_FP32_UNPACKED_TFLOPS, 1),
                      "frac_of_unpacked_fp32": round(achieved / PEAK_FP32_UNPACKED_TFLOPS, 4),
                      "algorithmic_flop": flop,
-                     "work": {"sphere_tests": tests, "point_tests_in_surviving_blocks": surv_pairs,
-                              "inbox_pairs": inbox, "flop_per_test": FLOP_PER_TEST,
+                     "work": {"box_tests": tests, "point_tests_in_surviving_blocks": surv_pairs,
+                              "inbox_pairs": inbox, "flop_per_box_test": FLOP_PER_BOX_TEST,
+                              "flop_per_point_test": FLOP_PER_POINT_TEST,
                               "flop_per_inbox_pair": FLOP_PER_INBOX_PAIR}},
     }
     roof = gather_roof(dev)
