@@ -337,7 +337,8 @@ __device__ __forceinline__ void collect(const QueryArgs& p, const PackedBox* __r
         // places are turned by 0.618 cpg from tile to tile: a workgroup's waves take
         // chunks half a grid or more apart, which would test the same part of the
         // cloud where that is near a multiple of cpg (500 x 100,000 on 128^3 grids
-        // beside a table, 2,008 workgroups, cpg 143: 67 us, 53 with the turn)
+        // beside a table, 2,008 workgroups, cpg 143: 67 us, 53 with the turn; the
+        // geometric mean over 12 other scenes is 44.3 us without it and 45.0 with it)
         mc += __umulhi((uint32_t)g * 2654435769u, (uint32_t)cpg);
         if (mc >= cpg) mc -= cpg;
         const int i = (int)((uint32_t)g / (uint32_t)cgroups);
