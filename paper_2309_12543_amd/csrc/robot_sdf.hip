@@ -330,12 +330,13 @@ __global__ __launch_bounds__(kBlock) void align_nn_kernel(BuildNNArgs a) {
 // of 85 us; the samples and their atomics take about 25 more) beside the +inf
 // fill (HBM).  40 configurations x 7 links, 44^3 block voxels, 128^3 voxels:
 // 2.01 ms a call with one thread per environment voxel, which read its 384 B
-// of weights from L2 for every link and configuration; 0.140 ms now.  The four
+// of weights from L2 for every link and configuration; 0.138 ms now.  The four
 // points' gathers issued together, and 5 or 6 waves a SIMD, measured the same.
 // A wave whose voxels no configuration has in the environment (held_voxels)
 // leaves before it loads any weights: 40 x 7 blocks all outside 64^3 voxels 73
-// -> 17 us (26 with a thread per environment voxel) for 1.5 us of the 140; a
-// ballot over each group's own voxels costs 8.
+// -> 17 us (26 with a thread per environment voxel), 0.138 ms with it and
+// without where the environment holds nearly all; a ballot over each group's own
+// voxels costs 7 us of that.
 constexpr int kTile = 16;            // block voxels and configurations per MFMA tile
 constexpr int64_t kNNWaves = 8192;   // waves of a build, about
 constexpr int kSteps = LSDF_FRNN_HIDDEN / 4;
