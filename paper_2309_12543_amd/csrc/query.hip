@@ -324,39 +324,42 @@ __device__ __forceinline__ void collect(const QueryArgs& p, const PackedBox* __r
         const TrajPlan& t = plan[w.k];
         const int64_t m_lo = t.m_lo, m_hi = t.m_hi;
         const int cgroups = t.cgroups, cpg = t.chunks_per_group;
+        // (plain 32-bit and unsigned arithmetic: a small call is bound by the issue of
+        // the some 400 mostly scalar instructions each wave needs to reach its
+        // boxes; 363 x 8,248 x 7 that meet nothing 12.5 us with signed 64-bit
+        // quotients and a modulo in mix_slot, 12.2 so)
         const int64_t local = w.q - t.chunk_start;
-        int64_t g, mc;
+        uint32_t g, mc;   // tile (at most L C / 64 of them) and chunk of it
         if (local < ((int64_t)1 << 32)) {
-            const uint32_t l32 = (uint32_t)local;
-            g = l32 / (uint32_t)cpg;
-            mc = l32 - (uint32_t)g * (uint32_t)cpg;
+            g = (uint32_t)local / (uint32_t)cpg;
+            mc = (uint32_t)local - g * (uint32_t)cpg;
         } else {
-            g = local / cpg;
-            mc = local - g * cpg;
+            g = (uint32_t)((uint64_t)local / (uint32_t)cpg);
+            mc = (uint32_t)(local - (int64_t)g * cpg);
         }
         // places are turned by 0.618 cpg from tile to tile: a workgroup's waves take
         // chunks half a grid or more apart, which would test the same part of the
         // cloud where that is near a multiple of cpg (500 x 100,000 on 128^3 grids
         // beside a table, 2,008 workgroups, cpg 143: 67 us, 53 with the turn; the
         // geometric mean over 12 other scenes is 44.3 us without it and 45.0 with it)
-        mc += __umulhi((uint32_t)g * 2654435769u, (uint32_t)cpg);
-        if (mc >= cpg) mc -= cpg;
-        const int i = (int)((uint32_t)g / (uint32_t)cgroups);
-        const int cb = (int)((uint32_t)g - (uint32_t)i * (uint32_t)cgroups);
+        mc += __umulhi(g * 2654435769u, (uint32_t)cpg);   // both below cpg < 2^31
+        if (mc >= (uint32_t)cpg) mc -= (uint32_t)cpg;
+        const int i = (int)(g / (uint32_t)cgroups);
+        const int cb = (int)(g - (uint32_t)i * (uint32_t)cgroups);
         const int c0 = t.c_lo + cb * 64, cn = min(t.c_n - cb * 64, 64);
         // the trajectory's points lie in groups of 8 blocks of 8 (aligned in the
         // concatenated cloud); chunk mc takes every cpg-th group from the
         // trajectory's group mc, so that points near a link, which lie together
         // in the cloud, spread over the chunks rather than piling onto a few
         // waves
-        const int64_t group0 = m_lo / kGroupPts;
-        const int ngroup = (int)((m_hi + kGroupPts - 1) / kGroupPts - group0);
+        const int64_t group0 = (uint64_t)m_lo / kGroupPts;
+        const int ngroup = (int)((uint64_t)(m_hi + kGroupPts - 1) / kGroupPts - group0);
         const Box* const gbox = groups + group0;
         // blocks of the trajectory, counted from its first group's
-        const uint32_t blk0 = (uint32_t)((m_lo - group0 * kGroupPts) / kBlockPts);
-        const uint32_t blk1 = (uint32_t)((m_hi - group0 * kGroupPts + kBlockPts - 1) / kBlockPts);
+        const uint32_t blk0 = ((uint32_t)m_lo & (kGroupPts - 1)) / kBlockPts;
+        const uint32_t blk1 = (uint32_t)((uint64_t)(m_hi - group0 * kGroupPts + kBlockPts - 1) / kBlockPts);
         // the share of a group's blocks that is the chunk's (all, or a part)
-        const int part = (int)mc & ((1 << p.split) - 1), gstep = cpg >> p.split;
+        const int part = (int)(mc & ((1u << p.split) - 1)), gstep = cpg >> p.split;
         const uint32_t share = ((1u << (kGroupBlocks >> p.split)) - 1) << (part * (kGroupBlocks >> p.split));
         Map m;
         load_map(p, i, c0, cn, lane, m);
@@ -462,7 +465,8 @@ __device__ __forceinline__ void collect(const QueryArgs& p, const PackedBox* __r
 // late links, early and late configuration groups).  A bijection of [0, n)
 // for each w.
 __device__ __forceinline__ int mix_slot(int b, int n, int w) {
-    int s = (w & 2) ? (b + n / 2) % n : b;
+    int s = (w & 2) ? b + n / 2 : b;
+    if (s >= n) s -= n;
     return (w & 1) ? n - 1 - s : s;
 }
 
