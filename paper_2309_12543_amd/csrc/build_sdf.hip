@@ -56,24 +56,36 @@ __device__ inline float dot(V3 a, V3 b) { return a.x * b.x + a.y * b.y + a.z * b
 __device__ inline float fdot(V3 a, V3 b) { return fmaf(a.x, b.x, fmaf(a.y, b.y, a.z * b.z)); }
 __device__ inline V3 cross(V3 a, V3 b) { return {a.y * b.z - a.z * b.y, a.z * b.x - a.x * b.z, a.x * b.y - a.y * b.x}; }
 
+// u v - x y within 2 units in the last place whatever cancels (Kahan's difference
+// of products).
+__device__ inline float diff_of_products(float u, float v, float x, float y) {
+    const float m = x * y;
+    return fmaf(u, v, -m) + fmaf(-x, y, m);
+}
+
 // Squared distance from p to triangle (a, b, c), by the Voronoi regions of
 // its vertices, edges and face: the closest point is a + v ab + w ac, or b + w bc
-// on edge bc, with v and w quotients over one denominator, which the first region
-// whose condition holds gives (selected from the last to the first; bc's
-// denominator is negated, which marks it).  A condition is one compare of a
-// minimum: comparisons combined in scalar registers left a wave waiting on the
-// scalar unit for most of the 1,500 cycles a triangle took.  Edge bc from b rounds
-// once where a + v ab + w ac rounds twice and leaves the edge: over grids of an
-// arm's links the root mean square error was 4 % above that of divisions and
-// separate multiplies and adds for every edge, and is 2 % below it so.
+// on edge bc, or a vertex itself, with v and w quotients over one denominator,
+// which the first region whose condition holds gives (selected from the last to
+// the first; a negative denominator marks what starts from b, or is c).  A
+// condition is one compare of a minimum: comparisons combined in scalar registers
+// left a wave waiting on the scalar unit for most of the 1,500 cycles a triangle
+// took.
+// Over grids of an arm's links, against double precision: with plain cross terms
+// the face's point strayed along the face by up to 2 um beside thin triangles, and
+// bc's as a + v ab + w ac rounds twice and leaves the edge; root mean square error
+// 3.30e-9 m (3.11e-9 where every region has a division, products and sums of its
+// own) and 6e-7 at worst, 2 um from the surface.  3.02e-9 and 6e-8 so, for 4 % of a
+// grid's time.
 __device__ inline float dist2_point_triangle(V3 p, V3 a, V3 b, V3 c) {
+    constexpr float kFromB = -1.0f, kAtC = -3e38f;   // denominators that mark a vertex
     const V3 ab = sub(b, a), ac = sub(c, a), ap = sub(p, a), bp = sub(p, b), cp = sub(p, c);
     const float d1 = fdot(ab, ap), d2 = fdot(ac, ap);
     const float d3 = fdot(ab, bp), d4 = fdot(ac, bp);
     const float d5 = fdot(ab, cp), d6 = fdot(ac, cp);
-    const float vc = fmaf(d1, d4, -(d3 * d2));
-    const float vb = fmaf(d5, d2, -(d1 * d6));
-    const float va = fmaf(d3, d6, -(d5 * d4));
+    const float vc = diff_of_products(d1, d4, d3, d2);
+    const float vb = diff_of_products(d5, d2, d1, d6);
+    const float va = diff_of_products(d3, d6, d5, d4);
     const float e43 = d4 - d3, e56 = d5 - d6, s = va + vb + vc;
     // the face; a degenerate triangle (s <= 0) takes a: its edges come first
     float v = vb, w = vc, den = s;
@@ -84,16 +96,21 @@ __device__ inline float dist2_point_triangle(V3 p, V3 a, V3 b, V3 c) {
     };
     take(s <= 0.0f, 0.0f, 0.0f, 1.0f);
     take(fminf(-va, fminf(e43, e56)) >= 0.0f, 0.0f, -e43, -(e43 + e56));   // edge bc
-    take(fminf(-vb, fminf(d2, -d6)) >= 0.0f, 0.0f, d2, d2 - d6);      // edge ac
-    take(fminf(d6, -e56) >= 0.0f, 0.0f, 1.0f, 1.0f);                  // c
-    take(fminf(-vc, fminf(d1, -d3)) >= 0.0f, d1, 0.0f, d1 - d3);      // edge ab
-    take(fminf(d3, -e43) >= 0.0f, 1.0f, 0.0f, 1.0f);                  // b
-    take(fmaxf(d1, d2) <= 0.0f, 0.0f, 0.0f, 1.0f);                    // a
+    take(fminf(-vb, fminf(d2, -d6)) >= 0.0f, 0.0f, d2, d2 - d6);           // edge ac
+    take(fminf(d6, -e56) >= 0.0f, 0.0f, 0.0f, kAtC);                       // c
+    take(fminf(-vc, fminf(d1, -d3)) >= 0.0f, d1, 0.0f, d1 - d3);           // edge ab
+    take(fminf(d3, -e43) >= 0.0f, 0.0f, 0.0f, kFromB);                     // b
+    take(fmaxf(d1, d2) <= 0.0f, 0.0f, 0.0f, 1.0f);                         // a
+    // quotients rounded as divisions, from one reciprocal (Markstein)
     const float inv = 1.0f / den;
-    v *= inv;
-    w *= inv;
-    const bool bc = den < 0.0f;
-    const V3 o = bc ? b : a, e = bc ? sub(c, b) : ac;
+    auto over_den = [&](float x) {
+        const float q = x * inv;
+        return fmaf(fmaf(-q, den, x), inv, q);
+    };
+    v = over_den(v);
+    w = over_den(w);
+    const bool from_b = den < 0.0f;
+    const V3 o = den == kAtC ? c : from_b ? b : a, e = from_b ? sub(c, b) : ac;
     // the point itself rounds with the mesh's size, p - o would with p's distance
     const V3 d = sub(p, {fmaf(w, e.x, fmaf(v, ab.x, o.x)), fmaf(w, e.y, fmaf(v, ab.y, o.y)),
                          fmaf(w, e.z, fmaf(v, ab.z, o.z))});
