@@ -30,7 +30,17 @@ namespace {
 
 using namespace lsdf;
 
-constexpr int kBlock = 512;
+// Threads of a workgroup.  A launch of few workgroups takes small ones: each SIMD
+// then has one wave to issue for instead of two, on twice the CUs.  One that fills
+// the chip takes large ones, as every workgroup stages the mesh for itself and two
+// are all that fit a CU; so does one with a mesh that small ones stage in more than
+// one go.  In us, with 512 and 256 threads: 31 triangles that are not closed on 16^3
+// nodes 34.5 and 30.1 (8 and 16 workgroups), 63 on 32^3 53.9 and 46.2, their labels
+// at 500 points 56.2 and 44.4; a box on 16^3 14.5 and 13.8, closed 256 triangles on
+// 32^3 46.0 and 44.2; but on 64^3, 1,024 workgroups of 256, a box 18.5 and 28.4, and
+// closed 512 triangles on 32^3 71.4 and 73.5.
+constexpr int kBlock = 512, kSmallBlock = 256;
+constexpr int64_t kMostSmall = 256;   // small workgroups of a launch: one a CU
 constexpr int kWavesPerSimd = 4;   // two workgroups a CU: 128 registers a lane, 80 KB of LDS a workgroup
 
 struct BuildArgs {
@@ -210,9 +220,10 @@ __device__ inline int vertex_index(const BuildArgs& p, int k) { return min(max(p
 // Edge sums of part comp into s.loose: over vertex indices, or over vertex
 // positions (a part whose triangles repeat their vertices).  The whole
 // workgroup, between barriers of the caller's.
+template <int BLOCK>
 __device__ void edge_sums(const BuildArgs& p, MeshLds& s, int comp, bool positions) {
     uint32_t sum[2] = {0u, 0u};
-    for (int t = p.comp_first[comp] + threadIdx.x; t < p.comp_first[comp + 1]; t += kBlock) {
+    for (int t = p.comp_first[comp] + threadIdx.x; t < p.comp_first[comp + 1]; t += BLOCK) {
         uint32_t h[2][3];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
@@ -247,9 +258,10 @@ __device__ inline int padded_slots(int n) { return (n + kSuper - 1) / kSuper * k
 // slots from slot0 (a multiple of kSuper) on, with their boxes.  The last
 // outer box's empty slots repeat the last triangle.  The whole workgroup,
 // between barriers of the caller's; returns the slots taken.
+template <int BLOCK>
 __device__ int stage_triangles(const BuildArgs& p, MeshLds& s, int comp, int first, int cnt, int slot0) {
     const int padded = padded_slots(cnt);
-    for (int k = threadIdx.x; k < padded; k += kBlock) {   // whole outer boxes: 16 adjacent lanes
+    for (int k = threadIdx.x; k < padded; k += BLOCK) {   // whole outer boxes: 16 adjacent lanes
         const int t = p.comp_first[comp] + first + min(k, cnt - 1);
         float v[9];
 #pragma unroll
@@ -457,20 +469,21 @@ __device__ inline void nearest(MeshLds& s, int slots, V3 pt, bool go, int lo, in
 
 // Signed distance of pt to the mesh.  Every lane of the workgroup takes part
 // in staging; lanes with want == false take no triangles.
+template <int BLOCK>
 __device__ inline float mesh_sdf(const BuildArgs& p, MeshLds& s, V3 pt, bool want) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int slots = 0;
     for (int c = 0; c < p.ncomp; ++c) slots += padded_slots(p.comp_first[c + 1] - p.comp_first[c]);
     const bool whole = slots <= kStage;   // the mesh is staged once, else a part's kStage triangles at a time
-    for (int k = threadIdx.x; k < 3 * LSDF_MAX_COMPONENTS; k += kBlock) {
+    for (int k = threadIdx.x; k < 3 * LSDF_MAX_COMPONENTS; k += BLOCK) {
         s.part_lo[k / 3][k % 3] = 0xffffffffu;
         s.part_hi[k / 3][k % 3] = 0u;
         if (k < 2 * LSDF_MAX_COMPONENTS) s.loose[k / 2][k % 2] = 0u;
     }
     __syncthreads();
     for (int c = 0, at = 0; c < p.ncomp; ++c) {
-        edge_sums(p, s, c, false);
-        if (whole) at += stage_triangles(p, s, c, 0, p.comp_first[c + 1] - p.comp_first[c], at);
+        edge_sums<BLOCK>(p, s, c, false);
+        if (whole) at += stage_triangles<BLOCK>(p, s, c, 0, p.comp_first[c + 1] - p.comp_first[c], at);
     }
     __syncthreads();
     uint32_t open = 0;   // parts whose indices do not cancel: their positions may
@@ -481,7 +494,7 @@ __device__ inline float mesh_sdf(const BuildArgs& p, MeshLds& s, V3 pt, bool wan
         if (threadIdx.x < 2 * LSDF_MAX_COMPONENTS) s.loose[threadIdx.x / 2][threadIdx.x % 2] = 0u;
         __syncthreads();
         for (int c = 0; c < p.ncomp; ++c)
-            if (open >> c & 1) edge_sums(p, s, c, true);
+            if (open >> c & 1) edge_sums<BLOCK>(p, s, c, true);
         __syncthreads();
     }
 
@@ -497,7 +510,7 @@ __device__ inline float mesh_sdf(const BuildArgs& p, MeshLds& s, V3 pt, bool wan
             const int cnt = min(step, nt - first);
             if (!whole) {
                 __syncthreads();   // the triangles staged before are done with
-                stage_triangles(p, s, c, first, cnt, 0);
+                stage_triangles<BLOCK>(p, s, c, first, cnt, 0);
                 __syncthreads();
             }
             if (!closed) {
@@ -563,7 +576,7 @@ __device__ inline float mesh_sdf(const BuildArgs& p, MeshLds& s, V3 pt, bool wan
             const int nt = p.comp_first[c + 1] - p.comp_first[c];
             const int cnt = min(kStage, nt - first);
             __syncthreads();
-            hi = stage_triangles(p, s, c, first, cnt, 0);
+            hi = stage_triangles<BLOCK>(p, s, c, first, cnt, 0);
             __syncthreads();
             go = want && (inside == 0 || (inside >> c & 1));
             last = first + cnt == nt;
@@ -588,31 +601,32 @@ struct BuildBatch {
 
 // Grid nodes: node idx of the grid described by p.
 // y: the link of the batch.
-__global__ __launch_bounds__(kBlock, kWavesPerSimd) void build_sdf_kernel(BuildBatch batch) {
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK, kWavesPerSimd * BLOCK / kBlock) void build_sdf_kernel(BuildBatch batch) {
     __shared__ MeshLds lds;
     const BuildArgs& p = batch.link[blockIdx.y];
     if (blockIdx.x >= (unsigned)p.blocks) return;   // the batch's largest grid sets the launch
-    int64_t kx, ky, kz;
+    uint32_t kx, ky, kz;   // (fewer than 2^32 threads: 32-bit quotients)
     if (p.bricks) {
         // a wave takes 4 x 4 x 4 nodes, which want the same few groups of triangles
-        const int bx = (p.n[0] + 3) / 4, by = (p.n[1] + 3) / 4;
-        const int64_t brick = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
-        const int64_t row = brick / bx;
-        const int t = threadIdx.x & 63;
+        const uint32_t bx = ((uint32_t)p.n[0] + 3) / 4, by = ((uint32_t)p.n[1] + 3) / 4;
+        const uint32_t brick = blockIdx.x * (BLOCK / 64) + (threadIdx.x >> 6);
+        const uint32_t row = brick / bx, layer = row / by;
+        const uint32_t t = threadIdx.x & 63;
         kx = 4 * (brick - row * bx) + (t & 3);
-        ky = 4 * (row % by) + (t >> 2 & 3);
-        kz = 4 * (row / by) + (t >> 4);
+        ky = 4 * (row - layer * by) + (t >> 2 & 3);
+        kz = 4 * layer + (t >> 4);
     } else {
-        const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-        kx = k % p.n[0];
-        ky = (k / p.n[0]) % p.n[1];
-        kz = k / ((int64_t)p.n[0] * p.n[1]);
+        const uint32_t k = blockIdx.x * BLOCK + threadIdx.x, row = k / (uint32_t)p.n[0];
+        kx = k - row * (uint32_t)p.n[0];
+        kz = row / (uint32_t)p.n[1];
+        ky = row - kz * (uint32_t)p.n[1];
     }
-    const bool active = kx < p.n[0] && ky < p.n[1] && kz < p.n[2];
-    const int64_t idx = (kz * p.n[1] + ky) * p.n[0] + kx;
+    const bool active = kx < (uint32_t)p.n[0] && ky < (uint32_t)p.n[1] && kz < (uint32_t)p.n[2];
+    const int64_t idx = ((int64_t)kz * p.n[1] + ky) * p.n[0] + kx;
     const V3 pt = {fmaf((float)kx, p.h[0], p.lo[0]), fmaf((float)ky, p.h[1], p.lo[1]),
                    fmaf((float)kz, p.h[2], p.lo[2])};
-    const float sdf = mesh_sdf(p, lds, pt, active);
+    const float sdf = mesh_sdf<BLOCK>(p, lds, pt, active);
     if (active) {
         // one rounding, to nearest even, into the storage type
         if (p.dtype == LSDF_BF16)
@@ -636,13 +650,13 @@ static_assert(sizeof(LabelBatch) <= 4096, "kernel arguments of a batch");
 
 // Labels: the grid value inside the grid box, the exact distance outside.
 // y: the link of the batch.
-template <bool CUBIC, int DT>
-__global__ __launch_bounds__(kBlock, kWavesPerSimd) void label_kernel(LabelBatch p) {
+template <bool CUBIC, int DT, int BLOCK>
+__global__ __launch_bounds__(BLOCK, kWavesPerSimd * BLOCK / kBlock) void label_kernel(LabelBatch p) {
     __shared__ MeshLds lds;
     const int link = blockIdx.y;
     const LinkGrid& lg = p.lg[link];
     const float* points = p.points[link];
-    const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t j = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
     const bool active = j < p.N;
     const int64_t jj = active ? j : p.N - 1;
     const V3 pt = {points[3 * jj + 0], points[3 * jj + 1], points[3 * jj + 2]};
@@ -653,7 +667,7 @@ __global__ __launch_bounds__(kBlock, kWavesPerSimd) void label_kernel(LabelBatch
     const bool exact = active && !(g < INFINITY);
     float v = g;
     if (__syncthreads_or(exact)) {
-        const float e = mesh_sdf(p.mesh[link], lds, pt, exact);
+        const float e = mesh_sdf<BLOCK>(p.mesh[link], lds, pt, exact);
         if (exact) v = e;
     }
     if (active) p.out[link][j] = v;
@@ -662,6 +676,11 @@ __global__ __launch_bounds__(kBlock, kWavesPerSimd) void label_kernel(LabelBatch
 }  // namespace
 
 namespace {
+
+// Does a launch of `blocks` small workgroups over n meshes take them?
+bool small_blocks(int64_t blocks, int32_t n, const int32_t* nt) {
+    return blocks <= kMostSmall && *std::max_element(nt, nt + n) <= kSmallBlock;
+}
 
 int mesh_args(const float* verts, int32_t nv, const int32_t* tris, int32_t nt, const int32_t* comp_first,
               int32_t ncomp, BuildArgs* p) {
@@ -725,15 +744,18 @@ LSDF_API int lsdf_sdf_labels_links(int32_t n, const float* const* verts, const i
         if (!grid_buf || !points[i] || !out[i]) return fail(LSDF_E_INVALID_ARG, "sdf_labels: NULL device pointer");
     a.grid = grid_buf;
     a.N = N;
-    const dim3 grid((unsigned)((N + kBlock - 1) / kBlock), (unsigned)n);
+    const bool small = small_blocks(n * ((N + kSmallBlock - 1) / kSmallBlock), n, nt);
+    const int block = small ? kSmallBlock : kBlock;
+    const dim3 grid((unsigned)((N + block - 1) / block), (unsigned)n);
     hipStream_t st = as_stream(stream);
+    auto launch = [&](auto few, auto many) { hipLaunchKernelGGL(small ? few : many, grid, dim3(block), 0, st, a); };
     switch (grids[0].dtype * 2 + (cubic ? 1 : 0)) {
-        case LSDF_F32 * 2 + 1: hipLaunchKernelGGL((label_kernel<true, LSDF_F32>), grid, dim3(kBlock), 0, st, a); break;
-        case LSDF_F32 * 2: hipLaunchKernelGGL((label_kernel<false, LSDF_F32>), grid, dim3(kBlock), 0, st, a); break;
-        case LSDF_BF16 * 2 + 1: hipLaunchKernelGGL((label_kernel<true, LSDF_BF16>), grid, dim3(kBlock), 0, st, a); break;
-        case LSDF_BF16 * 2: hipLaunchKernelGGL((label_kernel<false, LSDF_BF16>), grid, dim3(kBlock), 0, st, a); break;
-        case LSDF_F16 * 2 + 1: hipLaunchKernelGGL((label_kernel<true, LSDF_F16>), grid, dim3(kBlock), 0, st, a); break;
-        default: hipLaunchKernelGGL((label_kernel<false, LSDF_F16>), grid, dim3(kBlock), 0, st, a); break;
+        case LSDF_F32 * 2 + 1: launch(label_kernel<true, LSDF_F32, kSmallBlock>, label_kernel<true, LSDF_F32, kBlock>); break;
+        case LSDF_F32 * 2: launch(label_kernel<false, LSDF_F32, kSmallBlock>, label_kernel<false, LSDF_F32, kBlock>); break;
+        case LSDF_BF16 * 2 + 1: launch(label_kernel<true, LSDF_BF16, kSmallBlock>, label_kernel<true, LSDF_BF16, kBlock>); break;
+        case LSDF_BF16 * 2: launch(label_kernel<false, LSDF_BF16, kSmallBlock>, label_kernel<false, LSDF_BF16, kBlock>); break;
+        case LSDF_F16 * 2 + 1: launch(label_kernel<true, LSDF_F16, kSmallBlock>, label_kernel<true, LSDF_F16, kBlock>); break;
+        default: launch(label_kernel<false, LSDF_F16, kSmallBlock>, label_kernel<false, LSDF_F16, kBlock>); break;
     }
     return check_launch("sdf_labels");
 }
@@ -755,7 +777,8 @@ LSDF_API int lsdf_build_link_sdfs(int32_t n, const float* const* verts, const in
     if (!verts || !nv || !tris || !nt || !comp_first || !ncomp)
         return fail(LSDF_E_INVALID_ARG, "build_link_sdf: NULL array");
     BuildBatch batch{};
-    int64_t most = 0;
+    int64_t lanes[LSDF_MAX_LINKS], all = 0;   // all: workgroups of kSmallBlock
+    int32_t most = 0;
     for (int i = 0; i < n; ++i) {
         BuildArgs& p = batch.link[i];
         const lsdf_grid& desc = grids[i];
@@ -775,11 +798,17 @@ LSDF_API int lsdf_build_link_sdfs(int32_t n, const float* const* verts, const in
         // bricks unless their padding would leave more than half the lanes idle (thin grids)
         // or take 2^32 threads, which no launch may have (2 x 1,024 x 2^20 nodes)
         const int64_t bricks = (int64_t)((p.n[0] + 3) / 4) * ((p.n[1] + 3) / 4) * ((p.n[2] + 3) / 4);
-        p.bricks = bricks * 64 <= 2 * nodes && bricks * 64 < (int64_t)1 << 32;
-        const int64_t blocks = ((p.bricks ? bricks * 64 : nodes) + kBlock - 1) / kBlock;
-        p.blocks = (int32_t)blocks;   // nodes <= 2^31
-        most = std::max(most, blocks);
+        p.bricks = bricks * 64 <= 2 * nodes && bricks * 64 <= ((int64_t)1 << 32) - kBlock;
+        lanes[i] = p.bricks ? bricks * 64 : nodes;
+        all += (lanes[i] + kSmallBlock - 1) / kSmallBlock;
     }
-    hipLaunchKernelGGL(build_sdf_kernel, dim3((unsigned)most, (unsigned)n), dim3(kBlock), 0, as_stream(stream), batch);
+    const bool small = small_blocks(all, n, nt);
+    const int block = small ? kSmallBlock : kBlock;
+    for (int i = 0; i < n; ++i) {
+        batch.link[i].blocks = (int32_t)((lanes[i] + block - 1) / block);   // lanes < 2^32
+        most = std::max(most, batch.link[i].blocks);
+    }
+    const auto kernel = small ? build_sdf_kernel<kSmallBlock> : build_sdf_kernel<kBlock>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)most, (unsigned)n), dim3(block), 0, as_stream(stream), batch);
     return check_launch("build_link_sdf");
 }
