@@ -534,16 +534,17 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_num_sgpr(80))) void q
     for (;;) {
         collect<DEAL>(p, blocks, groups, plan, w, lane, sh);
         if (w.has && lane == 0) atomicAdd(&sh.open, 1);
+        __syncthreads();
+        const int nd = sh.listed, nt = sh.tiles;
+        const bool left = sh.open > 0;
+        const bool dry = DEAL && sh.taken >= sh.run;   // the run is through
+        if (nd == 0 && !left && (!DEAL || (dry && given >= hi))) break;
         if (threadIdx.x < (unsigned)p.L) {
             const LinkGrid& lg = p.link[threadIdx.x];
             sh.grid[threadIdx.x] =
                 GridView{{lg.half[0], lg.half[1], lg.half[2]}, {lg.n[0], lg.n[1], lg.n[2]}, (int64_t)lg.offset};
         }
         __syncthreads();
-        const int nd = sh.listed, nt = sh.tiles;
-        const bool left = sh.open > 0;
-        const bool dry = DEAL && sh.taken >= sh.run;   // the run is through
-        if (nd == 0 && !left && (!DEAL || (dry && given >= hi))) break;
         int64_t next_q = hi;
         if (dry && given < hi && threadIdx.x == 0) {   // fetched while the list is worked off
             const int64_t n = atomicAdd(&reinterpret_cast<PlanEnd*>(&plan[p.K])->next[xcd], 1);
