@@ -17,8 +17,8 @@
 // first), and the wave's (point, group) pairs go through queues in LDS, 64 at
 // a time, so that lanes with few groups do not wait for lanes with many.  Seven
 // 64^3 grids of 268 to 524 triangles a link: 4.40 ms of kernels with every
-// triangle for every node, 0.465 ms now; the labels of 7 x 262,144 samples
-// 4.70 -> 0.306 ms (57 % VALU busy).  The costliest waves are those near a
+// triangle for every node, 0.492 ms now (58 % VALU busy); the labels of 7 x 262,144
+// samples 4.70 -> 0.326 ms (90 %).  The costliest waves are those near a
 // part's axis, where every triangle is about as near as the next; the calls
 // that take several links run them in one launch, so one link's last waves
 // overlap the next link's.
